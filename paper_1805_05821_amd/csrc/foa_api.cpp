@@ -163,6 +163,20 @@ hipEvent_t take_event(foa_ctx_s *c) {
   return e;
 }
 
+// Whether passes B and C (nw wavefronts per workgroup) reduce the column sums
+// of the G workgroups of the pass before by themselves instead of a reduce
+// kernel between: by the number of sums a lane then adds up (columns in chunks
+// of 64 lanes, the other wavefronts split the rows).  Measured, us per push
+// fused / with reduce kernels: FP32, 4 wavefronts, 4133 x 64 (17 sums) 19.4 /
+// 21.8, 16384 x 100 (up to 128, fused to 32) 23.3 / 23.4; FP64, 16 wavefronts,
+// 4096 x 64 (4) 20.9 / 22.4, 16384 x 100 (32) 25.8 / 24.9, to 16 24.5 / 24.9.
+static bool pass_reduces(int nw, int G, int j) {
+  const int R = (j + 63) / 64;
+  if (R > nw) return false;
+  const int S = nw / R;
+  return (G + S - 1) / S <= (nw == 4 ? 32 : 16);
+}
+
 // Launch one row pass, bracketed by timing events when profiling is on.
 static hipError_t timed_pass(foa_ctx_s *c, int mode, bool v64, bool x64, bool pref, int G,
                              const PassArgs &pa, double alg_bytes) {
@@ -245,17 +259,43 @@ foa_status enqueue_push(foa_ctx_s *c, const void *x, bool x_f64) {
       return hip_err(c, e, "pass init");
     if ((e = launch_finalize_init(sa, s)) != hipSuccess) return hip_err(c, e, "finalize init");
   } else {
+    const bool fuse = pass_reduces(pass_nw(v64, c->nw, j), G, j);
+    if (fuse) pa.rstride = j;
     if ((e = timed_pass(c, PM_A, v64, x_f64, c->prefetch, G, pa, vbytes + nv * sX)) != hipSuccess)
       return hip_err(c, e, "pass A");
-    if ((e = launch_reduce(1, sa, s)) != hipSuccess) return hip_err(c, e, "reduce A");
+    if (fuse) {
+      // passes B and C reduce the sums of the pass before; B leaves its own in
+      // the second partial-sum area
+      pa.sigma = sa.sigma;
+      pa.h = sa.h;
+      pa.coefw = sa.coefB;
+      pa.hsum = sa.s;
+      pa.xn2 = &sa.st->xn2;
+      pa.rG = G;
+      pa.rpart = c->part;
+      pa.part = reinterpret_cast<double *>(static_cast<char *>(c->ws) + c->L.ls_part1);
+    } else if ((e = launch_reduce(1, sa, s)) != hipSuccess) {
+      return hip_err(c, e, "reduce A");
+    }
     if ((e = timed_pass(c, PM_B, v64, x_f64, c->prefetch, G, pa, vbytes)) != hipSuccess)
       return hip_err(c, e, "pass B");
-    if ((e = launch_reduce(2, sa, s)) != hipSuccess) return hip_err(c, e, "reduce B");
+    if (fuse) {
+      pa.rpart = pa.part;
+      sa.h = sa.s;  // pass C leaves h + s there
+    } else if ((e = launch_reduce(2, sa, s)) != hipSuccess) {
+      return hip_err(c, e, "reduce B");
+    }
     if ((e = timed_pass(c, PM_C, v64, x_f64, c->prefetch, G, pa, vbytes + nv * sV)) != hipSuccess)
       return hip_err(c, e, "pass C");
-    if ((e = launch_finalize(sa, s)) != hipSuccess) return hip_err(c, e, "finalize");
+    // one workgroup up to 256 columns: FP64 2^20 x 200, finalize and next b of
+    // their own 4.8 + 9.4 us per push, together 5.5 us
+    if (j <= kFinNextCols) {
+      if ((e = launch_finalize_next(sa, s)) != hipSuccess) return hip_err(c, e, "finalize");
+    } else if ((e = launch_finalize(sa, s)) != hipSuccess) {
+      return hip_err(c, e, "finalize");
+    }
   }
-  if ((e = launch_nextb(sa, s)) != hipSuccess) return hip_err(c, e, "next b");
+  if ((j == 0 || j > kFinNextCols) && (e = launch_nextb(sa, s)) != hipSuccess) return hip_err(c, e, "next b");
   c->q_host = j + 1;
   c->mirror_valid = false;
   c->dmd.valid = false;

@@ -42,6 +42,32 @@ __device__ __forceinline__ double xor_sum(double v) {
   return __builtin_bit_cast(double, p) + __builtin_bit_cast(double, q);
 }
 
+// A double moved between lanes by a DPP control (VALU, no LDS traffic).
+template <int CTRL>
+__device__ __forceinline__ double dpp_mov(double v) {
+  const u32x2 b = __builtin_bit_cast(u32x2, v);
+  const u32x2 r = u32x2{(unsigned)__builtin_amdgcn_update_dpp((int)b.x, (int)b.x, CTRL, 0xf, 0xf, true),
+                        (unsigned)__builtin_amdgcn_update_dpp((int)b.y, (int)b.y, CTRL, 0xf, 0xf, true)};
+  return __builtin_bit_cast(double, r);
+}
+
+// Sum over the L = 16, 32 or 64 consecutive lanes a lane belongs to, in every
+// lane: the xor butterfly of distances 1, 2, 4, ... in that order (bitwise the
+// same sums), on DPP moves and lane swaps.  Once the lanes of a quad agree, the
+// mirror of a half row brings the other quad's value, and the mirror of a row
+// the other half's.
+template <int L>
+__device__ __forceinline__ double lanes_sum(double v) {
+  static_assert(L == 16 || L == 32 || L == 64, "row, half-wave or wave");
+  v += dpp_mov<0xB1>(v);   // quad_perm 1,0,3,2
+  v += dpp_mov<0x4E>(v);   // quad_perm 2,3,0,1
+  v += dpp_mov<0x141>(v);  // row_half_mirror
+  v += dpp_mov<0x140>(v);  // row_mirror
+  if constexpr (L >= 32) v = xor_sum<16>(v);
+  if constexpr (L >= 64) v = xor_sum<32>(v);
+  return v;
+}
+
 // A value that is the same in every lane, moved to scalar registers.
 template <typename T>
 __device__ __forceinline__ T uniform(T v) {
@@ -192,7 +218,71 @@ __device__ __forceinline__ void xst(double *p, double v) {
     *p = v;
 }
 
-template <typename TV, typename TX, int NW, int QW, int MODE, bool PREF, bool COH = false>
+// Column sums of the preceding pass, reduced by every workgroup for itself at
+// the start of pass B (MODE PM_B: h = sigma o t) or C (PM_C: s = sigma o t):
+// the pass's last coefficient vector sigma o (sigma o t) goes to s_c, and one
+// workgroup (`first`) also writes what later kernels read: h and sigma o h, and
+// the reduced ||psi||^2 (PM_B), or h + s (PM_C, into a.hsum).  The sums come as
+// rows of rstride columns, one row per workgroup of that pass: a lane owns a
+// column, a wavefront a slice of the rows (16 loads in flight), and the
+// slices are added in order through s_p.  Bound: latency (a launch of its own
+// costs 2.6-2.9 us at any small size).  The pass's own sums go to another buffer
+// than a.rpart, which slower workgroups may still be reading.
+template <int NW, int JCAP, int MODE>
+__device__ __forceinline__ void reduce_prologue(const PassArgs &a, double *s_c, double *s_p, bool first) {
+  constexpr int U = 16;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int j = a.j, G = a.rG;
+  const int R = (j + 63) / 64;  // column chunks, at most NW
+  const int S = NW / R;         // row slices
+  const int sl = wave / R, c = (wave - sl * R) * 64 + lane;
+  double t = 0.0;
+  if (sl < S) {
+    const double *pc = a.rpart + (c < j ? c : j - 1);
+    for (int g = sl; g < G; g += S * U) {
+      double v[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) v[u] = g + u * S < G ? pc[(size_t)(g + u * S) * a.rstride] : 0.0;
+#pragma unroll
+      for (int u = 0; u < U; ++u) t += v[u];
+    }
+  }
+  s_p[threadIdx.x] = t;
+  double xn = 0.0;
+  if (MODE == PM_B && first && wave == NW - 1) {
+    for (int g = lane; g < G; g += 64) xn += a.partn[g];
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < JCAP; i += NW * 64) {
+    double co = 0.0;
+    if (i < j) {
+      double v = 0.0;
+      for (int k = 0; k < S; ++k) v += s_p[k * R * 64 + i];
+      const double sg = a.sigma[i];
+      v *= sg;
+      co = sg * v;
+      if (first) {
+        if (MODE == PM_B) {
+          a.h[i] = v;
+          a.coefw[i] = co;
+        } else {
+          a.hsum[i] = a.h[i] + v;
+        }
+      }
+    }
+    s_c[i] = co;
+  }
+  if (MODE == PM_B && first && wave == NW - 1) {
+    xn = lanes_sum<64>(xn);
+    if (lane == 0) *a.xn2 = xn;
+  }
+}
+
+// RED: the sums may be laid out for, and reduced by, the next pass; CHECK: the
+// pass returns if the stream is not active.
+template <typename TV, typename TX, int NW, int QW, int MODE, bool PREF, bool COH = false, bool RED = false,
+          bool CHECK = false>
 __device__ __forceinline__ void row_pass_body(const PassArgs &a, int64_t pstart, int64_t pend, int64_t pstep,
                                               int slot, double *lds) {
   // w_A, w_B and w_C are each rounded to FP64 before the next subtraction,
@@ -232,13 +322,6 @@ __device__ __forceinline__ void row_pass_body(const PassArgs &a, int64_t pstart,
   const int rg = lane % LPC;
   const int j = a.j;
 
-  __syncthreads();  // the previous call of this workgroup may still read LDS
-#pragma unroll
-  for (int k = 0; k < NC; ++k)
-    for (int c = tid; c < JCAP; c += NW * 64) s_coef[k][c] = (c < j) ? xld<COH>(a.coef[K0 + k] + c) : 0.0;
-  const double scale = (MODE == PM_INIT) ? 1.0 : uniform(a.st->scaleA);
-  __syncthreads();
-
   const int cbase = wave * CPW + cs;  // column of this lane in group 0
   // byte offset of this lane's 16-byte fragment of group g: goff0 + g * GBYTES
   const unsigned goff0 = (unsigned)((wave * CPW * PANEL + lane * EPL) * sizeof(TV));
@@ -272,9 +355,37 @@ __device__ __forceinline__ void row_pass_body(const PassArgs &a, int64_t pstart,
     }
   };
 
+  // The coefficients (one per thread and vector) and the first tile are fetched
+  // together, the coefficients first: loads complete in order, and theirs are
+  // needed in LDS before the tile is (100037 x 128, FP32: pass A 12.1 us with
+  // the tile behind them, 9.9 us so).
+  static_assert(NC == 0 || JCAP <= NW * 64, "one coefficient per thread");
+  const bool red = RED && a.rpart != nullptr;
+  double cv[NCS];
+#pragma unroll
+  for (int k = 0; k < NC; ++k) {
+    if (RED && k == NC - 1 && red) continue;  // the reduction below writes it
+    cv[k] = xld<COH>(a.coef[K0 + k] + (tid < j ? tid : j - 1));
+  }
+  const double scale = (MODE == PM_INIT) ? 1.0 : uniform(a.st->scaleA);
   int64_t p = pstart;
-  if (PREF && p < pend) {
-    load_tile(p, t, tile_bytes);
+  if (PREF) load_tile(p < pend ? p : pstart, t, p < pend ? tile_bytes : 0u);
+  // a stopped stream's kernels read and leave (the status is fetched with the
+  // rest: a round trip of its own before them costs every pass 0.5 us or more)
+  if (CHECK && uniform(a.st->status) != ST_ACTIVE) return;
+
+  __syncthreads();  // the previous call of this workgroup may still read LDS
+#pragma unroll
+  for (int k = 0; k < NC; ++k) {
+    if (RED && k == NC - 1 && red) continue;
+    if (tid < JCAP) s_coef[k][tid] = tid < j ? cv[k] : 0.0;
+  }
+  if constexpr (RED) {
+    // the row-sum buffers are free until the first panel
+    if (red) reduce_prologue<NW, JCAP, MODE>(a, s_coef[NC - 1], &s_red[0][0][0][0], slot == 0);
+  }
+  __syncthreads();
+  if (PREF) {
     // Complete the first tile before the loop: otherwise its pending loads
     // merge with the loop back edge and every iteration waits for the
     // prefetched tile before phase 1.
@@ -404,16 +515,16 @@ __device__ __forceinline__ void row_pass_body(const PassArgs &a, int64_t pstart,
   if (HAS_P2) {
 #pragma unroll
     for (int g = 0; g < QW; ++g) {
-      double v = acc[g];
-#pragma unroll
-      for (int m = 1; m < LPC; m <<= 1) v += xor_shfl(v, m);
+      const double v = lanes_sum<LPC>(acc[g]);
       const int c = cbase + g * GSTRIDE;
-      if (rg == 0 && c < j) xst<COH>(a.part + (size_t)c * a.ldg + slot, v);
+      if (rg == 0 && c < j) {
+        // one row per workgroup where the next pass sums the columns itself
+        xst<COH>(a.part + (RED && a.rstride ? (size_t)slot * a.rstride + c : (size_t)c * a.ldg + slot), v);
+      }
     }
   }
   if (MODE != PM_B) {
-#pragma unroll
-    for (int m = 1; m < 64; m <<= 1) nrm += xor_shfl(nrm, m);
+    nrm = lanes_sum<64>(nrm);
     if (lane == 0) s_nrm[wave] = nrm;
     __syncthreads();
     if (tid == 0) {
@@ -430,18 +541,33 @@ __device__ __forceinline__ void row_pass_body(const PassArgs &a, int64_t pstart,
 // coefB = sigma o h, and the extra wavefront c == j reduces ||psi||^2.
 // MODE 2 (after pass B): s = sigma o t, h += s, coefC = sigma o s.
 // ---------------------------------------------------------------------------
-template <int MODE, bool COH = false>
+// Sum of p[0 .. G) by one wavefront: lane-strided sums in order, then a
+// butterfly, with eight loads in flight per lane (one at a time the 1024
+// partials of a column took 7.2 us).
+template <bool COH>
+__device__ __forceinline__ double strided_sum(const double *p, int G, int lane) {
+  constexpr int U = 8;
+  double t = 0.0;
+  int g = lane;
+  for (; g + 64 * (U - 1) < G; g += 64 * U) {
+    double v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = xld<COH>(p + g + 64 * u);
+#pragma unroll
+    for (int u = 0; u < U; ++u) t += v[u];
+  }
+  for (; g < G; g += 64) t += xld<COH>(p + g);
+  return lanes_sum<64>(t);
+}
+
+template <int MODE, bool COH = false, bool CHECK = false>
 __device__ inline void reduce_body(const SmallArgs &a, int c0) {
   const int lane = threadIdx.x & 63;
   const int c = c0 + (threadIdx.x >> 6);
   if (c < a.j) {
-    const double *pc = a.part + (size_t)c * a.ldg;
-    double t = 0.0;
-    for (int g = lane; g < a.G; g += 64) t += xld<COH>(pc + g);
-#pragma unroll
-    for (int m = 1; m < 64; m <<= 1) t += xor_shfl(t, m);
-    if (lane == 0) {
-      const double sg = a.sigma[c];
+    const double sg = a.sigma[c];
+    const double t = strided_sum<COH>(a.part + (size_t)c * a.ldg, a.G, lane);
+    if (lane == 0 && (!CHECK || a.st->status == ST_ACTIVE)) {
       const double v = sg * t;
       if (MODE == 1) {
         xst<COH>(a.h + c, v);
@@ -453,11 +579,8 @@ __device__ inline void reduce_body(const SmallArgs &a, int c0) {
       }
     }
   } else if (MODE == 1 && c == a.j) {
-    double t = 0.0;
-    for (int g = lane; g < a.G; g += 64) t += xld<COH>(a.partn + g);
-#pragma unroll
-    for (int m = 1; m < 64; m <<= 1) t += xor_shfl(t, m);
-    if (lane == 0) xst<COH>(&a.st->xn2, t);
+    const double t = strided_sum<COH>(a.partn, a.G, lane);
+    if (lane == 0 && (!CHECK || a.st->status == ST_ACTIVE)) xst<COH>(&a.st->xn2, t);
   }
 }
 
@@ -608,6 +731,110 @@ __device__ inline void nextb_body_t(const SmallArgs &a, int chunk0) {
 }
 
 __device__ inline void nextb_body(const SmallArgs &a, int chunk) { nextb_body_t<256>(a, chunk); }
+
+// finalize_body and nextb_body in one workgroup of NT threads, for bases of up
+// to kFinNextCols columns: the new columns of H_bar and beta stay in LDS, where
+// the next push's partial beta column takes them from, and every thread works
+// out the status for itself, so one barrier stands between the loads and the
+// products.  Bound: latency; at 64 columns 4.4 us, the two kernels 3.8 + 3.1 us
+// and a launch more.  64 rows x (NT / 64 / row chunks) l-slices, slices summed in order.
+template <int NT>
+__device__ inline void finalize_next_body(const SmallArgs &a) {
+  constexpr int NWV = NT / 64;
+  __shared__ double s_n[NWV];
+  __shared__ double s_h[kFinNextCols + 1], s_b[kFinNextCols + 1];
+  __shared__ double s_p[NT];
+  DevState *st = a.st;
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int j = a.j, J = j + 1;
+  // everything is fetched at once, the status and the first products' part of
+  // H_bar with it: the kernel is a chain of round trips
+  const int status = st->status;
+  const double bjj = a.beta[(size_t)(j - 1) * a.ldB + (j - 1)];
+  const double xn2 = st->xn2, xf = st->xfro2 + xn2, tol = st->tol;
+  // b_i = sum_{l = max(i-1, 0)}^{j-1} H_bar[i, l] beta[l, j], i <= j; the column
+  // l = j - 1 comes from this push.  Wavefront: row chunk and l-slice
+  const int R = (J + 63) / 64, S = NWV / R;
+  const int sl = wave / R, i = (wave - sl * R) * 64 + lane;
+  const bool prod = sl < S && i < j;
+  const int lo = i > 0 ? i - 1 : 0;
+  const int len = prod && j - 1 > lo ? j - 1 - lo : 0;
+  const int a0 = lo + (len * sl) / S, a1 = lo + (len * (sl + 1)) / S;
+  constexpr int U = 8;
+  double v[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) v[u] = a0 + u < a1 ? a.H[(size_t)(a0 + u) * a.ldH + i] : 0.0;
+  const double sgi = sl == 0 && i < j ? a.sigma[i] : 0.0;
+  double t = 0.0;
+  for (int g = tid; g < a.G; g += NT) t += a.partn[g];
+  int bad = 0;
+  for (int c = tid; c < j; c += NT) {
+    const double hi = a.h[c];
+    bad |= !isfinite(hi);
+    s_h[c] = hi;
+    s_b[c] = a.bvec[c] + hi * bjj;  // beta completion
+  }
+  if (status != ST_ACTIVE) {
+    if (tid == 0) st->pushes += 1;
+    return;
+  }
+  t = lanes_sum<64>(t);
+  if (lane == 0) s_n[wave] = t;
+  bad = __syncthreads_or(bad);
+  double wn2 = 0.0;
+#pragma unroll
+  for (int w = 0; w < NWV; ++w) wn2 += s_n[w];
+  const double hn = sqrt(wn2);
+  if (bad || !isfinite(hn) || !isfinite(xn2)) {
+    if (tid == 0) {
+      st->status = ST_NONFINITE;
+      st->pushes += 1;
+    }
+    return;
+  }
+  const bool inv = hn * bjj <= tol * sqrt(xf);
+  for (int c = tid; c < j; c += NT) {
+    a.H[(size_t)(j - 1) * a.ldH + c] = s_h[c];
+    a.beta[(size_t)j * a.ldB + c] = s_b[c];
+  }
+  if (tid == 0) {
+    st->xfro2 = xf;
+    st->hlast = hn;
+    a.H[(size_t)(j - 1) * a.ldH + j] = inv ? 0.0 : hn;
+    a.beta[(size_t)j * a.ldB + j] = inv ? 0.0 : hn * bjj;
+    if (inv) {
+      st->status = ST_INVARIANT;
+    } else {
+      a.sigma[j] = 1.0 / hn;
+      st->q = J;
+      st->scaleA = 1.0 / (hn * bjj);
+    }
+    st->pushes += 1;
+  }
+  if (inv) return;
+  double acc = 0.0;
+#pragma unroll
+  for (int u = 0; u < U; ++u) acc = fma(v[u], s_b[a0 + u < a1 ? a0 + u : 0], acc);
+  int l = a0 + U;
+  for (; l + U <= a1; l += U) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = a.H[(size_t)(l + u) * a.ldH + i];
+#pragma unroll
+    for (int u = 0; u < U; ++u) acc = fma(v[u], s_b[l + u], acc);
+  }
+  for (; l < a1; ++l) acc = fma(a.H[(size_t)l * a.ldH + i], s_b[l], acc);
+  s_p[tid] = acc;
+  __syncthreads();
+  if (sl == 0 && i <= j) {
+    double b = 0.0;
+    for (int k = 0; k < S; ++k) b += s_p[(k * R) * 64 + i];
+    b = fma(i < j ? s_h[i] : hn, s_b[j - 1], b);
+    a.bvec[i] = b;
+    a.coefA[i] = (i < j ? sgi : 1.0 / hn) * b;
+  }
+}
 
 // Reset of one stream: scalar state, and zeros in every small array (the
 // entries of H_bar below the subdiagonal and of beta below the diagonal are

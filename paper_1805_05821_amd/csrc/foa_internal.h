@@ -69,7 +69,22 @@ struct PassArgs {
   int j;                // active columns (basis size q)
   int n_max;            // capacity (columns per panel)
   int ldg;              // leading dimension of part (>= gridDim.x)
+  // passes B and C that reduce the preceding pass's column sums themselves
+  // (small streams): rstride != 0: column sums as part[slot * rstride + c];
+  // rpart: the preceding pass's, rG rows (null in pass A); and where one
+  // workgroup leaves the results
+  const double *rpart;
+  int rG, rstride;
+  const double *sigma;
+  double *h;            // pass B writes h, pass C reads it
+  double *coefw;        // pass B: sigma o h
+  double *hsum;         // pass C: h + s
+  double *xn2;          // pass B: ||psi||^2
 };
+
+// Widest basis (columns before the push) of the one-workgroup finalize that
+// also forms the next push's partial beta column.
+constexpr int kFinNextCols = 256;
 
 // Small-matrix pointers of one stream (FP64, column-major).
 struct SmallArgs {
@@ -260,6 +275,7 @@ int pass_nw(bool tv_f64, int nw_opt, int j);
 int pass_occupancy(bool tv_f64, bool tx_f64, bool prefetch, int nw, int qw);
 hipError_t launch_reduce(int mode, const SmallArgs &a, hipStream_t s);
 hipError_t launch_finalize(const SmallArgs &a, hipStream_t s);
+hipError_t launch_finalize_next(const SmallArgs &a, hipStream_t s);
 hipError_t launch_finalize_init(const SmallArgs &a, hipStream_t s);
 hipError_t launch_nextb(const SmallArgs &a, hipStream_t s);
 hipError_t launch_copy_basis(bool tv_f64, const void *W, const double *sigma, int64_t r0,

@@ -38,19 +38,18 @@ namespace foa {
 
 template <typename TV, typename TX, int NW, int QW, int MODE, bool PREF>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(pass_waves<TV, QW>()))) void k_pass(PassArgs a) {
-  if (a.st->status != ST_ACTIVE) return;
   __shared__ double lds[pass_lds_doubles<TV, NW, QW, MODE>()];
-  row_pass_body<TV, TX, NW, QW, MODE, PREF>(a, blockIdx.x, a.P, gridDim.x, blockIdx.x, lds);
+  row_pass_body<TV, TX, NW, QW, MODE, PREF, false, MODE != PM_INIT, true>(a, blockIdx.x, a.P, gridDim.x, blockIdx.x, lds);
 }
 
 template <int MODE>
 __global__ __launch_bounds__(256) void k_reduce(SmallArgs a) {
-  if (a.st->status != ST_ACTIVE) return;
-  reduce_body<MODE>(a, blockIdx.x * 4);
+  reduce_body<MODE, false, true>(a, blockIdx.x * 4);
 }
 
 __global__ __launch_bounds__(256) void k_finalize(SmallArgs a) { finalize_body(a); }
 __global__ __launch_bounds__(256) void k_finalize_init(SmallArgs a) { finalize_init_body(a); }
+__global__ __launch_bounds__(1024) void k_finalize_next(SmallArgs a) { finalize_next_body<1024>(a); }
 __global__ __launch_bounds__(256) void k_nextb(SmallArgs a) { nextb_body(a, blockIdx.x); }
 
 __global__ __launch_bounds__(256) void k_init_state(SmallArgs a, double tol) { init_state_body(a, tol); }
@@ -239,6 +238,12 @@ hipError_t launch_reduce(int mode, const SmallArgs &a, hipStream_t s) {
 
 hipError_t launch_finalize(const SmallArgs &a, hipStream_t s) {
   hipLaunchKernelGGL(k_finalize, dim3(1), dim3(256), 0, s, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_finalize_next(const SmallArgs &a, hipStream_t s) {
+  if (a.j < 1 || a.j > kFinNextCols) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_finalize_next, dim3(1), dim3(1024), 0, s, a);
   return hipGetLastError();
 }
 

@@ -300,3 +300,30 @@ def test_max_capacity(prec):
         announce(f"f32 N={N}: kappa={kap:.2e} relH2={eH:.2e} orth={orth:.2e}")
         assert g["q"] == N and eH <= 10 * EPS32 * kap and orth <= 10 * np.sqrt(N) * EPS32
     g["stream"].close()
+
+
+@pytest.mark.parametrize("prec,n,N", [
+    ("f32", 64 * 16, 24),        # one row of sums per lane and less
+    ("f32", 64 * 128 - 3, 66),   # 128 workgroups: reduced in the passes up to 64 columns, by kernels beyond
+    ("f32", 64 * 129 + 1, 40),   # one workgroup more: reduce kernels from the first push
+    ("f32", 1500, 300),          # 24 workgroups, 8 wavefronts beyond 128 columns, column chunks 1..5
+    ("f64", 64 * 256, 66),       # 16 wavefronts: 256 workgroups up to 64 columns, kernels beyond
+    ("f64", 64 * 257 - 5, 40),   # reduce kernels from the first push
+    ("f64", 1300, 260),          # one-workgroup finalize up to 256 columns, two kernels beyond
+])
+def test_small_stream_reductions(prec, n, N):
+    """Streams on both sides of the line where passes B and C reduce the sums
+    of the pass before by themselves, and of the one-workgroup finalize:
+    Gaussian snapshots (kappa_2 < 10) against the oracle."""
+    X = np.random.default_rng(n + N).standard_normal((n, N))
+    st = oracle.foa_batch(X, tol=0.0)
+    g = run_gpu(X, prec, tol=0.0)
+    if prec == "f64":
+        _compare_f64(g, st)
+        return
+    m = st.q - 1
+    kap = kappa_of(st.beta[:m, :m])
+    eH = np.linalg.norm(g["H"][:m, :m] - st.H[:m, :m], 2) / np.linalg.norm(st.H[:m, :m], 2)
+    orth = np.linalg.norm(np.eye(g["q"]) - g["V"].T @ g["V"], 2)
+    announce(f"{n} x {N}: kappa={kap:.2e} relH2={eH:.2e} orth={orth:.2e}")
+    assert g["q"] == N and eH <= 10 * EPS32 * kap and orth <= 10 * np.sqrt(N) * EPS32
