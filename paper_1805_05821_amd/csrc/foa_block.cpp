@@ -16,8 +16,6 @@ namespace {
 constexpr size_t kAlign = 256;
 constexpr int kGramGrid = 1024;    // workgroups of the block Gram passes (partial slots)
 constexpr int kBlockSlots = 1024;  // partial slots of the block passes (their largest grid)
-constexpr int kNarrowCols = 128;   // FP32 basis sizes that take 4-wavefront block passes
-constexpr int kWindowCols = 256;   // widest column window of an FP64-basis block pass
 
 size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
@@ -79,59 +77,13 @@ hipError_t enqueue_block(foa_ctx_s *c, const BlockLayout &L, char *bws, const vo
   a.ldg = kBlockSlots;
   a.ldH = c->L.ldH;
   a.ldB = c->L.ldB;
-  // FP32 basis up to 128 columns: 4-wavefront workgroups, four per CU (the
-  // panels carry little data and the per-panel chain of barriers and LDS
-  // round trips dominates; smaller independent workgroups overlap it)
-  const bool narrow = !v64 && j <= kNarrowCols;
-  const int nw = v64 ? 16 : (narrow ? 4 : 8);
-  a.G = (int)std::min<int64_t>({(int64_t)kBlockSlots, c->L.P, (int64_t)(narrow ? 4 : 2) * c->cus});
+  const int64_t units = c->L.P * (v64 ? 2 : 1);  // 64 rows of an FP32 basis, 32 of an FP64 one
+  a.G = (int)std::min<int64_t>({(int64_t)kBlockSlots, units, (int64_t)block_shape(j).per_cu * c->cus});
   a.Gz = (int)std::min<int64_t>(kGramGrid, std::max<int64_t>(1, (c->L.P * PANEL + 255) / 256));
-  // FP32 basis: a 12-group tile for 257-384 columns (the 16-group one is up to
-  // a half empty there; the blocked run measured 4-7% faster) and a 14-group
-  // one for 385-448 (the 16-group both-phase sweep spills)
-  const int qw = narrow ? pick_qw(j, 16)
-                        : ((!v64 && j > 256 && j <= 384) ? 12 : ((!v64 && j > 384 && j <= 448) ? 14 : pick_qw(j, 32)));
+  a.Gg = a.G;
   hipStream_t s = c->stream;
   hipError_t e;
-  // An FP64 basis above kWindowCols columns goes through the row passes in
-  // column windows (the accumulators of a wider one do not fit a
-  // workgroup's registers): the first window takes what the others, of
-  // kWindowCols each, leave.  Column sums (D) of the windows are
-  // independent.  Z = Y - W C goes window by window: Z = Y - W_0 C_0, then
-  // Z -= W_i C_i, the last window forming its D = W_i^T Z in the same pass;
-  // the other windows' D follow in passes of their own (with the narrow
-  // window first, the widest one is read once).
-  const int nwin = v64 ? (j + kWindowCols - 1) / kWindowCols : 1;
-  auto window = [&](const BlockArgs &b, int i) {
-    BlockArgs w = b;
-    const int first = j - (nwin - 1) * kWindowCols;
-    w.c0 = i == 0 ? 0 : first + (i - 1) * kWindowCols;
-    w.j = i == 0 ? first : kWindowCols;
-    return w;
-  };
-  auto bpass = [&](int mode, bool src64, const BlockArgs &b) -> hipError_t {
-    if (nwin == 1) return launch_bpass(mode, v64, src64, nw, qw, b.G, b, s);
-    hipError_t r = hipSuccess;
-    for (int i = 0; i < nwin && r == hipSuccess; ++i) {
-      const BlockArgs w = window(b, i);
-      r = launch_bpass(mode, v64, src64, nw, pick_qw(w.j, 32), w.G, w, s);
-    }
-    return r;
-  };
-  auto bpass_z1 = [&](const BlockArgs &b) -> hipError_t {
-    if (nwin == 1) return launch_bpass(1, v64, x64, nw, qw, b.G, b, s);
-    BlockArgs w = window(b, 0);
-    hipError_t r = launch_bpass(4, v64, x64, nw, pick_qw(w.j, 32), w.G, w, s);  // Z = Y - W_0 C_0
-    for (int i = 1; i < nwin && r == hipSuccess; ++i) {
-      w = window(b, i);                                                          // Z -= W_i C_i
-      r = launch_bpass(i == nwin - 1 ? 5 : 2, v64, true, nw, pick_qw(w.j, 32), w.G, w, s);
-    }
-    for (int i = 0; i < nwin - 1 && r == hipSuccess; ++i) {
-      w = window(b, i);                                                          // D_i = W_i^T Z
-      r = launch_bpass(3, v64, true, nw, pick_qw(w.j, 32), w.G, w, s);
-    }
-    return r;
-  };
+  auto bpass = [&](int mode, bool src64, const BlockArgs &b) { return launch_bpass(mode, v64, src64, b.G, b, s); };
   if (have_d) {
     if ((e = launch_zgram(3, v64, x64, a.Gz, a, s)) != hipSuccess) return e;        // ||y_k||^2, q^T y_k
   } else {
@@ -139,17 +91,16 @@ hipError_t enqueue_block(foa_ctx_s *c, const BlockLayout &L, char *bws, const vo
     if ((e = bpass(0, x64, a)) != hipSuccess) return e;                             // D = W^T Y
   }
   if ((e = launch_breduce(1, a, s)) != hipSuccess) return e;                         // R1, coef
-  if ((e = bpass_z1(a)) != hipSuccess) return e;                                    // Z = Y - W C, D
+  if ((e = bpass(1, x64, a)) != hipSuccess) return e;                               // Z = Y - W C, D
   if ((e = launch_breduce(2, a, s)) != hipSuccess) return e;                         // R2, R += R2, coef
   if (xn) {
     BlockArgs r = a;
     r.xn = xn;
-    if ((e = bpass(6, x64, r)) != hipSuccess) return e;                             // Z = Z - W C, D' = W^T Y'
+    if ((e = bpass(4, x64, r)) != hipSuccess) return e;                             // Z = Z - W C, D' = W^T Y', Z^T Z
     if ((e = launch_breduce(4, r, s)) != hipSuccess) return e;                       // D' -> dnext
   } else {
-    if ((e = bpass(2, true, a)) != hipSuccess) return e;                            // Z = Z - W C
+    if ((e = bpass(2, true, a)) != hipSuccess) return e;                            // Z = Z - W C, Z^T Z
   }
-  if ((e = launch_zgram(1, v64, x64, a.Gz, a, s)) != hipSuccess) return e;          // Z^T Z
   // third projection, where the test asks for it (the gated kernels return
   // at once otherwise)
   int *gate = reinterpret_cast<int *>(bws + L.gate);
@@ -158,18 +109,18 @@ hipError_t enqueue_block(foa_ctx_s *c, const BlockLayout &L, char *bws, const vo
   g.gate = gate;
   if ((e = bpass(3, true, g)) != hipSuccess) return e;                              // D = W^T Z
   if ((e = launch_breduce(3, g, s)) != hipSuccess) return e;                         // R3, R += R3, coef
-  if ((e = bpass(2, true, g)) != hipSuccess) return e;                              // Z = Z - W C
-  if ((e = launch_zgram(1, v64, x64, g.Gz, g, s)) != hipSuccess) return e;          // Z^T Z
+  if ((e = bpass(2, true, g)) != hipSuccess) return e;                              // Z = Z - W C, Z^T Z
   // shifted CholeskyQR3: each Gram pass forms Z T_0 .. T_{t-1} row by row
   // from the unchanged Z, the last one writes Z T_0 T_1 T_2 into V
   BlockArgs q = a;
   if ((e = launch_bchol(0, a, s)) != hipSuccess) return e;                           // shifted: T_0
+  q.Gg = q.Gz;
   q.tlev = 1;
   if ((e = launch_zgram(1, v64, x64, q.Gz, q, s)) != hipSuccess) return e;          // Gram of Z T_0
-  if ((e = launch_bchol(1, a, s)) != hipSuccess) return e;                           // T_1
+  if ((e = launch_bchol(1, q, s)) != hipSuccess) return e;                           // T_1
   q.tlev = 2;
   if ((e = launch_zgram(1, v64, x64, q.Gz, q, s)) != hipSuccess) return e;          // Gram of Z T_0 T_1
-  if ((e = launch_bchol(2, a, s)) != hipSuccess) return e;                           // T_2
+  if ((e = launch_bchol(2, q, s)) != hipSuccess) return e;                           // T_2
   q.tlev = 3;
   if ((e = launch_zgram(2, v64, x64, q.Gz, q, s)) != hipSuccess) return e;          // V <- Z T_0 T_1 T_2
   if ((e = launch_bcommit(a, s)) != hipSuccess) return e;

@@ -33,6 +33,7 @@
 //   k_bchol   : Gram reduction, (shifted) Cholesky and triangular inverse;
 //   k_bcommit : breakdown test, beta, H_bar, sigma and the scalar state.
 #include <mutex>
+#include <type_traits>
 
 #include "foa.h"
 #include "foa_device.h"
@@ -77,217 +78,271 @@ hipError_t block_static_scratch(int device, char **ptr) {
   return g_scratch_err[device];
 }
 
-enum { BP_R1 = 0, BP_Z1 = 1, BP_Z2 = 2, BP_D = 3, BP_Z0 = 4, BP_ZD = 5, BP_ZR = 6 };
-bool block_supported(bool tv_f64, int qw);
+enum { BP_R1 = 0, BP_Z1 = 1, BP_Z2 = 2, BP_D = 3, BP_ZR = 4 };
 enum { ZG_YNORM = 0, ZG_GRAM = 1, ZG_WRITEV = 2, ZG_YNQ = 3 };
 
 // ---------------------------------------------------------------------------
-// Block row pass over the basis columns c0 .. c0 + j - 1 (a.c0, a.j; the
-// whole basis unless an FP64 basis is split in two windows).  MODE BP_R1:
-// D = W^T Y (column sums only).  BP_Z1: Z = Y - W C, D = W^T Z.  BP_Z2:
-// Z = Z - W C.  BP_D: D = W^T Z (column sums of the block: the split form of
-// BP_Z1's second phase and the third projection).  BP_Z0: Z = Y - W C, and
-// BP_ZD: Z = Z - W C, D = W^T Z (the first and last window of BP_Z1 over a
-// split basis).  BP_ZR: Z = Z - W C and D = W^T Y' for the next block's
-// snapshots Y' (a.xn) in the same sweep (the next block's first projection
-// over these columns; the two phases are independent, so Y' goes to LDS at
-// phase 1's barrier).  W is the stored basis (the
-// sigma scaling of its columns is folded into C and into the reduction of D).
-// Per panel, the BPK right-hand sides of a row are spread over the update
-// lanes (row, k); phase 1 and phase 2 are those of the single push with BPK
-// values per row.
+// Block row pass over the j basis columns.  MODE BP_R1: D = W^T Y (column sums
+// only).  BP_Z1: Z = Y - W C, D = W^T Z.  BP_Z2: Z = Z - W C.  BP_D: D = W^T Z
+// (the third projection).  BP_ZR: Z = Z - W C and D = W^T Y' for the next
+// block's snapshots Y' (a.xn) in the same sweep (the next block's first
+// projection over these columns; the two phases are independent, so Y' goes to
+// LDS at phase 1's barrier).  BP_Z2 and BP_ZR also leave the partial Gram matrix
+// of the Z they form in partg (a.G slots).  W is the stored basis (the sigma
+// scaling of its columns is folded into C and into the reduction of D).
+//
+// Unit of work: BROWS rows of a panel, 16 chunks of one 16-byte load each (64
+// rows with an FP32 basis, 32 with an FP64 one), walked by persistent
+// workgroups.  Lane l of a wavefront holds chunk l / 4 of column l % 4 of each
+// of its QW groups of four columns (wavefront w: groups w, w + NW, ...).
+//   phase 1 (row sums against BPK coefficient vectors): FMA per lane over its
+//     groups; then over the four lanes of a quad by DPP moves, each lane keeping
+//     one right-hand side; then over the wavefronts through LDS;
+//   update: (row, right-hand side) pairs, pos = e * 64 + chunk * 4 + k for row
+//     chunk * EPL + e, spread over the wavefronts; Z is kept in that order;
+//   phase 2 (column sums): the lanes hold a tile as the A operand of
+//     v_mfma_f64_4x4x4 (four blocks: columns x rows), the pairs of row e as its
+//     B operand, so a group's sums against the four right-hand sides take one
+//     accumulator per lane.  The FP64 matrix and vector rates are the same here
+//     (18.7 cycles per 256 FMAs, both on one pipe); what the matrix form buys is
+//     registers: 4 x QW FP64 accumulators per lane became QW, so tiles of every
+//     width are prefetched whole and an FP64 basis needs no column windows.
+// Bound: HBM.  2^22 rows, FP32 basis of 449-496 columns: BP_Z1 1382 us and BP_ZR
+// 1470 us (5.8 and 5.4 TB/s of basis reads beside the write stream of Z), 1925
+// and 1980 us with vector FMAs for phase 2 and no room to prefetch; with the
+// next tile loaded whole but one iteration ahead 1520 and 1680 us, and with each
+// unit's y loaded at its own start (or through a divergent resource) 1540 us.
+// FP64 basis, 300007 rows x 257-320 columns: 128 and 144 us, in two column
+// windows 330 us.
 // ---------------------------------------------------------------------------
-// PF: groups of the next panel's tile loaded ahead (0 .. QW; the rest load at
-// the start of their panel).
-// Register budget as waves per SIMD: the 8-group FP32 tile of the passes
-// with one phase over the basis rows (BP_R1, BP_D) is held to 128 VGPRs, so
-// two 8-wavefront workgroups share a CU (without prefetch: measured 22%
-// faster than one workgroup with it); the others take what they need.
-template <typename TV, int QW, int MODE>
-constexpr int bp_waves() {
-  return (sizeof(TV) == 4 && (MODE == BP_R1 || MODE == BP_D) && QW == 8) ? 4 : 1;
-}
-
-template <typename TV, typename TX, int NW, int QW, int MODE, int PF>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(bp_waves<TV, QW, MODE>()))) void k_bpass(
-    BlockArgs a) {
+template <typename TV, typename TX, int NW, int QW, int MODE>
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(QW >= 10 ? 2 : 1))) void k_bpass(BlockArgs a) {
   constexpr int EPL = Vec<TV>::EPL;
-  constexpr int LPC = 64 / EPL;
-  constexpr int CPW = EPL;
-  constexpr int JCAP = QW * NW * CPW;
-  constexpr int RPW = PANEL / NW;
-  constexpr int GSTRIDE = NW * CPW;
+  constexpr int BROWS = 16 * EPL;
+  constexpr int UPP = PANEL / BROWS;    // units per panel
+  constexpr int PAIRS = BROWS * BPK;
+  constexpr int UL = PAIRS / NW;        // update lanes of a wavefront
+  constexpr int JCAP = QW * NW * 4;
+  constexpr int GSTRIDE = NW * 4;       // columns between a wavefront's groups
   constexpr bool NEXT_Y = MODE == BP_ZR;
-  constexpr bool HAS_P1 = MODE == BP_Z1 || MODE == BP_Z2 || MODE == BP_Z0 || MODE == BP_ZD || NEXT_Y;
-  constexpr bool HAS_P2 = MODE == BP_R1 || MODE == BP_Z1 || MODE == BP_D || MODE == BP_ZD || NEXT_Y;
-  constexpr bool SRC_X = MODE == BP_R1 || MODE == BP_Z1 || MODE == BP_Z0;
-  constexpr bool STORE_Z = MODE == BP_Z1 || MODE == BP_Z2 || MODE == BP_Z0 || MODE == BP_ZD || NEXT_Y;
-  static_assert(RPW * BPK <= 64, "update lanes");
+  constexpr bool HAS_P1 = MODE == BP_Z1 || MODE == BP_Z2 || NEXT_Y;
+  constexpr bool HAS_P2 = MODE == BP_R1 || MODE == BP_Z1 || MODE == BP_D || NEXT_Y;
+  constexpr bool SRC_X = MODE == BP_R1 || MODE == BP_Z1;
+  constexpr bool GRAM = MODE == BP_Z2 || NEXT_Y;
+  static_assert(BPK == 4 && UL <= 64 && UL % 4 == 0, "update lanes");
 
   if (a.st->status != ST_ACTIVE || *a.flag || (a.gate && !*a.gate)) return;
 
   __shared__ double s_coef[HAS_P1 ? JCAP * BPK : 1];
-  __shared__ double s_red[2][NW][PANEL * BPK];
-  __shared__ double s_w[2][PANEL * BPK];
+  __shared__ double s_red[HAS_P1 ? 2 * NW * PAIRS : 1];
+  __shared__ double s_w[2][PAIRS];
+  __shared__ double s_g[GRAM ? NW * 12 : 1];
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int cs = lane / LPC;
-  const int rg = lane % LPC;
+  const int cl = lane & 3;
   const int j = a.j;
   const int slot = blockIdx.x;
 
   if (HAS_P1)
-    for (int c = tid; c < JCAP * BPK; c += NW * 64) s_coef[c] = (c < j * BPK) ? a.coef[a.c0 * BPK + c] : 0.0;
+    for (int c = tid; c < JCAP * BPK; c += NW * 64) s_coef[c] = (c < j * BPK) ? a.coef[c] : 0.0;
   __syncthreads();
 
-  const int cbase = wave * CPW + cs;
-  const unsigned goff0 = (unsigned)((wave * CPW * PANEL + lane * EPL) * sizeof(TV));
+  const int cbase = wave * 4 + cl;
+  const unsigned goff0 = (unsigned)(cbase * PANEL * sizeof(TV)) + (unsigned)(lane >> 2) * 16u;
   constexpr unsigned GBYTES = (unsigned)(GSTRIDE * PANEL * sizeof(TV));
   const unsigned tile_bytes = (unsigned)(j * PANEL * sizeof(TV));
-  // update lanes: (row, right-hand side) pairs of this wavefront's rows
-  const bool uact = lane < RPW * BPK;
-  const int urow = wave * RPW + (lane % (RPW * BPK)) / BPK;
-  const int uk = lane % BPK;
+  const bool uact = lane < UL;
+  const int pos = wave * UL + (lane & (UL - 1));
+  const int uk = pos & 3;
+  const int urow = ((pos & 63) >> 2) * EPL + (pos >> 6);
 
-  double acc[QW][BPK];
+  double acc[QW];
 #pragma unroll
-  for (int g = 0; g < QW; ++g)
-#pragma unroll
-    for (int k = 0; k < BPK; ++k) acc[g][k] = 0.0;
+  for (int g = 0; g < QW; ++g) acc[g] = 0.0;
+  double g0 = 0.0, g1 = 0.0, g2 = 0.0;
 
-  // the window's first column within each panel
-  const char *Wb = static_cast<const char *>(a.W) + (size_t)a.c0 * PANEL * sizeof(TV);
+  const char *Wb = static_cast<const char *>(a.W);
   const size_t pbytes = (size_t)a.n_max * PANEL * sizeof(TV);
-  TV t[QW][EPL];
-  TV tn[PF > 0 ? PF : 1][EPL];
+  TV ta[QW][EPL], tb[QW][EPL];
 
-  const int64_t pend = a.P, pstep = gridDim.x;
-  int64_t p = blockIdx.x;
-  if (PF > 0 && p < pend) {
-    load_tile_groups<TV, 0, PF, 0>(make_rsrc(Wb + (size_t)p * pbytes, tile_bytes), goff0, GBYTES, t);
-#pragma unroll
-    for (int g = 0; g < PF; ++g)
-#pragma unroll
-      for (int e = 0; e < EPL; ++e) asm volatile("" : "+v"(t[g][e]));
-  }
-  int par = 0;
-  for (; p < pend; p += pstep) {
-    double y;
-    if (SRC_X) {
-      const int64_t rem = a.n - p * PANEL;
-      const int valid = (int)(rem >= PANEL ? PANEL : (rem > 0 ? rem : 0));
-      const __amdgpu_buffer_rsrc_t rx = make_rsrc(static_cast<const TX *>(a.x) + p * PANEL,
-                                                  (unsigned)(((BPK - 1) * a.ldx + valid) * sizeof(TX)));
-      const unsigned off = (uact && urow < valid) ? (unsigned)((uk * a.ldx + urow) * sizeof(TX)) : kOOR;
-      y = buf_load_scalar<TX>(rx, off);
+  // the unit's rows of column c start at c * PANEL + half * BROWS of its panel;
+  // past the last unit every load is out of range and returns 0 without traffic
+  // (unit numbers, below 2^31 for any basis that fits the card, and the choices
+  // made from them are 32-bit and scalar: a resource that the compiler takes for
+  // divergent costs a loop per load)
+  const int pend = (int)a.P * UPP, pstep = (int)gridDim.x;
+  auto tile_rsrc = [&](int u) {
+    const int v = u < pend ? u : 0;
+    const unsigned half = UPP > 1 ? (unsigned)(v % UPP) * (unsigned)(BROWS * sizeof(TV)) : 0u;
+    return make_rsrc(Wb + (size_t)(v / UPP) * pbytes + half, u < pend ? tile_bytes - half : 0u);
+  };
+  auto load_group = [&](const __amdgpu_buffer_rsrc_t &r, int g, TV (&dst)[EPL]) {
+    unpack16<TV>(__builtin_amdgcn_raw_buffer_load_b128(r, (int)(goff0 + g * GBYTES), 0, kTileLoad), dst);
+  };
+  // snapshot rows of a unit: snapshot k's row r at byte (k * ldx + r) * sizeof(TX)
+  const unsigned xoff0 = (unsigned)((uk * a.ldx + urow) * sizeof(TX));
+  const int nfull = (int)(a.n / BROWS), nrem = (int)(a.n % BROWS);  // whole units, rows of the one after
+  auto load_xs = [&](const void *x, int u) {
+    const int v = u < pend ? u : 0;
+    const int valid = u < nfull ? BROWS : (u == nfull ? nrem : 0);
+    return buf_load_raw<TX>(make_rsrc(static_cast<const TX *>(x) + (size_t)v * BROWS,
+                                      (unsigned)(((BPK - 1) * a.ldx + BROWS) * sizeof(TX))),
+                            uact && urow < valid ? xoff0 : kOOR);
+  };
+  typedef typename std::conditional<SRC_X, TX, double>::type TY;
+  auto load_y = [&](int u) -> TY {
+    if constexpr (SRC_X) {
+      return load_xs(a.x, u);
     } else {
-      const __amdgpu_buffer_rsrc_t rz = make_rsrc(a.Z + p * PANEL * BPK, PANEL * BPK * 8);
-      y = buf_load_scalar<double>(rz, uact ? (unsigned)((uk * PANEL + urow) * 8) : kOOR);
+      const int v = u < pend ? u : 0;
+      return buf_load_raw<double>(make_rsrc(a.Z + (size_t)v * PAIRS, PAIRS * 8),
+                                  uact && u < pend ? (unsigned)(pos * 8) : kOOR);
     }
-    double yn = 0.0;
-    if constexpr (NEXT_Y) {
-      const int64_t rem = a.n - p * PANEL;
-      const int valid = (int)(rem >= PANEL ? PANEL : (rem > 0 ? rem : 0));
-      const __amdgpu_buffer_rsrc_t rx = make_rsrc(static_cast<const TX *>(a.xn) + p * PANEL,
-                                                  (unsigned)(((BPK - 1) * a.ldx + valid) * sizeof(TX)));
-      yn = buf_load_scalar<TX>(rx, (uact && urow < valid) ? (unsigned)((uk * a.ldx + urow) * sizeof(TX)) : kOOR);
-    }
-    if constexpr (PF < QW)  // the groups not prefetched, straight into their place
-      load_tile_groups<TV, PF, QW, PF>(make_rsrc(Wb + (size_t)p * pbytes, tile_bytes), goff0, GBYTES, t);
-    if constexpr (PF > 0) {
-      const bool more = p + pstep < pend;
-      load_tile_groups<TV, 0, PF, 0>(make_rsrc(Wb + (size_t)(more ? p + pstep : p) * pbytes, more ? tile_bytes : 0u),
-                                     goff0, GBYTES, tn);
-    }
+  };
 
-    double us = 0.0;
-    if (HAS_P1) {
+  TY y;
+  TX yn = 0;
+  int par = 0;
+  // One unit, tile t; the tile of the unit after next is loaded into the same
+  // registers group by group as the last phase is done with them, so between
+  // one and two tiles per wavefront are always on their way.  The next unit's
+  // y goes out before those loads: loads complete in order.
+  auto step = [&](int p, TV (&t)[QW][EPL]) {
+    const __amdgpu_buffer_rsrc_t rt = tile_rsrc(p + 2 * pstep);
+    double wv = 0.0;
+    if constexpr (!HAS_P1) wv = (double)y;
+    if constexpr (HAS_P1) {
       double u[EPL][BPK];
 #pragma unroll
       for (int e = 0; e < EPL; ++e)
 #pragma unroll
         for (int k = 0; k < BPK; ++k) u[e][k] = 0.0;
+      // the coefficients of group g + CD are read while group g's products run
+      // (left to itself the compiler reads them next to their use)
+      constexpr int CD = QW <= 12 ? 2 : (sizeof(TV) == 4 && QW == 16 && NW == 8 && NEXT_Y ? 0 : 1);  // 0: no register left
+      double cf[CD + 1][BPK];
+      auto read_cf = [&](int g) {
+#pragma unroll
+        for (int k = 0; k < BPK; ++k) cf[g % (CD + 1)][k] = s_coef[(cbase + g * GSTRIDE) * BPK + k];
+      };
+#pragma unroll
+      for (int g = 0; g < (CD < QW ? CD : QW); ++g) read_cf(g);
 #pragma unroll
       for (int g = 0; g < QW; ++g) {
+        if (g + CD < QW) read_cf(g + CD);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int k = 0; k < BPK; ++k) {
-          const double cf = s_coef[(cbase + g * GSTRIDE) * BPK + k];
 #pragma unroll
-          for (int e = 0; e < EPL; ++e) u[e][k] = fma((double)t[g][e], cf, u[e][k]);
+          for (int e = 0; e < EPL; ++e) u[e][k] = fma((double)t[g][e], cf[g % (CD + 1)][k], u[e][k]);
         }
+        __builtin_amdgcn_sched_barrier(0);
       }
+      // over the quad: lane cl ends with right-hand side cl of every row
+      double *red = s_red + par * NW * PAIRS;
 #pragma unroll
-      for (int e = 0; e < EPL; ++e)
-#pragma unroll
-        for (int k = 0; k < BPK; ++k) {
-          if constexpr (LPC <= 16) u[e][k] = xor_sum<16>(u[e][k]);
-          u[e][k] = xor_sum<32>(u[e][k]);
-        }
-      if (cs == 0) {
-#pragma unroll
-        for (int e = 0; e < EPL; ++e)
-#pragma unroll
-          for (int k = 0; k < BPK; ++k) s_red[par][wave][(rg * EPL + e) * BPK + k] = u[e][k];
+      for (int e = 0; e < EPL; ++e) {
+        const bool b0 = cl & 1, b1 = cl & 2;
+        const double r01 = (b0 ? u[e][1] : u[e][0]) + dpp_mov<0xB1>(b0 ? u[e][0] : u[e][1]);
+        const double r23 = (b0 ? u[e][3] : u[e][2]) + dpp_mov<0xB1>(b0 ? u[e][2] : u[e][3]);
+        red[wave * PAIRS + e * 64 + lane] = (b1 ? r23 : r01) + dpp_mov<0x4E>(b1 ? r01 : r23);
       }
-      if (NEXT_Y && uact) s_w[par][urow * BPK + uk] = yn;
+      if (NEXT_Y && uact) s_w[par][pos] = (double)yn;
       __syncthreads();
+      double us = 0.0;
 #pragma unroll
-      for (int w2 = 0; w2 < NW; ++w2) us += s_red[par][w2][urow * BPK + uk];
+      for (int w2 = 0; w2 < NW; ++w2) us += red[w2 * PAIRS + pos];
+      wv = (double)y - us;
+      buf_store_scalar<double>(wv, make_rsrc(a.Z + (size_t)p * PAIRS, PAIRS * 8), uact ? (unsigned)(pos * 8) : kOOR);
     }
-    const double wv = y - us;
-    if (STORE_Z) {
-      const __amdgpu_buffer_rsrc_t rz = make_rsrc(a.Z + p * PANEL * BPK, PANEL * BPK * 8);
-      buf_store_scalar<double>(wv, rz, uact ? (unsigned)((uk * PANEL + urow) * 8) : kOOR);
+    if constexpr (GRAM) {
+      // z_k z_k, z_k z_{k+1}, z_k z_{k+2} (k in the quad's lanes, mod 4)
+      const double z = uact ? wv : 0.0;
+      g0 = fma(z, z, g0);
+      g1 = fma(z, dpp_mov<0x39>(z), g1);  // quad_perm 1,2,3,0
+      g2 = fma(z, dpp_mov<0x4E>(z), g2);  // quad_perm 2,3,0,1
     }
-    if (HAS_P2) {
-      if (!NEXT_Y) {
-        if (uact) s_w[par][urow * BPK + uk] = wv;
-        __syncthreads();
-      }
+    if (HAS_P2 && !NEXT_Y) {
+      if (uact) s_w[par][pos] = wv;
+      __syncthreads();
+    }
+    y = load_y(p + pstep);
+    if constexpr (NEXT_Y) yn = load_xs(a.xn, p + pstep);
+    if constexpr (HAS_P2) {
       if constexpr (sizeof(TV) == 4) {
+        // keep only the FP32 tile live across the phases: convert again
 #pragma unroll
         for (int g = 0; g < QW; ++g)
 #pragma unroll
           for (int e = 0; e < EPL; ++e) asm volatile("" : "+v"(t[g][e]));
       }
-      // one row's right-hand sides at a time, which keeps fewer values live
-      // (each accumulator takes its rows in order e = 0 .. EPL-1)
+      double we[EPL];
 #pragma unroll
-      for (int e = 0; e < EPL; ++e) {
-        double wr[BPK];
+      for (int e = 0; e < EPL; ++e) we[e] = s_w[par][e * 64 + lane];
 #pragma unroll
-        for (int k = 0; k < BPK; ++k) wr[k] = s_w[par][(rg * EPL + e) * BPK + k];
+      for (int g4 = 0; g4 < QW; g4 += 4) {
 #pragma unroll
-        for (int g = 0; g < QW; ++g)
+        for (int e = 0; e < EPL; ++e)
 #pragma unroll
-          for (int k = 0; k < BPK; ++k) acc[g][k] = fma((double)t[g][e], wr[k], acc[g][k]);
+          for (int g = g4; g < (g4 + 4 < QW ? g4 + 4 : QW); ++g)
+            acc[g] = __builtin_amdgcn_mfma_f64_4x4x4f64((double)t[g][e], we[e], acc[g], 0, 0, 0);
+#pragma unroll
+        for (int g = g4; g < (g4 + 4 < QW ? g4 + 4 : QW); ++g) load_group(rt, g, t[g]);
+        __builtin_amdgcn_sched_barrier(0);
       }
-    }
-    if constexpr (PF > 0) {
+    } else {
 #pragma unroll
-      for (int g = 0; g < PF; ++g)
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) asm volatile("" : "+v"(tn[g][e]));
-#pragma unroll
-      for (int g = 0; g < PF; ++g)
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) t[g][e] = tn[g][e];
+      for (int g = 0; g < QW; ++g) load_group(rt, g, t[g]);
     }
     par ^= 1;
-  }
+  };
 
-  if (HAS_P2) {
+  int p = blockIdx.x;
+  y = load_y(p);
+  if constexpr (NEXT_Y) yn = load_xs(a.xn, p);
+  {
+    const __amdgpu_buffer_rsrc_t r0 = tile_rsrc(p), r1 = tile_rsrc(p + pstep);
+#pragma unroll
+    for (int g = 0; g < QW; ++g) load_group(r0, g, ta[g]);
+#pragma unroll
+    for (int g = 0; g < QW; ++g) load_group(r1, g, tb[g]);
+  }
+  for (; p + pstep < pend; p += 2 * pstep) {
+    step(p, ta);
+    step(p + pstep, tb);
+  }
+  if (p < pend) step(p, ta);
+
+  // accumulators: lane = rhs + 4 * block + 16 * column; the blocks (chunks mod
+  // 4) are added by rotations within a row of 16 lanes
+  if constexpr (HAS_P2) {
 #pragma unroll
     for (int g = 0; g < QW; ++g) {
-      const int c = cbase + g * GSTRIDE;
+      const int c = wave * 4 + g * GSTRIDE + (lane >> 4);
+      double v = acc[g] + dpp_mov<0x128>(acc[g]);
+      v += dpp_mov<0x124>(v);
+      if ((lane & 12) == 0 && c < j) a.partb[((size_t)c * BPK + cl) * a.ldg + slot] = v;
+    }
+  }
+  if constexpr (GRAM) {
+    double gv[3] = {g0, g1, g2};
 #pragma unroll
-      for (int k = 0; k < BPK; ++k) {
-        double v = acc[g][k];
-#pragma unroll
-        for (int m = 1; m < LPC; m <<= 1) v += xor_shfl(v, m);
-        if (rg == 0 && c < j) a.partb[((size_t)(a.c0 + c) * BPK + k) * a.ldg + slot] = v;
+    for (int m = 0; m < 3; ++m) {
+      double v = gv[m] + dpp_mov<0x128>(gv[m]);
+      v += dpp_mov<0x124>(v);
+      v = xor_sum<32>(xor_sum<16>(v));
+      if (lane < 4) s_g[wave * 12 + m * 4 + lane] = v;
+    }
+    __syncthreads();
+    if (tid < 12) {
+      const int m = tid >> 2, k = tid & 3, l = (k + m) & 3;
+      double v = 0.0;
+      for (int w2 = 0; w2 < NW; ++w2) v += s_g[w2 * 12 + tid];
+      if (m < 2 || k < 2) {
+        a.partg[(size_t)slot * BPK * BPK + k * BPK + l] = v;
+        a.partg[(size_t)slot * BPK * BPK + l * BPK + k] = v;
       }
     }
   }
@@ -325,6 +380,9 @@ __global__ __launch_bounds__(256) void k_zgram(BlockArgs a) {
   for (int k = 0; k < BPK; ++k)
 #pragma unroll
     for (int l = 0; l < BPK; ++l) g[k][l] = 0.0;
+  // Z's order: units of BROWS rows (see k_bpass), row chunk * EPL + e of a
+  // unit at e * 16 + chunk
+  constexpr int EPL = Vec<TV>::EPL, BROWS = 16 * EPL;
   const int64_t npad = a.P * PANEL;
   if constexpr (MODE == ZG_YNQ) {
     // ||y_k||^2 and h[c][k] = q_c^T y_k for the previous block's new columns
@@ -387,12 +445,9 @@ __global__ __launch_bounds__(256) void k_zgram(BlockArgs a) {
   // the snapshots above, measured 6-12% slower here)
   constexpr bool NORMS = MODE == ZG_YNORM || MODE == ZG_YNQ;
   for (int64_t r = (int64_t)blockIdx.x * 256 + tid; !NORMS && r < npad; r += (int64_t)gridDim.x * 256) {
-    const int64_t p = r / PANEL;
-    const int rr = (int)(r % PANEL);
     double z[BPK];
-    const double *zr = a.Z + p * PANEL * BPK + rr;
 #pragma unroll
-    for (int k = 0; k < BPK; ++k) z[k] = zr[k * PANEL];
+    for (int k = 0; k < BPK; ++k) z[k] = a.Z[r * BPK + k];
     for (int t = 0; t < tlev; ++t) {  // z <- z T_t
       const double *T = sT + t * BPK * BPK;
       double o[BPK];
@@ -407,7 +462,9 @@ __global__ __launch_bounds__(256) void k_zgram(BlockArgs a) {
       for (int l = 0; l < BPK; ++l) z[l] = o[l];
     }
     if (MODE == ZG_WRITEV) {
-      TV *vc = static_cast<TV *>(a.W) + (size_t)p * a.n_max * PANEL + (size_t)a.j * PANEL + rr;
+      const int rr = (int)(r % PANEL), ru = rr % BROWS;
+      TV *vc = static_cast<TV *>(a.W) + (size_t)(r / PANEL) * a.n_max * PANEL + (size_t)a.j * PANEL + (rr - ru) +
+               (ru % 16) * EPL + ru / 16;
 #pragma unroll
       for (int k = 0; k < BPK; ++k) vc[k * PANEL] = (TV)z[k];
       continue;
@@ -501,14 +558,14 @@ __device__ inline void gram_reduce(const BlockArgs &a, int tid, double *sh, doub
 #pragma unroll
   for (int m = 0; m < 8; ++m) t8[m] = 0.0;
   int g = s0;
-  for (; g + 7 * SL < a.Gz; g += 8 * SL) {
+  for (; g + 7 * SL < a.Gg; g += 8 * SL) {
 #pragma unroll
     for (int m = 0; m < 8; ++m) t8[m] += a.partg[(size_t)(g + m * SL) * GSLOT + e];
   }
   double t = 0.0;
 #pragma unroll
   for (int m = 0; m < 8; ++m) t += t8[m];
-  for (; g < a.Gz; g += SL) t += a.partg[(size_t)g * GSLOT + e];
+  for (; g < a.Gg; g += SL) t += a.partg[(size_t)g * GSLOT + e];
   sh[tid] = t;
   __syncthreads();
   if (tid < GSLOT) {
@@ -750,87 +807,70 @@ __global__ __launch_bounds__(256) void k_bthird(BlockArgs a, int *gate, double u
 // ---------------------------------------------------------------------------
 // Launchers
 // ---------------------------------------------------------------------------
-// Prefetched groups of a block pass (what fits beside the BPK accumulators).
-// FP32 basis: the whole tile, except 6 of 12 groups in BP_Z1, none at 14 and
-// 16 groups in BP_Z1, BP_R1 and BP_D (the 16-group BP_Z1 spills even without;
-// 2 of 14 in BP_Z1 and 8 of 14 or 16 in BP_R1 fit and were no faster), and
-// none at 8 groups in BP_R1 and BP_D (their 128-VGPR budget); FP64 basis: up
-// to 4 groups, in BP_Z2 up to 8.
-template <typename TV, int QW, int MODE>
-constexpr int bp_pf() {
-  if constexpr (sizeof(TV) == 8) {
-    return (QW <= 4 || MODE == BP_Z2 || MODE == BP_Z0) ? QW : 0;  // BP_ZD as BP_Z1
-  } else {
-    if (QW == 8 && (MODE == BP_R1 || MODE == BP_D)) return 0;
-    if (QW <= 8) return QW;
-    if (QW == 12) return (MODE == BP_Z1 || MODE == BP_ZR) ? 6 : 12;
-    return MODE == BP_Z2 ? QW : 0;  // 14 and 16 groups
+// Workgroup shape of the block passes over j columns (tiles of QW groups of
+// four columns on NW wavefronts) and its resident workgroups per CU.  The
+// narrowest tile that covers j, as the groups beyond it are arithmetic for
+// nothing; 4 wavefronts while their registers hold it (256 columns), 8 beyond,
+// which fill a CU.  The shape itself hardly matters: 2^22 rows, FP32, 8
+// wavefronts from 65 or 129 columns on instead of 4, 284.7 against 286.2 us per
+// snapshot at N = 256; 2, 3 or 4 workgroups per CU throughout 287.1, 290.7 and
+// 284.7 us, at 100037 x 200 39.0, 41.5 and 43.0 against 40.4 us.
+BlockShape block_shape(int j) {
+  static const int q4[] = {1, 2, 4, 6, 8, 10, 12, 14, 16}, q8[] = {10, 12, 14, 16};
+  if (j <= 256) {
+    for (int q : q4)
+      if (16 * q >= j) return {4, q, q <= 4 ? 4 : (q <= 8 ? 3 : 2)};
   }
+  for (int q : q8)
+    if (32 * q >= j) return {8, q, 1};
+  return {8, 16, 1};
 }
 
-template <typename TV, typename TX, int NW, int MODE>
-static hipError_t launch_bpass_q(int qw, int grid, const BlockArgs &a, hipStream_t s) {
-  constexpr int NT = NW * 64;
-  switch (qw) {
-    case 1: hipLaunchKernelGGL((k_bpass<TV, TX, NW, 1, MODE, bp_pf<TV, 1, MODE>()>), dim3(grid), dim3(NT), 0, s, a); break;
-    case 2: hipLaunchKernelGGL((k_bpass<TV, TX, NW, 2, MODE, bp_pf<TV, 2, MODE>()>), dim3(grid), dim3(NT), 0, s, a); break;
-    case 4: hipLaunchKernelGGL((k_bpass<TV, TX, NW, 4, MODE, bp_pf<TV, 4, MODE>()>), dim3(grid), dim3(NT), 0, s, a); break;
-    case 8: hipLaunchKernelGGL((k_bpass<TV, TX, NW, 8, MODE, bp_pf<TV, 8, MODE>()>), dim3(grid), dim3(NT), 0, s, a); break;
-    case 12:
-      if constexpr (sizeof(TV) == 4 && NW == 8) {
-        hipLaunchKernelGGL((k_bpass<TV, TX, NW, 12, MODE, bp_pf<TV, 12, MODE>()>), dim3(grid), dim3(NT), 0, s, a);
-        break;
-      }
-      return hipErrorInvalidValue;
-    case 14:
-      if constexpr (sizeof(TV) == 4 && NW == 8) {
-        hipLaunchKernelGGL((k_bpass<TV, TX, NW, 14, MODE, bp_pf<TV, 14, MODE>()>), dim3(grid), dim3(NT), 0, s, a);
-        break;
-      }
-      return hipErrorInvalidValue;
-    default:
-      if constexpr (NW * 16 * Vec<TV>::EPL <= 512)
-        hipLaunchKernelGGL((k_bpass<TV, TX, NW, 16, MODE, bp_pf<TV, 16, MODE>()>), dim3(grid), dim3(NT), 0, s, a);
-      else
-        return hipErrorInvalidValue;
-      break;
+template <typename TV, typename TX, int MODE>
+static hipError_t launch_bpass_q(int nw, int qw, int grid, const BlockArgs &a, hipStream_t s) {
+#define FOA_BPASS(NW, QW)                                                                              \
+  case NW * 100 + QW:                                                                                  \
+    hipLaunchKernelGGL((k_bpass<TV, TX, NW, QW, MODE>), dim3(grid), dim3(NW * 64), 0, s, a);           \
+    break;
+  switch (nw * 100 + qw) {
+    FOA_BPASS(4, 1)
+    FOA_BPASS(4, 2)
+    FOA_BPASS(4, 4)
+    FOA_BPASS(4, 6)
+    FOA_BPASS(4, 8)
+    FOA_BPASS(4, 10)
+    FOA_BPASS(4, 12)
+    FOA_BPASS(4, 14)
+    FOA_BPASS(4, 16)
+    FOA_BPASS(8, 10)
+    FOA_BPASS(8, 12)
+    FOA_BPASS(8, 14)
+    FOA_BPASS(8, 16)
+    default: return hipErrorInvalidValue;
   }
+#undef FOA_BPASS
   return hipGetLastError();
 }
 
-template <typename TV, typename TX, int NW>
-static hipError_t launch_bpass_m(int mode, int qw, int grid, const BlockArgs &a, hipStream_t s) {
-  if (!block_supported(sizeof(TV) == 8, qw)) return hipErrorInvalidValue;
+template <typename TV, typename TX>
+static hipError_t launch_bpass_m(int mode, const BlockShape &sh, int grid, const BlockArgs &a, hipStream_t s) {
   switch (mode) {
-    case BP_R1: return launch_bpass_q<TV, TX, NW, BP_R1>(qw, grid, a, s);
-    case BP_Z1: return launch_bpass_q<TV, TX, NW, BP_Z1>(qw, grid, a, s);
-    case BP_D: return launch_bpass_q<TV, double, NW, BP_D>(qw, grid, a, s);
-    case BP_Z0:
-      if constexpr (sizeof(TV) == 8) return launch_bpass_q<TV, TX, NW, BP_Z0>(qw, grid, a, s);
-      return hipErrorInvalidValue;
-    case BP_ZD:
-      if constexpr (sizeof(TV) == 8) return launch_bpass_q<TV, double, NW, BP_ZD>(qw, grid, a, s);
-      return hipErrorInvalidValue;
-    case BP_ZR: return launch_bpass_q<TV, TX, NW, BP_ZR>(qw, grid, a, s);
-    default: return launch_bpass_q<TV, double, NW, BP_Z2>(qw, grid, a, s);
+    case BP_R1: return launch_bpass_q<TV, TX, BP_R1>(sh.nw, sh.qw, grid, a, s);
+    case BP_Z1: return launch_bpass_q<TV, TX, BP_Z1>(sh.nw, sh.qw, grid, a, s);
+    case BP_D: return launch_bpass_q<TV, double, BP_D>(sh.nw, sh.qw, grid, a, s);
+    case BP_ZR: return launch_bpass_q<TV, TX, BP_ZR>(sh.nw, sh.qw, grid, a, s);
+    default: return launch_bpass_q<TV, double, BP_Z2>(sh.nw, sh.qw, grid, a, s);
   }
 }
 
-// Tile widths the block passes take: an FP64 window beyond 256 columns needs
-// more accumulator registers than a 16-wavefront workgroup has (a wider FP64
-// basis goes through the passes in windows of at most 256 columns).
-bool block_supported(bool tv_f64, int qw) { return !tv_f64 || qw <= 8; }
-
-hipError_t launch_bpass(int mode, bool tv_f64, bool tx_f64, int nw, int qw, int grid, const BlockArgs &a,
-                        hipStream_t s) {
+hipError_t launch_bpass(int mode, bool tv_f64, bool tx_f64, int grid, const BlockArgs &a, hipStream_t s) {
+  const BlockShape sh = block_shape(a.j);
+  if (sh.nw * sh.qw * 4 < a.j) return hipErrorInvalidValue;  // tile narrower than the basis
   if (tv_f64)
-    return tx_f64 ? launch_bpass_m<double, double, 16>(mode, qw, grid, a, s)
-                  : launch_bpass_m<double, float, 16>(mode, qw, grid, a, s);
-  if (nw == 4)
-    return tx_f64 ? launch_bpass_m<float, double, 4>(mode, qw, grid, a, s)
-                  : launch_bpass_m<float, float, 4>(mode, qw, grid, a, s);
-  return tx_f64 ? launch_bpass_m<float, double, 8>(mode, qw, grid, a, s)
-                : launch_bpass_m<float, float, 8>(mode, qw, grid, a, s);
+    return tx_f64 ? launch_bpass_m<double, double>(mode, sh, grid, a, s)
+                  : launch_bpass_m<double, float>(mode, sh, grid, a, s);
+  return tx_f64 ? launch_bpass_m<float, double>(mode, sh, grid, a, s)
+                : launch_bpass_m<float, float>(mode, sh, grid, a, s);
 }
 
 template <typename TV, typename TX>

@@ -93,6 +93,15 @@ __device__ __forceinline__ double buf_load_scalar<double>(__amdgpu_buffer_rsrc_t
   return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, 0));
 }
 
+// the value as stored (a conversion next to the load would wait for it)
+template <typename T>
+__device__ __forceinline__ T buf_load_raw(__amdgpu_buffer_rsrc_t r, unsigned off) {
+  if constexpr (sizeof(T) == 4)
+    return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0));
+  else
+    return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, 0));
+}
+
 template <typename T>
 __device__ __forceinline__ void buf_store_scalar(T v, __amdgpu_buffer_rsrc_t r, unsigned off);
 template <>

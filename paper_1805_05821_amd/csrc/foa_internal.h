@@ -190,7 +190,7 @@ struct BlockArgs {
   void *W;          // stored basis (panel layout)
   const void *x;    // first snapshot of the block; snapshot k at x + k * ldx (elements)
   int64_t ldx;
-  double *Z;        // n_pad x BPK block, panel layout [panel][k][64]
+  double *Z;        // n_pad x BPK block, in the passes' order of (row, k) pairs (k_bpass)
   double *coef;     // pass coefficients, [c * BPK + k]
   double *partb;    // block-pass partials, [(c * BPK + k) * ldg + slot]
   double *partg;    // block Gram partials, [slot * BPK * BPK + k * BPK + l]
@@ -198,7 +198,6 @@ struct BlockArgs {
   int *flag;        // nonzero: the block (or an earlier one) was rejected
   const int *gate;  // non-null: the kernel runs only while *gate is nonzero (third projection)
   int tlev;         // block passes: triangular factors T_0 .. T_{tlev-1} applied to each row of Z
-  int c0;           // block row passes: first basis column of the window (j columns from it)
   const void *xn;   // BP_ZR: first snapshot of the next block (same ldx and type as x)
   double *dnext;    // raw column sums V^T Y of the next block over this block's j columns, [c * BPK + k]
   double *partq;    // ZG_YNQ partials of (previous block's new columns)^T Y, [slot * BPK * BPK + c * BPK + k]
@@ -209,6 +208,7 @@ struct BlockArgs {
   int j, n_max, ldg, ldH, ldB;
   int G;            // workgroups of the block passes (partial slots)
   int Gz;           // workgroups of the block Gram passes
+  int Gg;           // slots of partg: G after a block row pass, Gz after a Gram pass
 };
 
 // ---- one-reduction form (foa_lowsync.hip) -----------------------------------
@@ -257,9 +257,12 @@ struct LsSmall {
 hipError_t launch_pass(int mode, bool tv_f64, bool tx_f64, bool prefetch, int nw, int grid,
                        const PassArgs &a, hipStream_t s);
 // blocked form (foa_block.hip)
-bool block_supported(bool tv_f64, int qw);
-hipError_t launch_bpass(int mode, bool tv_f64, bool tx_f64, int nw, int qw, int grid, const BlockArgs &a,
-                        hipStream_t s);
+struct BlockShape {
+  int nw, qw;   // wavefronts per workgroup, groups of four columns per wavefront
+  int per_cu;   // workgroups a CU holds
+};
+BlockShape block_shape(int j);
+hipError_t launch_bpass(int mode, bool tv_f64, bool tx_f64, int grid, const BlockArgs &a, hipStream_t s);
 hipError_t launch_zgram(int mode, bool tv_f64, bool tx_f64, int grid, const BlockArgs &a, hipStream_t s);
 hipError_t launch_breduce(int mode, const BlockArgs &a, hipStream_t s);
 hipError_t launch_bchol(int round, const BlockArgs &a, hipStream_t s);

@@ -227,3 +227,33 @@ def test_blocked_argument_errors():
         F.foa_push_blocked(s.ctx, X, 1000, 4, F.FOA_F32, small, small.numel())
     assert ei.value.code == F.FOA_E_NOMEM
     s.close()
+
+
+@pytest.mark.parametrize("prec,n,N", [
+    ("f64", 70, 30),      # the last panel's second half has no rows
+    ("f64", 97, 60),      # one row in the last half panel
+    ("f32", 70, 30),
+    ("f64", 1100, 276),   # 4 wavefronts up to 256 columns, 8 beyond
+    ("f64", 1500, 512),   # the widest tile, full
+    ("f32", 1500, 512),
+])
+def test_block_tiles(prec, n, N):
+    """Every tile width of the block passes and ragged last units, from single
+    snapshots on (ld > n, FP32 snapshots): Gaussian snapshots (kappa_2 < 20)
+    against the sequential oracle."""
+    import torch
+
+    from paper_1805_05821_amd.stream import FOAStream
+
+    X = np.random.default_rng(n + N).standard_normal((n, N)).astype(np.float32).astype(np.float64)
+    seq = oracle.foa_batch(X, tol=0.0)
+    Xd = torch.full((N, n + 5), float("nan"), dtype=torch.float32, device="cuda")
+    Xd[:, :n] = torch.from_numpy(np.ascontiguousarray(X.T)).to("cuda")
+    s = FOAStream(n, N, prec=prec, breakdown_tol=0.0, ws_fill=0xFF)
+    s.push_blocked(Xd[:, :n])
+    H, B, q, m = s.state()
+    g = dict(q=q, m=m, H=H, beta=B, V=s.basis(q).cpu().numpy().T)
+    eps = EPS64 if prec == "f64" else EPS32
+    kap, orth = _compare(g, seq, 10.0, eps, f"{prec} {n} x {N}")
+    assert orth <= 10 * np.sqrt(q) * eps
+    s.close()
