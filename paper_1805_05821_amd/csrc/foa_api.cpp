@@ -61,8 +61,8 @@ Layout make_layout(int64_t n, int n_max, foa_prec prec, int ldg) {
   L.coefB = take(vec);
   L.coefC = take(vec);
   L.st = take(sizeof(DevState));
-  // mode coefficients: FP64 k x r, or the padded FP32 layout of the MFMA path
-  L.mcoef = take(std::max((size_t)n_max * n_max * 8, (size_t)modes_kpad(n_max) * modes_rpad(n_max) * 4));
+  // mode coefficients in the layout of the path that takes them
+  L.mcoef = take(std::max((size_t)n_max * n_max * 8, modes_coef_bytes(n_max)));
   // one-reduction form: second partial-sum array (with the scalar rows), the
   // reduced sums and the prefix sums of the snapshot norms; with an FP32
   // basis also the partial sums of the finished column's rounding error, the

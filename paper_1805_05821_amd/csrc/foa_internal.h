@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <vector>
+
 namespace foa {
 
 // Rows per storage panel.  V lives in the workspace in "panel" layout: rows are
@@ -287,14 +289,16 @@ hipError_t launch_copy_basis(bool tv_f64, const void *W, const double *sigma, in
 hipError_t launch_init_state(const SmallArgs &a, double tol, hipStream_t s);
 // Phi = W * B for the panel-layout basis W (n x k used columns) and a k x r
 // coefficient matrix (sigma already folded in); Phi is column-major with
-// leading dimension ld.  Two coefficient layouts, chosen by modes_use_mfma:
-//  * FP32 MFMA path (FP32 basis and FP32 output): B is FP32, row-major
-//    modes_kpad(k) x modes_rpad(r) (mode index contiguous), zero-padded;
-//  * otherwise: B is FP64, column-major k x r (leading dimension k).
-bool modes_use_mfma(bool tv_f64, bool out_f64);
-int modes_kpad(int k);
+// leading dimension ld.  The coefficients go to the device as modes_pack lays
+// them out for the path: MODES_F64 (FP64 products; FP64 basis or output),
+// MODES_SPLIT and MODES_F32 (FP32 basis and output).
+enum { MODES_F64 = 0, MODES_F32 = 1, MODES_SPLIT = 2 };
+int modes_path(bool tv_f64, bool out_f64);  // MODES_F64 or MODES_F32
+bool modes_split_ok(const float *B, int k, int r, size_t ldp);  // B as packed for MODES_F32
 int modes_rpad(int r);
-hipError_t launch_modes_gemm(bool tv_f64, const void *W, int64_t n, int n_max, int k,
+size_t modes_coef_bytes(int n_max);  // largest packed size for k, r <= n_max
+void modes_pack(int path, const double *B, int k, int r, std::vector<char> &out);  // B: column-major k x r
+hipError_t launch_modes_gemm(int path, bool tv_f64, const void *W, int64_t n, int n_max, int k,
                              const void *B, int r, void *out, int64_t ld, bool out_f64,
                              hipStream_t s);
 

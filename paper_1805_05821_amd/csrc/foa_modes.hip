@@ -1,43 +1,261 @@
 // Mode reconstruction Phi = V B (the modes of Algorithm 1): the panel-layout
 // basis W (n x k columns in use, FP32 or FP64) times the k x r coefficient
 // matrix B (FP64, sigma folded in, packed real columns).  An FP32 basis with
-// FP32 output runs on FP32 MFMA; every other combination uses the FP64-
-// accumulating row kernel.
+// FP32 output runs on bf16 MFMA with every value split in three (FP32 MFMA for
+// coefficients outside the split's range), every other combination on FP64
+// MFMA.
 #include <algorithm>
+#include <cmath>
+#include <cstring>
 
 #include "foa_buffer.h"
 #include "foa_internal.h"
 
 namespace foa {
 
-// Reference kernel: one thread per row, 16 output columns per block column,
-// the block's 16 columns of B staged in LDS, FP64 accumulation.
-template <typename TV, typename TO>
-__global__ __launch_bounds__(256) void k_modes_rowwise(const TV *W, int64_t n, int n_max, int k,
-                                                       const double *B, int r, TO *out, int64_t ld) {
-  __shared__ double sB[512 * 16];
-  const int c0 = blockIdx.y * 16;
-  const int nc = min(16, r - c0);
-  for (int idx = threadIdx.x; idx < k * 16; idx += 256) {
-    const int l = idx / 16, cc = idx % 16;
-    sB[idx] = cc < nc ? B[(size_t)(c0 + cc) * k + l] : 0.0;
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4v __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+
+// FP64-accumulating kernel (FP64 basis or FP64 output): Phi^T = B^T W^T on
+// v_mfma_f64_16x16x4.  A wavefront owns 32 rows (two row tiles: the even and the
+// odd rows, so a lane's load is two consecutive rows) x MB 16-mode blocks; four
+// wavefronts share the coefficients, staged through LDS 16 basis columns at a
+// time.  The basis goes straight from memory to the operand registers, the next
+// stage's columns one stage ahead: each is used by its own wavefront alone.
+// Coefficients come as operand fragments, [k / 4][mode / 16][lane]: mode lane %
+// 16, column lane / 16 (D: row = lane % 16, mode 4 t + lane / 16).
+// Bound: the FP64 matrix rate (78.6 TFLOP/s); 2 n k r flops.  One thread per row
+// with 16 modes' sums in registers (each reading the basis again, every product
+// behind an LDS read) ran 2^18 x 149 x 60 in 438 us, 10.7 TFLOP/s.
+constexpr int M64_K = 16, M64_MB = 8;
+
+template <typename TV, typename TO, int MB>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_modes_mfma64(
+    const TV *W, int64_t n, int64_t P, int n_max, int kdim, const double *Bf, int rblocks, int r, TO *out, int64_t ld) {
+  constexpr int KS = M64_K / 4;      // MFMA steps of a stage
+  constexpr int FR = KS * MB;        // fragments of a stage (512 bytes each)
+  constexpr int NL = (FR + 3) / 4;   // loads per wavefront
+  __shared__ double sB[FR * 64];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t m0 = (int64_t)blockIdx.x * 128 + wave * 32;
+  const int64_t p = m0 / PANEL;
+  const int mb0 = blockIdx.y * MB;
+  // columns beyond kdim (and a panel beyond the last) read as 0
+  const __amdgpu_buffer_rsrc_t rw =
+      make_rsrc(W + (size_t)(p < P ? p : 0) * n_max * PANEL, p < P ? (unsigned)(kdim * PANEL * sizeof(TV)) : 0u);
+  const unsigned woff = (unsigned)(((lane >> 4) * PANEL + (int)(m0 % PANEL) + 2 * (lane & 15)) * sizeof(TV));
+  f64x4 acc[2][MB];
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int b = 0; b < MB; ++b) acc[a][b] = f64x4{0.0, 0.0, 0.0, 0.0};
+  TV w[KS][2];
+  double bn[NL];
+  auto load_w = [&](int k0) {
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      const unsigned off = woff + (unsigned)((k0 + 4 * s) * PANEL * sizeof(TV));
+      if constexpr (sizeof(TV) == 8) {
+        const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rw, (int)off, 0, kTileLoad);
+        w[s][0] = __builtin_bit_cast(double, u32x2{v.x, v.y});
+        w[s][1] = __builtin_bit_cast(double, u32x2{v.z, v.w});
+      } else {
+        const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rw, (int)off, 0, kTileLoad);
+        typedef float f32x2 __attribute__((ext_vector_type(2)));
+        const f32x2 f = __builtin_bit_cast(f32x2, v);
+        w[s][0] = f.x;
+        w[s][1] = f.y;
+      }
+    }
+  };
+  auto load_b = [&](int k0) {
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      const int f = wave + 4 * i;  // fragment of the stage: step f / MB, mode block f % MB
+      if (f < FR) bn[i] = Bf[((size_t)(k0 / 4 + f / MB) * rblocks + mb0 + f % MB) * 64 + lane];
+    }
+  };
+  load_b(0);
+  load_w(0);
+  for (int k0 = 0; k0 < kdim; k0 += M64_K) {
+    if (k0) __syncthreads();
+#pragma unroll
+    for (int i = 0; i < NL; ++i)
+      if (wave + 4 * i < FR) sB[(wave + 4 * i) * 64 + lane] = bn[i];
+    __syncthreads();
+    TV wc[KS][2];
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      wc[s][0] = w[s][0];
+      wc[s][1] = w[s][1];
+    }
+    if (k0 + M64_K < kdim) {
+      load_b(k0 + M64_K);
+      load_w(k0 + M64_K);
+    }
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      const double w0 = (double)wc[s][0], w1 = (double)wc[s][1];
+#pragma unroll
+      for (int b = 0; b < MB; ++b) {
+        const double c = sB[(s * MB + b) * 64 + lane];
+        acc[0][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(c, w0, acc[0][b], 0, 0, 0);
+        acc[1][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(c, w1, acc[1][b], 0, 0, 0);
+      }
+    }
   }
-  __syncthreads();
-  const int64_t row = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int64_t row = m0 + 2 * (lane & 15);
   if (row >= n) return;
-  const TV *base = W + (size_t)(row / PANEL) * n_max * PANEL + (row % PANEL);
-  double acc[16];
+  const bool both = row + 1 < n;
 #pragma unroll
-  for (int cc = 0; cc < 16; ++cc) acc[cc] = 0.0;
-  for (int l = 0; l < k; ++l) {
-    const double w = (double)base[(size_t)l * PANEL];
+  for (int b = 0; b < MB; ++b)
 #pragma unroll
-    for (int cc = 0; cc < 16; ++cc) acc[cc] = fma(w, sB[l * 16 + cc], acc[cc]);
-  }
-  for (int cc = 0; cc < nc; ++cc) out[(size_t)(c0 + cc) * ld + row] = (TO)acc[cc];
+    for (int t = 0; t < 4; ++t) {
+      const int mode = (mb0 + b) * 16 + 4 * t + (lane >> 4);
+      if (mode < r) {
+        TO *o = out + (size_t)mode * ld + row;
+        o[0] = (TO)acc[0][b][t];
+        if (both) o[1] = (TO)acc[1][b][t];
+      }
+    }
 }
 
-// MFMA kernel (FP32 basis, FP32 output): Phi^T = B^T W^T on 32x32x2 FP32 MFMA
+// FP32 basis and FP32 output on the bf16 matrix units: every FP32 value is the
+// sum of three bf16 values exactly, w = w1 + w2 + w3 (w1 by truncation, which
+// cannot overflow; w2 the rest rounded to nearest; w3 what is left) and b likewise
+// (split by the caller, each piece to nearest), and the six products
+//   b1 w1 + (b1 w2 + b2 w1) + (b1 w3 + b2 w2 + b3 w1)
+// are accumulated in FP32; what is left out is below 2^-24 |b w|.  The products
+// are exact and 16 columns enter an accumulator at once, so the error against 64
+// bits is no larger than of FP32 products summed two columns at a time (see
+// modes_split_ok for the range of the coefficients).
+// Tile: 128 rows x 32 NB modes per workgroup, wavefront w its rows 32 w .. + 31.
+// The basis goes from memory straight to registers (lane: row lane % 32, eight
+// columns from 8 (lane / 32)) and is split there, one stage of 32 columns ahead;
+// the coefficients are staged through LDS as operand fragments, [k / 16][mode /
+// 32][piece][lane][8].
+// Bound: HBM (n k + n r values of 4 bytes) up to about 200 modes per pass, the
+// bf16 rate beyond.
+constexpr int MS_K = 32;
+
+template <int NB>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_modes_split(
+    const float *W, int64_t n, int64_t P, int n_max, int kdim, const u32x4 *Bf, int rblocks, int r, float *out,
+    int64_t ld) {
+  constexpr int KS = MS_K / 16;
+  constexpr int FR = KS * NB * 3;
+  constexpr int NL = (FR + 3) / 4;
+  __shared__ u32x4 sB[FR * 64];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+const int64_t m0 = (int64_t)blockIdx.x * 128 + wave * 32;
+  const int64_t p = m0 / PANEL;
+  const int rb0 = blockIdx.y * NB;
+  const __amdgpu_buffer_rsrc_t rw =
+      make_rsrc(W + (size_t)(p < P ? p : 0) * n_max * PANEL, p < P ? (unsigned)(kdim * PANEL * 4) : 0u);
+  const unsigned woff = (unsigned)(((lane >> 5) * 8 * PANEL + (int)(m0 % PANEL) + (lane & 31)) * 4);
+  const __amdgpu_buffer_rsrc_t rb = make_rsrc(Bf, (unsigned)((kdim + MS_K - 1) / MS_K * KS * rblocks * 3 * 1024));
+  f32x16 acc[NB];
+#pragma unroll
+  for (int b = 0; b < NB; ++b)
+#pragma unroll
+    for (int t = 0; t < 16; ++t) acc[b][t] = 0.f;
+  unsigned w[KS][8];
+  u32x4 bn[NL];
+  auto load_w = [&](int k0) {
+#pragma unroll
+    for (int s = 0; s < KS; ++s)
+#pragma unroll
+      for (int m = 0; m < 8; ++m)
+        w[s][m] = __builtin_amdgcn_raw_buffer_load_b32(rw, (int)woff, (k0 + 16 * s + m) * PANEL * 4, kTileLoad);
+  };
+  auto load_b = [&](int k0) {
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      const int f = wave + 4 * i;  // step f / (3 NB), block and piece f % (3 NB)
+      if (f < FR)
+        bn[i] = __builtin_amdgcn_raw_buffer_load_b128(
+            rb, lane * 16, (((k0 / 16 + f / (3 * NB)) * rblocks + rb0) * 3 + f % (3 * NB)) * 1024, 0);
+    }
+  };
+  load_b(0);
+  load_w(0);
+  for (int k0 = 0; k0 < kdim; k0 += MS_K) {
+    if (k0) __syncthreads();
+#pragma unroll
+    for (int i = 0; i < NL; ++i)
+      if (wave + 4 * i < FR) sB[(wave + 4 * i) * 64 + lane] = bn[i];
+    // the three pieces of this stage's values, two columns to a register
+    u32x4 w1[KS], w2[KS], w3[KS];
+#pragma unroll
+    for (int s = 0; s < KS; ++s)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const unsigned x0 = w[s][2 * q], x1 = w[s][2 * q + 1];
+        const float f0 = __builtin_bit_cast(float, x0), f1 = __builtin_bit_cast(float, x1);
+        w1[s][q] = __builtin_amdgcn_perm(x1, x0, 0x07060302u);  // the upper halves
+        const float r0 = f0 - __builtin_bit_cast(float, x0 & 0xffff0000u);
+        const float r1 = f1 - __builtin_bit_cast(float, x1 & 0xffff0000u);
+        typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+        const unsigned c2 = __builtin_bit_cast(unsigned, bf16x2{(__bf16)r0, (__bf16)r1});
+        w2[s][q] = c2;
+        const float t0 = r0 - __builtin_bit_cast(float, c2 << 16);
+        const float t1 = r1 - __builtin_bit_cast(float, c2 & 0xffff0000u);
+        w3[s][q] = __builtin_bit_cast(unsigned, bf16x2{(__bf16)t0, (__bf16)t1});
+      }
+    __syncthreads();
+    if (k0 + MS_K < kdim) {
+      load_b(k0 + MS_K);
+      load_w(k0 + MS_K);
+    }
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      const bf16x8 W1 = __builtin_bit_cast(bf16x8, w1[s]), W2 = __builtin_bit_cast(bf16x8, w2[s]),
+                   W3 = __builtin_bit_cast(bf16x8, w3[s]);
+      // mode blocks in pairs, so that consecutive products go to different sums
+#pragma unroll
+      for (int b = 0; b < NB; b += 2) {
+        bf16x8 B[2];
+        auto piece = [&](int c) {
+#pragma unroll
+          for (int i = 0; i < 2; ++i)
+            if (b + i < NB) B[i] = __builtin_bit_cast(bf16x8, sB[((s * NB + b + i) * 3 + c) * 64 + lane]);
+        };
+        auto term = [&](const bf16x8 &w) {
+#pragma unroll
+          for (int i = 0; i < 2; ++i)
+            if (b + i < NB) acc[b + i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(B[i], w, acc[b + i], 0, 0, 0);
+        };
+        piece(2);
+        term(W1);
+        piece(1);
+        term(W2);
+        term(W1);
+        piece(0);
+        term(W3);
+        term(W2);
+        term(W1);
+      }
+    }
+  }
+  // D[i][j]: j = lane % 32 (data row), i = 8 (t / 4) + 4 (lane / 32) + t % 4 (mode)
+  const int64_t row = m0 + (lane & 31);
+  if (row >= n) return;
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+#pragma unroll
+    for (int t = 0; t < 16; ++t) {
+      const int mode = (rb0 + b) * 32 + 8 * (t >> 2) + 4 * (lane >> 5) + (t & 3);
+      if (mode < r) out[(size_t)mode * ld + row] = acc[b][t];
+    }
+  }
+}
+
+// FP32-product kernel (FP32 basis, FP32 output, coefficients outside the range
+// of k_modes_split): Phi^T = B^T W^T on 32x32x2 FP32 MFMA
 // with FP32 accumulation.  Tile: 128 data rows (two panels) x 32*NB mode
 // columns per workgroup; wavefront w owns data rows 32w..32w+31 and all NB
 // 32-mode blocks, so for r <= 256 the basis is read exactly once.  k advances
@@ -50,18 +268,97 @@ __global__ __launch_bounds__(256) void k_modes_rowwise(const TV *W, int64_t n, i
 // k-offset l/32), B = W^T (lane l holds data row l%32, k-offset l/32); the
 // result D[i][j] has j = lane % 32, so each store instruction writes 32
 // consecutive rows of one mode column.
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x4v __attribute__((ext_vector_type(4)));
-
 constexpr int MT_ROWS = 128, MT_K = 32, MT_LDA = 160;
 
-__host__ __device__ constexpr int mfma_nb(int r) { return r <= 32 ? 1 : (r + 31) / 32 < 8 ? (r + 31) / 32 : 8; }
+// 32-mode blocks per workgroup (at most 8): the blocks of r modes split evenly
+// over the fewest workgroups
+__host__ __device__ constexpr int mfma_nb(int r) {
+  const int all = r <= 32 ? 1 : (r + 31) / 32, wgs = (all + 7) / 8;
+  return (all + wgs - 1) / wgs;
+}
 
-bool modes_use_mfma(bool tv_f64, bool out_f64) { return !tv_f64 && !out_f64; }
 int modes_kpad(int k) { return (k + MT_K - 1) / MT_K * MT_K; }
 int modes_rpad(int r) {
   const int t = 32 * mfma_nb(r);
   return (r + t - 1) / t * t;
+}
+
+// mode blocks of 16 per workgroup of the FP64 kernel, and all of them (whole workgroups)
+static int m64_mb(int r) {
+  const int all = r <= 16 ? 1 : (r + 15) / 16, wgs = (all + M64_MB - 1) / M64_MB;
+  return (all + wgs - 1) / wgs;
+}
+static int m64_blocks(int r) {
+  const int mb = m64_mb(r), all = (r + 15) / 16;
+  return (all + mb - 1) / mb * mb;
+}
+
+// An upper bound of every path's packed size: splitting the blocks evenly over
+// up to 2 (32-mode) or 4 (16-mode) workgroups adds at most 1 or 3 blocks.
+size_t modes_coef_bytes(int n_max) {
+  const size_t k = (size_t)modes_kpad(n_max);
+  return std::max(k * ((n_max + 31) / 32 + 1) * 32 * 6, k * ((n_max + 15) / 16 + 3) * 16 * 8);
+}
+
+// The range in which three bf16 pieces carry an FP32 coefficient and the basis
+// values beside it without loss: a coefficient is a column's scale sigma (the
+// stored column has norm 1 / sigma) times an entry of a unit vector, so bounds on
+// the largest coefficient of each basis column bound both.  Products outside go
+// to the FP32 kernel.
+bool modes_split_ok(const float *B, int k, int r, size_t ldp) {
+  for (int l = 0; l < k; ++l) {
+    float m = 0.f;
+    for (int c = 0; c < r; ++c) {
+      const float v = std::fabs(B[(size_t)l * ldp + c]);
+      if (!(v <= 0x1p60f)) return false;  // also NaN
+      m = std::max(m, v);
+    }
+    if (m != 0.f && m < 0x1p-60f) return false;
+  }
+  return true;
+}
+
+int modes_path(bool tv_f64, bool out_f64) { return !tv_f64 && !out_f64 ? MODES_F32 : MODES_F64; }
+
+// FP32 value to three bf16 values, each to nearest even (finite, |v| <= 2^60)
+static void split3(float v, uint16_t (&o)[3]) {
+  for (int i = 0; i < 3; ++i) {
+    uint32_t u;
+    std::memcpy(&u, &v, 4);
+    u = (u + 0x7fffu + ((u >> 16) & 1u)) & 0xffff0000u;
+    o[i] = (uint16_t)(u >> 16);
+    float f;
+    std::memcpy(&f, &u, 4);
+    v -= f;
+  }
+}
+
+void modes_pack(int path, const double *B, int k, int r, std::vector<char> &out) {
+  if (path == MODES_F64) {
+    const int ks = (k + M64_K - 1) / M64_K * (M64_K / 4), rb = m64_blocks(r);
+    out.assign((size_t)ks * rb * 64 * 8, 0);
+    double *o = reinterpret_cast<double *>(out.data());
+    for (int c = 0; c < r; ++c)
+      for (int l = 0; l < k; ++l) o[((size_t)(l / 4) * rb + c / 16) * 64 + (l % 4) * 16 + c % 16] = B[(size_t)c * k + l];
+    return;
+  }
+  const int kp = modes_kpad(k), rp = modes_rpad(r);
+  if (path == MODES_F32) {
+    out.assign((size_t)kp * rp * 4, 0);
+    float *o = reinterpret_cast<float *>(out.data());
+    for (int c = 0; c < r; ++c)
+      for (int l = 0; l < k; ++l) o[(size_t)l * rp + c] = (float)B[(size_t)c * k + l];
+    return;
+  }
+  out.assign((size_t)kp * rp * 6, 0);
+  uint16_t *o = reinterpret_cast<uint16_t *>(out.data());
+  for (int c = 0; c < r; ++c)
+    for (int l = 0; l < k; ++l) {
+      uint16_t q[3];
+      split3((float)B[(size_t)c * k + l], q);
+      for (int i = 0; i < 3; ++i)
+        o[((((size_t)(l / 16) * (rp / 32) + c / 32) * 3 + i) * 64 + (l % 16) / 8 * 32 + c % 32) * 8 + l % 8] = q[i];
+    }
 }
 
 // Up to NB = 5 the registers fit three wavefronts per SIMD (three workgroups
@@ -183,27 +480,73 @@ static void launch_mfma(const float *W, int64_t n, int n_max, int k, const float
   }
 }
 
-hipError_t launch_modes_gemm(bool tv_f64, const void *W, int64_t n, int n_max, int k, const void *Bv, int r,
+template <int NB>
+static void launch_split_nb(const float *W, int64_t n, int n_max, int k, const u32x4 *Bf, int r, float *out, int64_t ld,
+                            hipStream_t s) {
+  const int rb = modes_rpad(r) / 32;
+  dim3 g((unsigned)((n + 127) / 128), (unsigned)(rb / NB));
+  hipLaunchKernelGGL((k_modes_split<NB>), g, dim3(256), 0, s, W, n, (n + PANEL - 1) / PANEL, n_max, k, Bf, rb, r, out,
+                     ld);
+}
+
+static void launch_split(const float *W, int64_t n, int n_max, int k, const u32x4 *Bf, int r, float *out, int64_t ld,
+                         hipStream_t s) {
+  switch (mfma_nb(r)) {
+    case 1: launch_split_nb<1>(W, n, n_max, k, Bf, r, out, ld, s); break;
+    case 2: launch_split_nb<2>(W, n, n_max, k, Bf, r, out, ld, s); break;
+    case 3: launch_split_nb<3>(W, n, n_max, k, Bf, r, out, ld, s); break;
+    case 4: launch_split_nb<4>(W, n, n_max, k, Bf, r, out, ld, s); break;
+    case 5: launch_split_nb<5>(W, n, n_max, k, Bf, r, out, ld, s); break;
+    case 6: launch_split_nb<6>(W, n, n_max, k, Bf, r, out, ld, s); break;
+    case 7: launch_split_nb<7>(W, n, n_max, k, Bf, r, out, ld, s); break;
+    default: launch_split_nb<8>(W, n, n_max, k, Bf, r, out, ld, s); break;
+  }
+}
+
+template <typename TV, typename TO, int MB>
+static void launch_m64_mb(const TV *W, int64_t n, int n_max, int k, const double *Bf, int r, TO *out, int64_t ld,
+                          hipStream_t s) {
+  const int rb = m64_blocks(r);
+  dim3 g((unsigned)((n + 127) / 128), (unsigned)(rb / MB));
+  hipLaunchKernelGGL((k_modes_mfma64<TV, TO, MB>), g, dim3(256), 0, s, W, n, (n + PANEL - 1) / PANEL, n_max, k, Bf, rb, r,
+                     out, ld);
+}
+
+template <typename TV, typename TO>
+static void launch_m64(const void *W, int64_t n, int n_max, int k, const double *Bf, int r, void *out, int64_t ld,
+                       hipStream_t s) {
+  const TV *w = (const TV *)W;
+  TO *o = (TO *)out;
+  switch (m64_mb(r)) {
+    case 1: launch_m64_mb<TV, TO, 1>(w, n, n_max, k, Bf, r, o, ld, s); break;
+    case 2: launch_m64_mb<TV, TO, 2>(w, n, n_max, k, Bf, r, o, ld, s); break;
+    case 3: launch_m64_mb<TV, TO, 3>(w, n, n_max, k, Bf, r, o, ld, s); break;
+    case 4: launch_m64_mb<TV, TO, 4>(w, n, n_max, k, Bf, r, o, ld, s); break;
+    case 5: launch_m64_mb<TV, TO, 5>(w, n, n_max, k, Bf, r, o, ld, s); break;
+    case 6: launch_m64_mb<TV, TO, 6>(w, n, n_max, k, Bf, r, o, ld, s); break;
+    case 7: launch_m64_mb<TV, TO, 7>(w, n, n_max, k, Bf, r, o, ld, s); break;
+    default: launch_m64_mb<TV, TO, 8>(w, n, n_max, k, Bf, r, o, ld, s); break;
+  }
+}
+
+hipError_t launch_modes_gemm(int path, bool tv_f64, const void *W, int64_t n, int n_max, int k, const void *Bv, int r,
                              void *out, int64_t ld, bool out_f64, hipStream_t s) {
   if (r <= 0 || k <= 0) return hipSuccess;
-  if (k > 512) return hipErrorInvalidValue;
-  if (modes_use_mfma(tv_f64, out_f64)) {
+  if (k > 512 || k > n_max) return hipErrorInvalidValue;
+  if (path == MODES_SPLIT && !tv_f64 && !out_f64)
+    launch_split((const float *)W, n, n_max, k, (const u32x4 *)Bv, r, (float *)out, ld, s);
+  else if (path == MODES_F32 && !tv_f64 && !out_f64)
     launch_mfma((const float *)W, n, n_max, k, (const float *)Bv, r, (float *)out, ld, s);
-    return hipGetLastError();
-  }
-  const double *B = (const double *)Bv;
-  dim3 grid((unsigned)((n + 255) / 256), (unsigned)((r + 15) / 16));
-  if (tv_f64) {
-    if (out_f64)
-      hipLaunchKernelGGL((k_modes_rowwise<double, double>), grid, dim3(256), 0, s, (const double *)W, n, n_max, k,
-                         B, r, (double *)out, ld);
-    else
-      hipLaunchKernelGGL((k_modes_rowwise<double, float>), grid, dim3(256), 0, s, (const double *)W, n, n_max, k,
-                         B, r, (float *)out, ld);
-  } else {
-    hipLaunchKernelGGL((k_modes_rowwise<float, double>), grid, dim3(256), 0, s, (const float *)W, n, n_max, k, B,
-                       r, (double *)out, ld);
-  }
+  else if (path != MODES_F64)
+    return hipErrorInvalidValue;
+  else if (tv_f64 && out_f64)
+    launch_m64<double, double>(W, n, n_max, k, (const double *)Bv, r, out, ld, s);
+  else if (tv_f64)
+    launch_m64<double, float>(W, n, n_max, k, (const double *)Bv, r, out, ld, s);
+  else if (out_f64)
+    launch_m64<float, double>(W, n, n_max, k, (const double *)Bv, r, out, ld, s);
+  else
+    return hipErrorInvalidValue;
   return hipGetLastError();
 }
 

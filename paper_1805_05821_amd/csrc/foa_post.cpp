@@ -247,29 +247,28 @@ foa_status foa_modes(foa_ctx c, int32_t m_max, double *h_lambda, int8_t *h_kind,
   // packed real coefficients, sigma folded in: V = W diag(sigma)
   const int m = d.m;
   const bool v64 = c->prec == FOA_PREC_F64, o64 = phi_dtype == FOA_F64;
-  const bool mfma = modes_use_mfma(v64, o64);
-  const size_t ldp = mfma ? (size_t)modes_rpad(ncols) : 1;   // stride between rows l
-  const size_t cst = mfma ? 1 : (size_t)m;                    // stride between columns
-  std::vector<double> Bp(mfma ? (size_t)modes_kpad(m) * ldp : (size_t)m * ncols, 0.0);
+  std::vector<double> Bp((size_t)m * ncols, 0.0);
   int col = 0;
   for (int e = 0; e < cnt; ++e) {
     const int i = d.entries[e];
     const cd *b = d.B.data() + (size_t)i * m;
-    for (int l = 0; l < m; ++l) Bp[col * cst + l * ldp] = c->hsigma[l] * b[l].real();
+    for (int l = 0; l < m; ++l) Bp[(size_t)col * m + l] = c->hsigma[l] * b[l].real();
     ++col;
     if (!d.is_real[i]) {
-      for (int l = 0; l < m; ++l) Bp[col * cst + l * ldp] = c->hsigma[l] * b[l].imag();
+      for (int l = 0; l < m; ++l) Bp[(size_t)col * m + l] = c->hsigma[l] * b[l].imag();
       ++col;
     }
   }
   void *dB = static_cast<char *>(c->ws) + c->L.mcoef;
-  hipError_t e;
-  if (mfma) {
-    std::vector<float> Bf(Bp.begin(), Bp.end());
-    e = hipMemcpy(dB, Bf.data(), Bf.size() * sizeof(float), hipMemcpyHostToDevice);
-  } else {
-    e = hipMemcpy(dB, Bp.data(), Bp.size() * sizeof(double), hipMemcpyHostToDevice);
+  int path = modes_path(v64, o64);
+  std::vector<char> packed;
+  modes_pack(path, Bp.data(), m, ncols, packed);
+  if (path == MODES_F32 &&
+      modes_split_ok(reinterpret_cast<const float *>(packed.data()), m, ncols, (size_t)modes_rpad(ncols))) {
+    path = MODES_SPLIT;
+    modes_pack(path, Bp.data(), m, ncols, packed);
   }
+  hipError_t e = hipMemcpy(dB, packed.data(), packed.size(), hipMemcpyHostToDevice);
   if (e != hipSuccess) return hip_err(c, e, "hipMemcpy mode coefficients");
   hipEvent_t e0 = nullptr, e1 = nullptr;
   if (c->profile) {
@@ -277,7 +276,7 @@ foa_status foa_modes(foa_ctx c, int32_t m_max, double *h_lambda, int8_t *h_kind,
     e1 = take_event(c);
     if (e0 && e1) (void)hipEventRecord(e0, c->stream);
   }
-  e = launch_modes_gemm(v64, c->W, c->n, c->n_max, m, dB, ncols, d_phi, ld_phi, o64, c->stream);
+  e = launch_modes_gemm(path, v64, c->W, c->n, c->n_max, m, dB, ncols, d_phi, ld_phi, o64, c->stream);
   if (c->profile && e0 && e1) {
     (void)hipEventRecord(e1, c->stream);
     c->ev_pending.push_back({e0, e1, 2.0 * (double)c->n * m * ncols, 1});

@@ -263,3 +263,54 @@ def test_mfma_modes_match_oracle(n, N, r_force):
              f"max phase-aligned column error {worst_err:.2e}, max err/bound {worst:.2e}")
     assert worst <= 1.0
     s.close()
+
+
+@pytest.mark.parametrize("prec,n,N,scale", [
+    ("f64", 40, 2, 1.0), ("f64", 127, 18, 1.0), ("f64", 129, 17, 1.0),   # 1, 16 and 17 modes
+    ("f64", 1000, 130, 1.0), ("f64", 64 * 5 + 33, 146, 1.0),             # two groups of 16-mode blocks
+    ("f32", 40, 2, 1.0), ("f32", 128, 33, 1.0), ("f32", 161, 34, 1.0),
+    ("f32", 1000, 161, 1.0), ("f32", 900, 258, 1.0),                     # 257 modes: two workgroups of blocks
+    ("f32", 700, 50, 2.0 ** 70), ("f32", 700, 50, 2.0 ** -70),           # beyond the range of the split
+])
+def test_mode_kernels(prec, n, N, scale):
+    """Every reconstruction kernel at the edges of its tiles (rows, mode
+    blocks, column stages), with more capacity than snapshots in a workspace
+    of NaN bytes: FP64 output against V z with z from numpy's eigenpairs of the
+    device's H (eigenvector sensitivity times rounding, plus k FP64
+    multiply-adds), FP32 output against the FP64 output of the same stream
+    ((k + 2) sqrt(k) 2^-24, as above)."""
+    import torch
+
+    import parity_bounds as PB
+    from gpu_helpers import EPS64
+    from paper_1805_05821_amd import foa as F
+
+    X = np.random.default_rng(n + N).standard_normal((n, N)).astype(np.float32) * np.float32(scale)
+    g = run_gpu(X, prec, tol=0.0, n_max=N + 21)
+    s, m = g["stream"], g["m"]
+    assert m == N - 1
+    phi = torch.full((m + 1, n), float("nan"), dtype=torch.float64, device="cuda")
+    lam, kind, amp, err = F.foa_modes(s.ctx, m, phi, n, m + 1, F.FOA_F64)
+    assert int(np.sum(np.where(kind == 1, 2, 1))) == m and torch.isnan(phi[m]).all()
+    P64 = phi[:m].cpu().numpy()
+    Hm = g["H"][:m, :m]
+    lam_c, Z, Yn, cond = PB.eig_condition(Hm)
+    sens = PB.eigvec_sensitivity(lam_c, Z, Yn)
+    Pg = PB.unpack(P64.T, kind)
+    ja, jb = PB.match(lam, lam_c)
+    hn = np.linalg.norm(Hm, 2)
+    worst = 0.0
+    for a, b in zip(ja, jb):
+        ref = g["V"][:, :m] @ (Z[:, b] / np.linalg.norm(Z[:, b]))
+        tol = PB.C * m * EPS64 * hn * sens[b] + (m + 2) * np.sqrt(m) * 2.0 ** -52
+        worst = max(worst, PB.phase_aligned_error(Pg[a], ref) / tol)
+    announce(f"{prec} n={n} m={m}: FP64 output err/bound {worst:.2e}")
+    assert worst <= 1.0
+    if prec == "f32":
+        p32 = torch.full((m + 1, n), float("nan"), dtype=torch.float32, device="cuda")
+        F.foa_modes(s.ctx, m, p32, n, m + 1, F.FOA_F32)
+        assert torch.isnan(p32[m]).all()
+        e = np.linalg.norm(p32[:m].double().cpu().numpy() - P64, axis=1) / np.linalg.norm(P64, axis=1)
+        announce(f"FP32 output err {e.max():.2e}")
+        assert e.max() <= (m + 2) * np.sqrt(m) * 2.0 ** -24
+    s.close()
