@@ -287,7 +287,7 @@ foa_status enqueue_push(foa_ctx_s *c, const void *x, bool x_f64) {
     }
     if ((e = timed_pass(c, PM_C, v64, x_f64, c->prefetch, G, pa, vbytes + nv * sV)) != hipSuccess)
       return hip_err(c, e, "pass C");
-    // one workgroup up to 256 columns: FP64 2^20 x 200, finalize and next b of
+    // one workgroup up to 255 columns: FP64 2^20 x 200, finalize and next b of
     // their own 4.8 + 9.4 us per push, together 5.5 us
     if (j <= kFinNextCols) {
       if ((e = launch_finalize_next(sa, s)) != hipSuccess) return hip_err(c, e, "finalize");

@@ -234,7 +234,8 @@ __device__ __forceinline__ void xst(double *p, double v) {
 // the reduced ||psi||^2 (PM_B), or h + s (PM_C, into a.hsum).  The sums come as
 // rows of rstride columns, one row per workgroup of that pass: a lane owns a
 // column, a wavefront a slice of the rows (16 loads in flight), and the
-// slices are added in order through s_p.  Bound: latency (a launch of its own
+// slices are added through s_p, all in the order of reduce_body (bitwise its
+// sums).  Bound: latency (a launch of its own
 // costs 2.6-2.9 us at any small size).  The pass's own sums go to another buffer
 // than a.rpart, which slower workgroups may still be reading.
 template <int NW, int JCAP, int MODE>
@@ -244,17 +245,43 @@ __device__ __forceinline__ void reduce_prologue(const PassArgs &a, double *s_c, 
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int j = a.j, G = a.rG;
   const int R = (j + 63) / 64;  // column chunks, at most NW
-  const int S = NW / R;         // row slices
+  // row slices: a power of two; slice sl takes the rows g with g % 64 in
+  // [sl * 64 / S, (sl + 1) * 64 / S), summed as reduce_body's butterfly sums them
+  const int S = NW >= 16 * R ? 16 : (NW >= 8 * R ? 8 : (NW >= 4 * R ? 4 : (NW >= 2 * R ? 2 : 1)));
   const int sl = wave / R, c = (wave - sl * R) * 64 + lane;
+  const int width = 64 / S;
   double t = 0.0;
   if (sl < S) {
     const double *pc = a.rpart + (c < j ? c : j - 1);
-    for (int g = sl; g < G; g += S * U) {
+    double pair = 0.0;
+    const int nch = (width + U - 1) / U;
+#pragma unroll 1
+    for (int k = 0; k < nch; ++k) {
       double v[U];
 #pragma unroll
-      for (int u = 0; u < U; ++u) v[u] = g + u * S < G ? pc[(size_t)(g + u * S) * a.rstride] : 0.0;
+      for (int u = 0; u < U; ++u) {
+        const int g = sl * width + k * U + u;
+        v[u] = u < width && g < G ? pc[(size_t)g * a.rstride] : 0.0;
+      }
+#pragma unroll 1
+      for (int g0 = 64; g0 < G; g0 += 64) {
 #pragma unroll
-      for (int u = 0; u < U; ++u) t += v[u];
+        for (int u = 0; u < U; ++u) {
+          const int g = g0 + sl * width + k * U + u;
+          v[u] += u < width && g < G ? pc[(size_t)g * a.rstride] : 0.0;
+        }
+      }
+#pragma unroll
+      for (int m = 1; m < U; m <<= 1) {
+#pragma unroll
+        for (int u = 0; u < U; u += 2 * m) v[u] += v[u + m];
+      }
+      if (k & 1) {
+        t += pair + v[0];
+      } else {
+        pair = v[0];
+        if (k + 1 == nch) t += pair;
+      }
     }
   }
   s_p[threadIdx.x] = t;
@@ -266,10 +293,16 @@ __device__ __forceinline__ void reduce_prologue(const PassArgs &a, double *s_c, 
   for (int i = threadIdx.x; i < JCAP; i += NW * 64) {
     double co = 0.0;
     if (i < j) {
-      double v = 0.0;
-      for (int k = 0; k < S; ++k) v += s_p[k * R * 64 + i];
+      double w[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        double x[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) x[k] = 4 * q + k < S ? s_p[(4 * q + k) * R * 64 + i] : 0.0;
+        w[q] = (x[0] + x[1]) + (x[2] + x[3]);
+      }
       const double sg = a.sigma[i];
-      v *= sg;
+      const double v = sg * ((w[0] + w[1]) + (w[2] + w[3]));
       co = sg * v;
       if (first) {
         if (MODE == PM_B) {
@@ -288,8 +321,9 @@ __device__ __forceinline__ void reduce_prologue(const PassArgs &a, double *s_c, 
   }
 }
 
-// RED: the sums may be laid out for, and reduced by, the next pass; CHECK: the
-// pass returns if the stream is not active.
+// RED: the preceding pass's sums are reduced here (a.rpart), and this pass's laid
+// out for the next to reduce (a.rstride); CHECK: the pass returns if the stream is
+// not active.
 template <typename TV, typename TX, int NW, int QW, int MODE, bool PREF, bool COH = false, bool RED = false,
           bool CHECK = false>
 __device__ __forceinline__ void row_pass_body(const PassArgs &a, int64_t pstart, int64_t pend, int64_t pstep,
@@ -369,11 +403,11 @@ __device__ __forceinline__ void row_pass_body(const PassArgs &a, int64_t pstart,
   // needed in LDS before the tile is (100037 x 128, FP32: pass A 12.1 us with
   // the tile behind them, 9.9 us so).
   static_assert(NC == 0 || JCAP <= NW * 64, "one coefficient per thread");
-  const bool red = RED && a.rpart != nullptr;
+  constexpr bool PRO = RED && MODE != PM_A;  // pass A follows no pass
   double cv[NCS];
 #pragma unroll
   for (int k = 0; k < NC; ++k) {
-    if (RED && k == NC - 1 && red) continue;  // the reduction below writes it
+    if (PRO && k == NC - 1) continue;  // the reduction below writes it
     cv[k] = xld<COH>(a.coef[K0 + k] + (tid < j ? tid : j - 1));
   }
   const double scale = (MODE == PM_INIT) ? 1.0 : uniform(a.st->scaleA);
@@ -386,12 +420,12 @@ __device__ __forceinline__ void row_pass_body(const PassArgs &a, int64_t pstart,
   __syncthreads();  // the previous call of this workgroup may still read LDS
 #pragma unroll
   for (int k = 0; k < NC; ++k) {
-    if (RED && k == NC - 1 && red) continue;
+    if (PRO && k == NC - 1) continue;
     if (tid < JCAP) s_coef[k][tid] = tid < j ? cv[k] : 0.0;
   }
-  if constexpr (RED) {
+  if constexpr (PRO) {
     // the row-sum buffers are free until the first panel
-    if (red) reduce_prologue<NW, JCAP, MODE>(a, s_coef[NC - 1], &s_red[0][0][0][0], slot == 0);
+    reduce_prologue<NW, JCAP, MODE>(a, s_coef[NC - 1], &s_red[0][0][0][0], slot == 0);
   }
   __syncthreads();
   if (PREF) {
@@ -528,7 +562,7 @@ __device__ __forceinline__ void row_pass_body(const PassArgs &a, int64_t pstart,
       const int c = cbase + g * GSTRIDE;
       if (rg == 0 && c < j) {
         // one row per workgroup where the next pass sums the columns itself
-        xst<COH>(a.part + (RED && a.rstride ? (size_t)slot * a.rstride + c : (size_t)c * a.ldg + slot), v);
+        xst<COH>(a.part + (RED ? (size_t)slot * a.rstride + c : (size_t)c * a.ldg + slot), v);
       }
     }
   }
@@ -741,18 +775,17 @@ __device__ inline void nextb_body_t(const SmallArgs &a, int chunk0) {
 
 __device__ inline void nextb_body(const SmallArgs &a, int chunk) { nextb_body_t<256>(a, chunk); }
 
-// finalize_body and nextb_body in one workgroup of NT threads, for bases of up
-// to kFinNextCols columns: the new columns of H_bar and beta stay in LDS, where
-// the next push's partial beta column takes them from, and every thread works
-// out the status for itself, so one barrier stands between the loads and the
-// products.  Bound: latency; at 64 columns 4.4 us, the two kernels 3.8 + 3.1 us
-// and a launch more.  64 rows x (NT / 64 / row chunks) l-slices, slices summed in order.
-template <int NT>
+// finalize_body and nextb_body in one workgroup of 1024 threads, for bases of up
+// to kFinNextCols columns, with the same sums in the same order (the results are
+// bitwise those of the two kernels).  The new columns of H_bar and beta stay in
+// LDS, where the next push's partial beta column takes them from, and every
+// thread works out the status for itself, so one barrier stands between the loads
+// and the products.  Bound: latency; at 64 columns 4.4 us, the two kernels 3.8 +
+// 3.1 us and a launch more.
 __device__ inline void finalize_next_body(const SmallArgs &a) {
-  constexpr int NWV = NT / 64;
-  __shared__ double s_n[NWV];
+  __shared__ double s_n[256];
   __shared__ double s_h[kFinNextCols + 1], s_b[kFinNextCols + 1];
-  __shared__ double s_p[NT];
+  __shared__ double s_p[16][64];
   DevState *st = a.st;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -763,38 +796,42 @@ __device__ inline void finalize_next_body(const SmallArgs &a) {
   const int status = st->status;
   const double bjj = a.beta[(size_t)(j - 1) * a.ldB + (j - 1)];
   const double xn2 = st->xn2, xf = st->xfro2 + xn2, tol = st->tol;
-  // b_i = sum_{l = max(i-1, 0)}^{j-1} H_bar[i, l] beta[l, j], i <= j; the column
-  // l = j - 1 comes from this push.  Wavefront: row chunk and l-slice
-  const int R = (J + 63) / 64, S = NWV / R;
-  const int sl = wave / R, i = (wave - sl * R) * 64 + lane;
-  const bool prod = sl < S && i < j;
+  // b_i = sum_{l = max(i-1, 0)}^{j-1} H_bar[i, l] beta[l, j], i <= j, as 64-row
+  // chunks x 4 l-slices, a wavefront each; the column l = j - 1 is this push's
+  const int sl = wave & 3, i = (wave >> 2) * 64 + lane;
   const int lo = i > 0 ? i - 1 : 0;
-  const int len = prod && j - 1 > lo ? j - 1 - lo : 0;
-  const int a0 = lo + (len * sl) / S, a1 = lo + (len * (sl + 1)) / S;
+  const int len = i < J ? j - lo : 0;
+  const int a0 = lo + (len * sl) / 4, a1 = lo + (len * (sl + 1)) / 4;
+  const int ah = a1 < j - 1 ? a1 : j - 1;  // columns held in memory
   constexpr int U = 8;
   double v[U];
 #pragma unroll
-  for (int u = 0; u < U; ++u) v[u] = a0 + u < a1 ? a.H[(size_t)(a0 + u) * a.ldH + i] : 0.0;
+  for (int u = 0; u < U; ++u) v[u] = a0 + u < ah ? a.H[(size_t)(a0 + u) * a.ldH + i] : 0.0;
   const double sgi = sl == 0 && i < j ? a.sigma[i] : 0.0;
-  double t = 0.0;
-  for (int g = tid; g < a.G; g += NT) t += a.partn[g];
+  static_assert(kStreamSlots <= 4 * 256, "slots of a pass");
+  double pn[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) pn[u] = tid < 256 && tid + 256 * u < a.G ? a.partn[tid + 256 * u] : 0.0;
   int bad = 0;
-  for (int c = tid; c < j; c += NT) {
-    const double hi = a.h[c];
-    bad |= !isfinite(hi);
-    s_h[c] = hi;
-    s_b[c] = a.bvec[c] + hi * bjj;  // beta completion
+  if (tid < 256) s_n[tid] = ((pn[0] + pn[1]) + pn[2]) + pn[3];
+  if (tid < j) {
+    const double hi = a.h[tid];
+    bad = !isfinite(hi);
+    s_h[tid] = hi;
+    s_b[tid] = a.bvec[tid] + hi * bjj;  // beta completion
   }
   if (status != ST_ACTIVE) {
     if (tid == 0) st->pushes += 1;
     return;
   }
-  t = lanes_sum<64>(t);
-  if (lane == 0) s_n[wave] = t;
   bad = __syncthreads_or(bad);
-  double wn2 = 0.0;
-#pragma unroll
-  for (int w = 0; w < NWV; ++w) wn2 += s_n[w];
+  // the tree of block_sum_256, in every wavefront
+  double wn2 = (s_n[lane] + s_n[lane + 128]) + (s_n[lane + 64] + s_n[lane + 192]);
+  wn2 = xor_sum<16>(xor_sum<32>(wn2));
+  wn2 += dpp_mov<0x128>(wn2);  // row_ror by 8, 4, 2, 1: the values repeat with that period
+  wn2 += dpp_mov<0x124>(wn2);
+  wn2 += dpp_mov<0x122>(wn2);
+  wn2 += dpp_mov<0x121>(wn2);
   const double hn = sqrt(wn2);
   if (bad || !isfinite(hn) || !isfinite(xn2)) {
     if (tid == 0) {
@@ -804,9 +841,9 @@ __device__ inline void finalize_next_body(const SmallArgs &a) {
     return;
   }
   const bool inv = hn * bjj <= tol * sqrt(xf);
-  for (int c = tid; c < j; c += NT) {
-    a.H[(size_t)(j - 1) * a.ldH + c] = s_h[c];
-    a.beta[(size_t)j * a.ldB + c] = s_b[c];
+  if (tid < j) {
+    a.H[(size_t)(j - 1) * a.ldH + tid] = s_h[tid];
+    a.beta[(size_t)j * a.ldB + tid] = s_b[tid];
   }
   if (tid == 0) {
     st->xfro2 = xf;
@@ -825,21 +862,21 @@ __device__ inline void finalize_next_body(const SmallArgs &a) {
   if (inv) return;
   double acc = 0.0;
 #pragma unroll
-  for (int u = 0; u < U; ++u) acc = fma(v[u], s_b[a0 + u < a1 ? a0 + u : 0], acc);
+  for (int u = 0; u < U; ++u)
+    if (a0 + u < ah) acc = fma(v[u], s_b[a0 + u], acc);
   int l = a0 + U;
-  for (; l + U <= a1; l += U) {
+  for (; l + U <= ah; l += U) {
 #pragma unroll
     for (int u = 0; u < U; ++u) v[u] = a.H[(size_t)(l + u) * a.ldH + i];
 #pragma unroll
     for (int u = 0; u < U; ++u) acc = fma(v[u], s_b[l + u], acc);
   }
-  for (; l < a1; ++l) acc = fma(a.H[(size_t)l * a.ldH + i], s_b[l], acc);
-  s_p[tid] = acc;
+  for (; l < ah; ++l) acc = fma(a.H[(size_t)l * a.ldH + i], s_b[l], acc);
+  if (a0 < a1 && a1 == j) acc = fma(i < j ? s_h[i] : hn, s_b[j - 1], acc);
+  s_p[wave][lane] = acc;
   __syncthreads();
-  if (sl == 0 && i <= j) {
-    double b = 0.0;
-    for (int k = 0; k < S; ++k) b += s_p[(k * R) * 64 + i];
-    b = fma(i < j ? s_h[i] : hn, s_b[j - 1], b);
+  if (sl == 0 && i < J) {
+    const double b = ((s_p[wave][lane] + s_p[wave + 1][lane]) + s_p[wave + 2][lane]) + s_p[wave + 3][lane];
     a.bvec[i] = b;
     a.coefA[i] = (i < j ? sgi : 1.0 / hn) * b;
   }

@@ -73,7 +73,7 @@ struct PassArgs {
   int ldg;              // leading dimension of part (>= gridDim.x)
   // passes B and C that reduce the preceding pass's column sums themselves
   // (small streams): rstride != 0: column sums as part[slot * rstride + c];
-  // rpart: the preceding pass's, rG rows (null in pass A); and where one
+  // rpart: the preceding pass's, rG rows (passes B and C); and where one
   // workgroup leaves the results
   const double *rpart;
   int rG, rstride;
@@ -86,7 +86,7 @@ struct PassArgs {
 
 // Widest basis (columns before the push) of the one-workgroup finalize that
 // also forms the next push's partial beta column.
-constexpr int kFinNextCols = 256;
+constexpr int kFinNextCols = 255;
 
 // Small-matrix pointers of one stream (FP64, column-major).
 struct SmallArgs {

@@ -31,15 +31,17 @@
 // (per-lane register sums in panel order, butterfly within a wavefront, fixed
 // per-block order); no floating-point atomics are used.
 
+#include <type_traits>
+
 #include "foa_device.h"
 
 
 namespace foa {
 
-template <typename TV, typename TX, int NW, int QW, int MODE, bool PREF>
+template <typename TV, typename TX, int NW, int QW, int MODE, bool PREF, bool RED>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(pass_waves<TV, QW>()))) void k_pass(PassArgs a) {
   __shared__ double lds[pass_lds_doubles<TV, NW, QW, MODE>()];
-  row_pass_body<TV, TX, NW, QW, MODE, PREF, false, MODE != PM_INIT, true>(a, blockIdx.x, a.P, gridDim.x, blockIdx.x, lds);
+  row_pass_body<TV, TX, NW, QW, MODE, PREF, false, RED, true>(a, blockIdx.x, a.P, gridDim.x, blockIdx.x, lds);
 }
 
 template <int MODE>
@@ -49,7 +51,7 @@ __global__ __launch_bounds__(256) void k_reduce(SmallArgs a) {
 
 __global__ __launch_bounds__(256) void k_finalize(SmallArgs a) { finalize_body(a); }
 __global__ __launch_bounds__(256) void k_finalize_init(SmallArgs a) { finalize_init_body(a); }
-__global__ __launch_bounds__(1024) void k_finalize_next(SmallArgs a) { finalize_next_body<1024>(a); }
+__global__ __launch_bounds__(1024) void k_finalize_next(SmallArgs a) { finalize_next_body(a); }
 __global__ __launch_bounds__(256) void k_nextb(SmallArgs a) { nextb_body(a, blockIdx.x); }
 
 __global__ __launch_bounds__(256) void k_init_state(SmallArgs a, double tol) { init_state_body(a, tol); }
@@ -101,29 +103,29 @@ int pass_qw(bool tv_f64, int nw, int j) {
   return pick_qw(j > 0 ? j : 1, tv_f64 ? 32 : nw * 4);
 }
 
-template <typename TV, typename TX, int NW, int MODE, bool PREF>
+template <typename TV, typename TX, int NW, int MODE, bool PREF, bool RED>
 static hipError_t launch_pass_q(int qw, int grid, const PassArgs &a, hipStream_t s) {
   constexpr int NT = NW * 64;
   switch (qw) {
-    case 1: hipLaunchKernelGGL((k_pass<TV, TX, NW, 1, MODE, PREF>), dim3(grid), dim3(NT), 0, s, a); break;
-    case 2: hipLaunchKernelGGL((k_pass<TV, TX, NW, 2, MODE, PREF>), dim3(grid), dim3(NT), 0, s, a); break;
-    case 4: hipLaunchKernelGGL((k_pass<TV, TX, NW, 4, MODE, PREF>), dim3(grid), dim3(NT), 0, s, a); break;
-    case 8: hipLaunchKernelGGL((k_pass<TV, TX, NW, 8, MODE, PREF>), dim3(grid), dim3(NT), 0, s, a); break;
+    case 1: hipLaunchKernelGGL((k_pass<TV, TX, NW, 1, MODE, PREF, RED>), dim3(grid), dim3(NT), 0, s, a); break;
+    case 2: hipLaunchKernelGGL((k_pass<TV, TX, NW, 2, MODE, PREF, RED>), dim3(grid), dim3(NT), 0, s, a); break;
+    case 4: hipLaunchKernelGGL((k_pass<TV, TX, NW, 4, MODE, PREF, RED>), dim3(grid), dim3(NT), 0, s, a); break;
+    case 8: hipLaunchKernelGGL((k_pass<TV, TX, NW, 8, MODE, PREF, RED>), dim3(grid), dim3(NT), 0, s, a); break;
     case 6:
       if constexpr (sizeof(TV) == 4 && NW >= 8) {
-        hipLaunchKernelGGL((k_pass<TV, TX, NW, 6, MODE, PREF>), dim3(grid), dim3(NT), 0, s, a);
+        hipLaunchKernelGGL((k_pass<TV, TX, NW, 6, MODE, PREF, RED>), dim3(grid), dim3(NT), 0, s, a);
         break;
       }
       return hipErrorInvalidValue;
     case 12:
       if constexpr (sizeof(TV) == 4 && NW == 8) {
-        hipLaunchKernelGGL((k_pass<TV, TX, NW, 12, MODE, PREF>), dim3(grid), dim3(NT), 0, s, a);
+        hipLaunchKernelGGL((k_pass<TV, TX, NW, 12, MODE, PREF, RED>), dim3(grid), dim3(NT), 0, s, a);
         break;
       }
       return hipErrorInvalidValue;
     default:
       if constexpr (NW * 16 * Vec<TV>::EPL <= 512)
-        hipLaunchKernelGGL((k_pass<TV, TX, NW, 16, MODE, PREF>), dim3(grid), dim3(NT), 0, s, a);
+        hipLaunchKernelGGL((k_pass<TV, TX, NW, 16, MODE, PREF, RED>), dim3(grid), dim3(NT), 0, s, a);
       else
         return hipErrorInvalidValue;
       break;
@@ -143,17 +145,19 @@ static hipError_t launch_pass_m(int mode, bool pref, int grid, const PassArgs &a
   const int qw = pass_qw(sizeof(TV) == 8, NW, a.j);
   if (qw * NW * Vec<TV>::EPL < a.j) return hipErrorInvalidValue;  // tile narrower than the basis
   pref = pref && prefetch_fits<TV, NW>(qw);
+  auto go = [&](auto m) -> hipError_t {
+    constexpr int M = decltype(m)::value;
+    if (a.rstride)
+      return pref ? launch_pass_q<TV, TX, NW, M, true, true>(qw, grid, a, s)
+                  : launch_pass_q<TV, TX, NW, M, false, true>(qw, grid, a, s);
+    return pref ? launch_pass_q<TV, TX, NW, M, true, false>(qw, grid, a, s)
+                : launch_pass_q<TV, TX, NW, M, false, false>(qw, grid, a, s);
+  };
   switch (mode) {
-    case PM_INIT: return launch_pass_q<TV, TX, NW, PM_INIT, false>(1, grid, a, s);
-    case PM_A:
-      return pref ? launch_pass_q<TV, TX, NW, PM_A, true>(qw, grid, a, s)
-                  : launch_pass_q<TV, TX, NW, PM_A, false>(qw, grid, a, s);
-    case PM_B:
-      return pref ? launch_pass_q<TV, TX, NW, PM_B, true>(qw, grid, a, s)
-                  : launch_pass_q<TV, TX, NW, PM_B, false>(qw, grid, a, s);
-    default:
-      return pref ? launch_pass_q<TV, TX, NW, PM_C, true>(qw, grid, a, s)
-                  : launch_pass_q<TV, TX, NW, PM_C, false>(qw, grid, a, s);
+    case PM_INIT: return launch_pass_q<TV, TX, NW, PM_INIT, false, false>(1, grid, a, s);
+    case PM_A: return go(std::integral_constant<int, PM_A>{});
+    case PM_B: return go(std::integral_constant<int, PM_B>{});
+    default: return go(std::integral_constant<int, PM_C>{});
   }
 }
 
@@ -193,8 +197,8 @@ hipError_t launch_pass(int mode, bool tv_f64, bool tx_f64, bool prefetch, int nw
 template <typename TV, typename TX, int NW, int QW>
 static int occ_q(bool pref) {
   int nb = 0;
-  const void *f = pref ? reinterpret_cast<const void *>(&k_pass<TV, TX, NW, QW, PM_A, true>)
-                       : reinterpret_cast<const void *>(&k_pass<TV, TX, NW, QW, PM_A, false>);
+  const void *f = pref ? reinterpret_cast<const void *>(&k_pass<TV, TX, NW, QW, PM_A, true, false>)
+                       : reinterpret_cast<const void *>(&k_pass<TV, TX, NW, QW, PM_A, false, false>);
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, f, NW * 64, 0) != hipSuccess) return 1;
   return nb > 0 ? nb : 1;
 }

@@ -309,7 +309,7 @@ def test_max_capacity(prec):
     ("f32", 1500, 300),          # 24 workgroups, 8 wavefronts beyond 128 columns, column chunks 1..5
     ("f64", 64 * 256, 66),       # 16 wavefronts: 256 workgroups up to 64 columns, kernels beyond
     ("f64", 64 * 257 - 5, 40),   # reduce kernels from the first push
-    ("f64", 1300, 260),          # one-workgroup finalize up to 256 columns, two kernels beyond
+    ("f64", 1300, 260),          # one-workgroup finalize up to 255 columns, two kernels beyond
 ])
 def test_small_stream_reductions(prec, n, N):
     """Streams on both sides of the line where passes B and C reduce the sums
