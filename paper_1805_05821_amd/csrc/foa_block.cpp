@@ -123,10 +123,7 @@ hipError_t enqueue_block(foa_ctx_s *c, const BlockLayout &L, char *bws, const vo
   if ((e = launch_bchol(2, q, s)) != hipSuccess) return e;                           // T_2
   q.tlev = 3;
   if ((e = launch_zgram(2, v64, x64, q.Gz, q, s)) != hipSuccess) return e;          // V <- Z T_0 T_1 T_2
-  if ((e = launch_bcommit(a, s)) != hipSuccess) return e;
-  SmallArgs sa = c->sa;
-  sa.j = j + BPK;  // nextb sizes its grid from j + 1 and reads the committed q itself
-  return launch_nextb(sa, s);
+  return launch_bcommit(a, s);
 }
 
 foa_status push_blocked_impl(foa_ctx_s *c, const void *d_X, int64_t ld, int32_t p, foa_dtype x_dtype,
@@ -226,6 +223,13 @@ foa_status push_blocked_impl(foa_ctx_s *c, const void *d_X, int64_t ld, int32_t 
     for (int b = 0; b < nblk && e == hipSuccess; ++b)
       e = enqueue_block(c, L, bws, X + (size_t)(k + b * BPK) * ld * es, ld, x64, q0 + b * BPK,
                         b + 1 < nblk ? X + (size_t)(k + (b + 1) * BPK) * ld * es : nullptr, b > 0);
+    if (e == hipSuccess) {
+      // only a sequential push reads the next partial beta column: once per run,
+      // for whatever the run committed (the kernel reads q itself)
+      SmallArgs sa = c->sa;
+      sa.j = q0 + nblk * BPK;
+      e = launch_nextb(sa, c->stream);
+    }
     if (e != hipSuccess) return hip_err(c, e, "blocked push");
     c->mirror_valid = false;
     c->dmd.valid = false;

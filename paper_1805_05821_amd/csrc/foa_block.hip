@@ -151,7 +151,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(QW >= 1
 
   const int cbase = wave * 4 + cl;
   const unsigned goff0 = (unsigned)(cbase * PANEL * sizeof(TV)) + (unsigned)(lane >> 2) * 16u;
-  constexpr unsigned GBYTES = (unsigned)(GSTRIDE * PANEL * sizeof(TV));
+  constexpr unsigned GBYTES = (unsigned)(GSTRIDE * PANEL * sizeof(TV));  // group to group, in a scalar register
   const unsigned tile_bytes = (unsigned)(j * PANEL * sizeof(TV));
   const bool uact = lane < UL;
   const int pos = wave * UL + (lane & (UL - 1));
@@ -179,7 +179,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(QW >= 1
     return make_rsrc(Wb + (size_t)(v / UPP) * pbytes + half, u < pend ? tile_bytes - half : 0u);
   };
   auto load_group = [&](const __amdgpu_buffer_rsrc_t &r, int g, TV (&dst)[EPL]) {
-    unpack16<TV>(__builtin_amdgcn_raw_buffer_load_b128(r, (int)(goff0 + g * GBYTES), 0, kTileLoad), dst);
+    unpack16<TV>(__builtin_amdgcn_raw_buffer_load_b128(r, (int)goff0, (int)(g * GBYTES), kTileLoad), dst);
   };
   // snapshot rows of a unit: snapshot k's row r at byte (k * ldx + r) * sizeof(TX)
   const unsigned xoff0 = (unsigned)((uk * a.ldx + urow) * sizeof(TX));
@@ -221,7 +221,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(QW >= 1
         for (int k = 0; k < BPK; ++k) u[e][k] = 0.0;
       // the coefficients of group g + CD are read while group g's products run
       // (left to itself the compiler reads them next to their use)
-      constexpr int CD = QW <= 12 ? 2 : (sizeof(TV) == 4 && QW == 16 && NW == 8 && NEXT_Y ? 0 : 1);  // 0: no register left
+      constexpr int CD = QW <= 12 ? 2 : 1;
       double cf[CD + 1][BPK];
       auto read_cf = [&](int g) {
 #pragma unroll
@@ -363,11 +363,30 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(QW >= 1
 // workgroup.
 // ---------------------------------------------------------------------------
 constexpr int GSLOT = BPK * BPK;
+constexpr int GTRI = BPK * (BPK + 1) / 2;
+constexpr int kBhRows = 576;  // rows of a column of H_bar products (j + BPK <= 512, in whole chunks)
+
+// Sums of v[0 .. N) over a workgroup of 256 threads into sh[0 .. N) (wavefront
+// sums, then over the wavefronts in order); sh: 5 N doubles.
+template <int N>
+__device__ __forceinline__ void wg_sums(const double (&v)[N], double *sh) {
+#pragma unroll
+  for (int n = 0; n < N; ++n) {
+    const double t = lanes_sum<64>(v[n]);
+    if ((threadIdx.x & 63) == 0) sh[N + (threadIdx.x >> 6) * N + n] = t;
+  }
+  __syncthreads();
+  if (threadIdx.x < N) {
+    const double *w = sh + N + threadIdx.x;
+    sh[threadIdx.x] = ((w[0] + w[N]) + w[2 * N]) + w[3 * N];
+  }
+  __syncthreads();
+}
 
 template <typename TV, typename TX, int MODE>
 __global__ __launch_bounds__(256) void k_zgram(BlockArgs a) {
   if (a.st->status != ST_ACTIVE || *a.flag || (a.gate && !*a.gate)) return;
-  __shared__ double sh[256];
+  __shared__ double sh[5 * (BPK + BPK * BPK)];
   __shared__ double sT[3 * BPK * BPK];
   const int tid = threadIdx.x;
   const int tlev = a.tlev;
@@ -375,80 +394,62 @@ __global__ __launch_bounds__(256) void k_zgram(BlockArgs a) {
     if (tid < tlev * BPK * BPK) sT[tid] = a.sm[SM_T + tid];
     __syncthreads();
   }
-  double g[BPK][BPK];
-#pragma unroll
-  for (int k = 0; k < BPK; ++k)
-#pragma unroll
-    for (int l = 0; l < BPK; ++l) g[k][l] = 0.0;
   // Z's order: units of BROWS rows (see k_bpass), row chunk * EPL + e of a
   // unit at e * 16 + chunk
   constexpr int EPL = Vec<TV>::EPL, BROWS = 16 * EPL;
   const int64_t npad = a.P * PANEL;
-  if constexpr (MODE == ZG_YNQ) {
-    // ||y_k||^2 and h[c][k] = q_c^T y_k for the previous block's new columns
-    // q_c = V(:, j - BPK + c): one row per grid stride
+  const int64_t stride = (int64_t)gridDim.x * 256;
+  if constexpr (MODE == ZG_YNORM || MODE == ZG_YNQ) {
+    // ||y_k||^2 and (ZG_YNQ) h[c][k] = q_c^T y_k for the previous block's new
+    // columns q_c = V(:, j - BPK + c), R rows in flight per thread (each sum takes
+    // its rows in order)
+    constexpr bool Q = MODE == ZG_YNQ;
+    constexpr int R = Q ? 2 : 4;
     const TX *x = static_cast<const TX *>(a.x);
     const TV *W = static_cast<const TV *>(a.W);
-    double h[BPK][BPK];
+    double s[Q ? BPK + BPK * BPK : BPK];
 #pragma unroll
-    for (int c = 0; c < BPK; ++c)
+    for (int k = 0; k < (Q ? BPK + BPK * BPK : BPK); ++k) s[k] = 0.0;
+    auto rows = [&](int64_t r, auto nr) {
+      constexpr int N = decltype(nr)::value;
+      double y[N][BPK], q[N][BPK];
 #pragma unroll
-      for (int k = 0; k < BPK; ++k) h[c][k] = 0.0;
-    for (int64_t r = (int64_t)blockIdx.x * 256 + tid; r < a.n; r += (int64_t)gridDim.x * 256) {
-      const TV *qr = W + ((r / PANEL) * a.n_max + (a.j - BPK)) * PANEL + r % PANEL;
-      double y[BPK], q[BPK];
+      for (int u = 0; u < N; ++u) {
+        const int64_t ru = r + u * stride;
 #pragma unroll
-      for (int k = 0; k < BPK; ++k) y[k] = (double)x[(int64_t)k * a.ldx + r];
+        for (int k = 0; k < BPK; ++k) y[u][k] = (double)x[(int64_t)k * a.ldx + ru];
+        if constexpr (Q) {
+          const TV *qr = W + ((ru / PANEL) * a.n_max + (a.j - BPK)) * PANEL + ru % PANEL;
 #pragma unroll
-      for (int c = 0; c < BPK; ++c) q[c] = (double)qr[c * PANEL];
-#pragma unroll
-      for (int k = 0; k < BPK; ++k) g[k][k] = fma(y[k], y[k], g[k][k]);
-#pragma unroll
-      for (int c = 0; c < BPK; ++c)
-#pragma unroll
-        for (int k = 0; k < BPK; ++k) h[c][k] = fma(q[c], y[k], h[c][k]);
-    }
-#pragma unroll
-    for (int c = 0; c < BPK; ++c)
-#pragma unroll
-      for (int k = 0; k < BPK; ++k) {
-        const double v = block_sum_256(h[c][k], sh);
-        if (tid == 0) a.partq[(size_t)blockIdx.x * GSLOT + c * BPK + k] = v;
+          for (int c = 0; c < BPK; ++c) q[u][c] = (double)qr[c * PANEL];
+        }
       }
-  }
-  if constexpr (MODE == ZG_YNORM) {
-    // the snapshots' rows, four grid strides in flight per thread (each sum
-    // still takes its rows in the order of the plain loop below)
-    const int64_t stride = (int64_t)gridDim.x * 256;
-    const TX *x = static_cast<const TX *>(a.x);
+#pragma unroll
+      for (int u = 0; u < N; ++u) {
+#pragma unroll
+        for (int k = 0; k < BPK; ++k) s[k] = fma(y[u][k], y[u][k], s[k]);
+        if constexpr (Q) {
+#pragma unroll
+          for (int c = 0; c < BPK; ++c)
+#pragma unroll
+            for (int k = 0; k < BPK; ++k) s[BPK + c * BPK + k] = fma(q[u][c], y[u][k], s[BPK + c * BPK + k]);
+        }
+      }
+    };
     int64_t r = (int64_t)blockIdx.x * 256 + tid;
-    for (; r + 3 * stride < a.n; r += 4 * stride) {
-      double v[4][BPK];
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int k = 0; k < BPK; ++k) v[u][k] = (double)x[(int64_t)k * a.ldx + r + u * stride];
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int k = 0; k < BPK; ++k) g[k][k] = fma(v[u][k], v[u][k], g[k][k]);
-    }
-    for (; r < a.n; r += stride) {
-#pragma unroll
-      for (int k = 0; k < BPK; ++k) {
-        const double v = (double)x[(int64_t)k * a.ldx + r];
-        g[k][k] = fma(v, v, g[k][k]);
-      }
-    }
+    for (; r + (R - 1) * stride < a.n; r += R * stride) rows(r, std::integral_constant<int, R>{});
+    for (; r < a.n; r += stride) rows(r, std::integral_constant<int, 1>{});
+    wg_sums(s, sh);
+    if (tid < BPK) a.partg[(size_t)blockIdx.x * GSLOT + tid * BPK + tid] = sh[tid];
+    if (Q && tid < GSLOT) a.partq[(size_t)blockIdx.x * GSLOT + tid] = sh[BPK + tid];
+    return;
   }
-  // the other passes take one row per grid stride (four in flight, as for
-  // the snapshots above, measured 6-12% slower here)
-  constexpr bool NORMS = MODE == ZG_YNORM || MODE == ZG_YNQ;
-  for (int64_t r = (int64_t)blockIdx.x * 256 + tid; !NORMS && r < npad; r += (int64_t)gridDim.x * 256) {
-    double z[BPK];
+  double g[GTRI];  // upper triangle by rows
 #pragma unroll
-    for (int k = 0; k < BPK; ++k) z[k] = a.Z[r * BPK + k];
-    for (int t = 0; t < tlev; ++t) {  // z <- z T_t
+  for (int k = 0; k < GTRI; ++k) g[k] = 0.0;
+  // z <- z T_0 .. T_{tlev-1}
+  auto transform = [&](double (&z)[BPK]) {
+    for (int t = 0; t < tlev; ++t) {
       const double *T = sT + t * BPK * BPK;
       double o[BPK];
 #pragma unroll
@@ -461,28 +462,41 @@ __global__ __launch_bounds__(256) void k_zgram(BlockArgs a) {
 #pragma unroll
       for (int l = 0; l < BPK; ++l) z[l] = o[l];
     }
-    if (MODE == ZG_WRITEV) {
-      const int rr = (int)(r % PANEL), ru = rr % BROWS;
-      TV *vc = static_cast<TV *>(a.W) + (size_t)(r / PANEL) * a.n_max * PANEL + (size_t)a.j * PANEL + (rr - ru) +
-               (ru % 16) * EPL + ru / 16;
+  };
+  for (int64_t r = (int64_t)blockIdx.x * 256 + tid; r < npad; r += 2 * stride) {
+    // two rows in flight (the second past the end reads the first again)
+    double z[2][BPK];
+    const bool two = r + stride < npad;
 #pragma unroll
-      for (int k = 0; k < BPK; ++k) vc[k * PANEL] = (TV)z[k];
-      continue;
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int k = 0; k < BPK; ++k) z[u][k] = a.Z[(r + (u && two ? stride : 0)) * BPK + k];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      transform(z[u]);
+      if (u && !two) break;
+      if (MODE == ZG_WRITEV) {
+        const int64_t ru = r + u * stride;
+        const int rr = (int)(ru % PANEL), ri = rr % BROWS;
+        TV *vc = static_cast<TV *>(a.W) + (size_t)(ru / PANEL) * a.n_max * PANEL + (size_t)a.j * PANEL + (rr - ri) +
+                 (ri % 16) * EPL + ri / 16;
+#pragma unroll
+        for (int k = 0; k < BPK; ++k) vc[k * PANEL] = (TV)z[u][k];
+        continue;
+      }
+      int m = 0;
+#pragma unroll
+      for (int k = 0; k < BPK; ++k)
+#pragma unroll
+        for (int l = k; l < BPK; ++l, ++m) g[m] = fma(z[u][k], z[u][l], g[m]);
     }
-#pragma unroll
-    for (int k = 0; k < BPK; ++k)
-#pragma unroll
-      for (int l = 0; l < BPK; ++l) g[k][l] = fma(z[k], z[l], g[k][l]);
   }
   if (MODE == ZG_WRITEV) return;
-#pragma unroll
-  for (int k = 0; k < BPK; ++k)
-#pragma unroll
-    for (int l = 0; l < BPK; ++l) {
-      if (NORMS && k != l) continue;
-      const double s = block_sum_256(g[k][l], sh);
-      if (tid == 0) a.partg[(size_t)blockIdx.x * GSLOT + k * BPK + l] = s;
-    }
+  wg_sums(g, sh);
+  if (tid < GSLOT) {
+    const int k = min(tid / BPK, tid % BPK), l = max(tid / BPK, tid % BPK);
+    a.partg[(size_t)blockIdx.x * GSLOT + tid] = sh[k * BPK - k * (k - 1) / 2 + l - k];
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -495,6 +509,19 @@ __global__ __launch_bounds__(256) void k_zgram(BlockArgs a) {
 // that block), of the previous block's 4 from the ZG_YNQ partials.  MODE 4
 // (after BP_ZR): the raw sums D into dnext, for the next block.
 // ---------------------------------------------------------------------------
+// sum of p[g * GSLOT], g < G, by one wavefront, eight loads in flight per lane
+__device__ __forceinline__ double slot_sum(const double *p, int G, int lane) {
+  double t = 0.0;
+  for (int g = lane; g < G; g += 64 * 8) {
+    double v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = g + 64 * u < G ? p[(size_t)(g + 64 * u) * GSLOT] : 0.0;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) t += v[u];
+  }
+  return lanes_sum<64>(t);
+}
+
 template <int MODE>
 __global__ __launch_bounds__(256) void k_breduce(BlockArgs a) {
   if (a.st->status != ST_ACTIVE || *a.flag || (a.gate && !*a.gate)) return;
@@ -508,14 +535,9 @@ __global__ __launch_bounds__(256) void k_breduce(BlockArgs a) {
       t = a.dnext[wv];
     } else if (MODE == 1 && a.qy) {
       const int e = (c - (a.j - BPK)) * BPK + k;
-      for (int g = lane; g < a.Gz; g += 64) t += a.partq[(size_t)g * GSLOT + e];
-#pragma unroll
-      for (int m = 1; m < 64; m <<= 1) t += xor_shfl(t, m);
+      t = slot_sum(a.partq + e, a.Gz, lane);
     } else {
-      const double *pc = a.partb + (size_t)wv * a.ldg;
-      for (int g = lane; g < a.G; g += 64) t += pc[g];
-#pragma unroll
-      for (int m = 1; m < 64; m <<= 1) t += xor_shfl(t, m);
+      t = strided_sum<false>(a.partb + (size_t)wv * a.ldg, a.G, lane);
     }
     if (MODE == 4) {
       if (lane == 0) a.dnext[wv] = t;
@@ -534,10 +556,7 @@ __global__ __launch_bounds__(256) void k_breduce(BlockArgs a) {
     }
   } else if (MODE == 1 && wv < npairs + BPK) {
     const int k = wv - npairs;
-    double t = 0.0;
-    for (int g = lane; g < a.Gz; g += 64) t += a.partg[(size_t)g * GSLOT + k * BPK + k];
-#pragma unroll
-    for (int m = 1; m < 64; m <<= 1) t += xor_shfl(t, m);
+    const double t = slot_sum(a.partg + k * BPK + k, a.Gz, lane);
     if (lane == 0) a.sm[SM_YN2 + k] = t;
   }
 }
@@ -545,33 +564,30 @@ __global__ __launch_bounds__(256) void k_breduce(BlockArgs a) {
 // ---------------------------------------------------------------------------
 // The Gram partials of the workgroups of a block pass, reduced in a fixed
 // order into sG[0 .. GSLOT): thread t sums entry t % GSLOT over the slots
-// t / GSLOT, + 16, + 32, ... (eight interleaved sums, so eight loads are in
-// flight, then added in order); the 16 partial sums of an entry are then
-// added in slot order.  One workgroup of 256 threads; sG is complete on
-// return.
+// t / GSLOT, + 64, ... (at most 1024 / 64 = 16, all in flight); the four
+// slot lanes of a wavefront are then added by lane swaps, the wavefronts in
+// order.  One workgroup of kGramThreads threads; sG is complete on return.
+// (256 threads, eight loads at a time: 6 of k_bchol's 12 us.)
 // ---------------------------------------------------------------------------
-static_assert(GSLOT == 16, "256 threads as 16 entries x 16 slot lanes");
+constexpr int kGramThreads = 1024;
+static_assert(GSLOT == 16, "four slot lanes of 16 entries per wavefront");
 __device__ inline void gram_reduce(const BlockArgs &a, int tid, double *sh, double *sG) {
-  constexpr int SL = 256 / GSLOT;  // slot lanes per entry
+  constexpr int SL = kGramThreads / GSLOT;  // slot lanes per entry
   const int e = tid % GSLOT, s0 = tid / GSLOT;
-  double t8[8];
+  double v[16];
 #pragma unroll
-  for (int m = 0; m < 8; ++m) t8[m] = 0.0;
-  int g = s0;
-  for (; g + 7 * SL < a.Gg; g += 8 * SL) {
-#pragma unroll
-    for (int m = 0; m < 8; ++m) t8[m] += a.partg[(size_t)(g + m * SL) * GSLOT + e];
-  }
+  for (int m = 0; m < 16; ++m) v[m] = s0 + m * SL < a.Gg ? a.partg[(size_t)(s0 + m * SL) * GSLOT + e] : 0.0;
   double t = 0.0;
 #pragma unroll
-  for (int m = 0; m < 8; ++m) t += t8[m];
-  for (; g < a.Gg; g += SL) t += a.partg[(size_t)g * GSLOT + e];
-  sh[tid] = t;
+  for (int m = 0; m < 16; ++m) t += v[m];
+  t = xor_sum<32>(xor_sum<16>(t));
+  if ((tid & 63) < GSLOT) sh[(tid >> 6) * GSLOT + e] = t;
   __syncthreads();
   if (tid < GSLOT) {
-    double v = 0.0;
-    for (int j = 0; j < 256 / GSLOT; ++j) v += sh[j * GSLOT + tid];
-    sG[tid] = v;
+    double r = 0.0;
+#pragma unroll
+    for (int w = 0; w < kGramThreads / 64; ++w) r += sh[w * GSLOT + tid];
+    sG[tid] = r;
   }
   __syncthreads();
 }
@@ -583,7 +599,7 @@ __device__ inline void gram_reduce(const BlockArgs &a, int tid, double *sh, doub
 // rejects the block.  One workgroup; the 4 x 4 algebra runs in thread 0.
 // ---------------------------------------------------------------------------
 template <int ROUND>
-__global__ __launch_bounds__(256) void k_bchol(BlockArgs a) {
+__global__ __launch_bounds__(kGramThreads) void k_bchol(BlockArgs a) {
   if (a.st->status != ST_ACTIVE || *a.flag) return;
   __shared__ double sh[256];
   __shared__ double sG[GSLOT];
@@ -656,11 +672,61 @@ __global__ __launch_bounds__(256) void k_bchol(BlockArgs a) {
 // Commit of an accepted block (one workgroup): breakdown test on the new
 // diagonal of beta, then beta's columns j .. j+BPK-1, sigma and the scalar
 // state.  On rejection nothing is written except the flag.  H_bar follows in
-// k_bcommit_h.
+// k_bcommit_h; workgroups 1, 2, ... form the products it starts from (they need
+// nothing of the commit).
 // ---------------------------------------------------------------------------
+// Sums over the old columns l < j-1 of H_bar[i, l] beta[l, j-1+k], k < BPK (beta's
+// new columns from the small area): 64 rows x 4 slices of the l range of one of
+// bh_slices(j) workgroups per row chunk, into partb[(slice * BPK + k) * 512 + i].
+// One workgroup per row chunk read all of H_bar through 8 CUs: 32 us at 250
+// columns.
+__host__ __device__ constexpr int bh_slices(int j) { return j < 128 ? 1 : (j < 512 ? j / 64 : 8); }
+__device__ inline void bcommit_products(const BlockArgs &a, int wg) {
+  __shared__ double sh[4][64][BPK];
+  const int j = a.j;
+  const int S = bh_slices(j), chunk = wg / S, sl = (wg - chunk * S) * 4 + (threadIdx.x >> 6);
+  const int r = threadIdx.x & 63, i = chunk * 64 + r;  // 0-based row, below j - 1 + BPK
+  double t[BPK];
+#pragma unroll
+  for (int k = 0; k < BPK; ++k) t[k] = 0.0;
+  const int lo = i > 0 ? i - 1 : 0, hi = j - 1, len = hi > lo ? hi - lo : 0;
+  const int a0 = lo + (len * sl) / (4 * S), a1 = lo + (len * (sl + 1)) / (4 * S);
+  const double *bj = a.beta + (size_t)(j - 1) * a.ldB;
+  int l = a0;
+  for (; l + 4 <= a1; l += 4) {
+    double h[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) h[u] = a.H[(size_t)(l + u) * a.ldH + i];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      t[0] = fma(h[u], bj[l + u], t[0]);
+#pragma unroll
+      for (int k = 1; k < BPK; ++k) t[k] = fma(h[u], a.sm[SM_R + (l + u) * BPK + k - 1], t[k]);
+    }
+  }
+  for (; l < a1; ++l) {
+    const double h = a.H[(size_t)l * a.ldH + i];
+    t[0] = fma(h, bj[l], t[0]);
+#pragma unroll
+    for (int k = 1; k < BPK; ++k) t[k] = fma(h, a.sm[SM_R + l * BPK + k - 1], t[k]);
+  }
+#pragma unroll
+  for (int k = 0; k < BPK; ++k) sh[threadIdx.x >> 6][r][k] = t[k];
+  __syncthreads();
+  if (threadIdx.x < 64) {
+#pragma unroll
+    for (int k = 0; k < BPK; ++k)
+      a.partb[(size_t)((wg - chunk * S) * BPK + k) * kBhRows + i] = ((sh[0][r][k] + sh[1][r][k]) + sh[2][r][k]) + sh[3][r][k];
+  }
+}
+
 __global__ __launch_bounds__(256) void k_bcommit(BlockArgs a) {
   DevState *st = a.st;
   if (st->status != ST_ACTIVE || *a.flag) return;
+  if (blockIdx.x > 0) {
+    bcommit_products(a, (int)blockIdx.x - 1);
+    return;
+  }
   __shared__ int s_ok;
   const int tid = threadIdx.x;
   const int j = a.j;
@@ -705,45 +771,29 @@ __global__ __launch_bounds__(256) void k_bcommit(BlockArgs a) {
 // ---------------------------------------------------------------------------
 // H_bar's new columns c = j-1 .. j+BPK-2 (0-based) of an accepted block, from
 // H_bar_{:,c} beta_{c,c} = beta_{:,c+1} - H_bar_{:,0:c-1} beta_{0:c-1,c}.  The
-// part of the sum over the old columns (l < j-1) is the same kind of product
-// for all BPK new columns, so it is formed first, for every row at once (64
-// rows x 4 l-slices per workgroup, slices combined in order); then each row
-// runs the BPK-step recurrence over the new columns by itself.
+// part of the sum over the old columns comes from k_bcommit's other workgroups
+// (slices added in order); each row then runs the BPK-step recurrence over the
+// new columns by itself.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_bcommit_h(BlockArgs a) {
+__global__ __launch_bounds__(64) void k_bcommit_h(BlockArgs a) {
   DevState *st = a.st;
-  if (*a.flag || st->q != a.j + BPK) return;  // rejected, or nothing committed
-  __shared__ double sh[4][64][BPK];
   const int j = a.j;
-  const int r = threadIdx.x & 63;
-  const int sl = threadIdx.x >> 6;
-  const int i = blockIdx.x * 64 + r;  // 0-based row
-  const int rows = j + BPK;           // rows 0 .. j+BPK-1 carry the new columns
+  const int i = blockIdx.x * 64 + threadIdx.x;  // 0-based row
+  const int rows = j + BPK;                     // rows 0 .. j+BPK-1 carry the new columns
+  const int S = bh_slices(j);
   double t[BPK];
 #pragma unroll
-  for (int k = 0; k < BPK; ++k) t[k] = 0.0;
-  if (i < rows) {
-    const int lo = i > 0 ? i - 1 : 0;
-    const int hi = j - 1;  // old columns l < j-1
-    const int len = hi > lo ? hi - lo : 0;
-    const int a0 = lo + (len * sl) / 4;
-    const int a1 = lo + (len * (sl + 1)) / 4;
-    for (int l = a0; l < a1; ++l) {
-      const double h = a.H[(size_t)l * a.ldH + i];
-#pragma unroll
-      for (int k = 0; k < BPK; ++k) t[k] = fma(h, a.beta[(size_t)(j - 1 + k) * a.ldB + l], t[k]);
-    }
+  for (int k = 0; k < BPK; ++k) {
+    t[k] = 0.0;
+    for (int q = 0; q < S; ++q) t[k] += a.partb[(size_t)(q * BPK + k) * kBhRows + i];
   }
-#pragma unroll
-  for (int k = 0; k < BPK; ++k) sh[sl][r][k] = t[k];
-  __syncthreads();
-  if (sl != 0 || i >= rows) return;
+  if (*a.flag || st->q != j + BPK || i >= rows) return;  // rejected, or nothing committed
   double hn[BPK];
 #pragma unroll
   for (int k = 0; k < BPK; ++k) {
     const int c = j - 1 + k;
     double v = a.beta[(size_t)(c + 1) * a.ldB + i];
-    v -= ((sh[0][r][k] + sh[1][r][k]) + sh[2][r][k]) + sh[3][r][k];
+    v -= t[k];
     for (int kk = 0; kk < k; ++kk) v -= hn[kk] * a.beta[(size_t)c * a.ldB + (j - 1 + kk)];
     hn[k] = (i <= c + 1) ? v / a.beta[(size_t)c * a.ldB + c] : 0.0;
     a.H[(size_t)c * a.ldH + i] = hn[k];
@@ -762,37 +812,42 @@ __global__ void k_bflag_clear(int *flag) {
 // (||R2||_F / ||R1||_F) ||R2_k|| > unit ||Z_k|| / 10 for some k, else 0
 // (also for a rejected block).  One workgroup.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_bthird(BlockArgs a, int *gate, double unit) {
-  __shared__ double sh[256];
+__global__ __launch_bounds__(kGramThreads) void k_bthird(BlockArgs a, int *gate, double unit) {
+  __shared__ double sh[kGramThreads / 64 * GSLOT];
   __shared__ double sG[GSLOT];
-  __shared__ double s_z2[BPK], s_r2[BPK];
+  __shared__ double s_w[kGramThreads / 64][BPK + 1];
   const int tid = threadIdx.x;
   if (a.st->status != ST_ACTIVE || *a.flag) {
     if (tid == 0) *gate = 0;
     return;
   }
+  // thread t: right-hand side t % BPK of the columns t / BPK, + 256, ...
   const int npairs = a.j * BPK;
-  double r1 = 0.0;
-  double r2k[BPK];
-#pragma unroll
-  for (int k = 0; k < BPK; ++k) r2k[k] = 0.0;
-  for (int e = tid; e < npairs; e += 256) {
+  double r1 = 0.0, r2 = 0.0;
+  for (int e = tid; e < npairs; e += kGramThreads) {
     const double v2 = a.sm[SM_R2 + e];
     const double v1 = a.sm[SM_R + e] - v2;
     r1 = fma(v1, v1, r1);
-#pragma unroll
-    for (int k = 0; k < BPK; ++k)
-      if (e % BPK == k) r2k[k] = fma(v2, v2, r2k[k]);
+    r2 = fma(v2, v2, r2);
   }
-  const double r1s = block_sum_256(r1, sh);
+  r1 = lanes_sum<64>(r1);
+  r2 = r2 + dpp_mov<0x128>(r2);  // over the lanes of equal t % BPK
+  r2 = r2 + dpp_mov<0x124>(r2);
+  r2 = xor_sum<32>(xor_sum<16>(r2));
+  if ((tid & 63) < BPK) s_w[tid >> 6][tid & 63] = r2;
+  if ((tid & 63) == BPK) s_w[tid >> 6][BPK] = r1;
+  gram_reduce(a, tid, sh, sG);
+  double s_r2[BPK], s_z2[BPK], r1s = 0.0;
 #pragma unroll
   for (int k = 0; k < BPK; ++k) {
-    const double v = block_sum_256(r2k[k], sh);
-    if (tid == 0) s_r2[k] = v;
+    s_r2[k] = 0.0;
+    s_z2[k] = sG[k * BPK + k];
   }
-  gram_reduce(a, tid, sh, sG);
-  if (tid < BPK) s_z2[tid] = sG[tid * BPK + tid];
-  __syncthreads();
+  for (int w = 0; w < kGramThreads / 64; ++w) {
+#pragma unroll
+    for (int k = 0; k < BPK; ++k) s_r2[k] += s_w[w][k];
+    r1s += s_w[w][BPK];
+  }
   if (tid != 0) return;
   int third = 0;
   if (r1s > 0.0) {
@@ -906,17 +961,19 @@ hipError_t launch_breduce(int mode, const BlockArgs &a, hipStream_t s) {
 
 hipError_t launch_bchol(int round, const BlockArgs &a, hipStream_t s) {
   if (round == 0)
-    hipLaunchKernelGGL(k_bchol<0>, dim3(1), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(k_bchol<0>, dim3(1), dim3(kGramThreads), 0, s, a);
   else if (round == 1)
-    hipLaunchKernelGGL(k_bchol<1>, dim3(1), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(k_bchol<1>, dim3(1), dim3(kGramThreads), 0, s, a);
   else
-    hipLaunchKernelGGL(k_bchol<2>, dim3(1), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(k_bchol<2>, dim3(1), dim3(kGramThreads), 0, s, a);
   return hipGetLastError();
 }
 
 hipError_t launch_bcommit(const BlockArgs &a, hipStream_t s) {
-  hipLaunchKernelGGL(k_bcommit, dim3(1), dim3(256), 0, s, a);
-  hipLaunchKernelGGL(k_bcommit_h, dim3((a.j + BPK + 63) / 64), dim3(256), 0, s, a);
+  const int chunks = (a.j + BPK + 63) / 64;
+  if (chunks * 64 > kBhRows) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_bcommit, dim3(1 + chunks * bh_slices(a.j)), dim3(256), 0, s, a);
+  hipLaunchKernelGGL(k_bcommit_h, dim3(chunks), dim3(64), 0, s, a);
   return hipGetLastError();
 }
 
@@ -926,7 +983,7 @@ hipError_t launch_bflag_clear(int *flag, hipStream_t s) {
 }
 
 hipError_t launch_bthird(const BlockArgs &a, int *gate, double unit, hipStream_t s) {
-  hipLaunchKernelGGL(k_bthird, dim3(1), dim3(256), 0, s, a, gate, unit);
+  hipLaunchKernelGGL(k_bthird, dim3(1), dim3(kGramThreads), 0, s, a, gate, unit);
   return hipGetLastError();
 }
 
