@@ -82,7 +82,7 @@ struct foa_ctx_s {
   // dependent or non-finite snapshot, which the next synchronising call reads)
   int form = 0;
   int ls_hu = 0, ls_hx = 0;
-  int ls_occ[2][2][3][7] = {};  // resident sweep workgroups per CU [v64][x64][nw][tile_slot]
+  int ls_occ[2][2][3][17] = {};  // resident sweep workgroups per CU [v64][x64][nw][groups]
   int ls_nw_opt = 0;            // option "ls_nw": 0 automatic, 16 = 16-wavefront sweeps above 128 columns
   // row-pass timing (foa_profile)
   bool profile = false;

@@ -251,6 +251,8 @@ struct LsSmall {
   int nt;                // host's expectation of q (upper bound of the device's)
   int flush;
   int gram;              // 1: FP32 basis, the second projection uses (I - E) w
+  double *hp;            // single stream: the two products in hs slices, [(kind * hs + slice) * (n_max + 1)]
+  int hs;                // (batched form: null, the products in bvec and what)
 };
 
 // ---- launchers (defined in foa_kernels.hip) --------------------------------

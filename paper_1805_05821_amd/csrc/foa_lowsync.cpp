@@ -51,6 +51,10 @@ LsSmall ls_small(foa_ctx_s *c, int G, bool flush) {
   a.G = G;
   a.nt = c->q_host;
   a.flush = flush ? 1 : 0;
+  // the products' slices go to the first partial-sum area, which the reduction
+  // has read by then: 2 * 8 * (n_max + 1) values of its n_max * 1024
+  a.hp = c->part;
+  a.hs = std::min(8, std::max(1, a.nt / 64));
   return a;
 }
 
@@ -62,9 +66,8 @@ int ls_grid(foa_ctx_s *c, int q, bool x64) {
   if (g <= 0) {
     const bool v64 = c->prec == FOA_PREC_F64;
     const int nw = ls_nw(v64, q, c->ls_nw_opt), qw = ls_qw(v64, q, c->ls_nw_opt);
-    const int qi = tile_slot(qw);
     const int ni = nw == 4 ? 0 : (nw == 8 ? 1 : 2);
-    int &occ = c->ls_occ[v64 ? 1 : 0][x64 ? 1 : 0][ni][qi];
+    int &occ = c->ls_occ[v64 ? 1 : 0][x64 ? 1 : 0][ni][qw];
     if (occ <= 0) occ = ls_occupancy(v64, x64, q, c->ls_nw_opt);
     g = std::max(c->grid_auto, occ * c->cus);
   }

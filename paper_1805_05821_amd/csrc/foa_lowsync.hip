@@ -29,76 +29,68 @@
 // the rounded values the next sweep will read.
 //
 // Kernels (all on the context stream):
-//   k_ls_pass     : the sweep (panel walk, tile layout and prefetch of the
-//                   three-sweep row pass; two coefficient vectors in phase 1,
-//                   two right-hand sides in phase 2, six scalar sums);
+//   k_ls_pass     : the sweep (tile layout of the blocked passes; two coefficient
+//                   vectors in phase 1, two or three right-hand sides in phase 2,
+//                   six scalar sums);
 //   k_ls_reduce   : fixed-order reduction of the workgroup partials;
 //   k_ls_finalize : one workgroup: the finished column's norm, scale and
 //                   breakdown test, H_bar's column from beta, beta's column of
 //                   the new pending column, the next sweep's coefficients.
 #include "foa_device.h"
-#include "foa_tile.h"
 
 namespace foa {
 
 // ---------------------------------------------------------------------------
-// Sweep body.  One workgroup walks panels blockIdx.x, + gridDim.x, ...
-// Tile: the q final columns of a panel (lane layout of row_pass_body).  The
-// pending columns and the snapshot are read per update row.
+// Sweep body.  One workgroup walks units pstart, + pstep, ... < pend (in panels)
+// of one stream and writes its partial sums to slot `slot`.  Called uniformly by
+// the whole workgroup (it synchronises).
+//
+// Unit and tile are those of the blocked passes (foa_block.hip): BROWS rows of a
+// panel (64 with an FP32 basis, 32 with an FP64 one), lane l of a wavefront holding
+// the 16-byte chunk l / 4 of column l % 4 of each of its QW groups of four of the
+// q final columns.  Phase 1 sums the tile's rows against sigma o w and sigma o z
+// (FMA per lane, DPP over the quad, LDS over the wavefronts); the update rows,
+// contiguous per wavefront, read the pending column, the snapshot copy and the
+// new snapshot; phase 2 forms the column sums on v_mfma_f64_4x4x4, whose four
+// right-hand sides take the formed column, the snapshot and, with an FP32 basis,
+// the rounding error of the finished column (the Gram correction of the second
+// projection; an FP64 basis needs none).  That is one accumulator per group where
+// vector FMAs took two FP64 and one FP32 and left the 16-group tile room to
+// prefetch half; a tile's registers are refilled for the unit after next as
+// phase 2 is done with them, the next unit's row inputs ahead of them.  The three
+// columns go out 64 rows at a time.
+// Bound: HBM, with three column writes per panel in the read stream.
 // ---------------------------------------------------------------------------
-#ifndef LS_PF16
-#define LS_PF16 8
-#endif
-#ifndef LS_PF8
-#define LS_PF8 4
-#endif
-
 template <typename TV, int NW, int QW>
 constexpr int ls_lds_doubles() {
-  constexpr int JCAP = QW * NW * Vec<TV>::EPL;
-  return 2 * JCAP + 2 * 2 * NW * PANEL + 3 * PANEL + NW * LS_NSC;
+  constexpr int BROWS = 16 * Vec<TV>::EPL;
+  return 2 * QW * NW * 4 + 2 * NW * BROWS * 2 + BROWS * 4 + 3 * BROWS + NW * LS_NSC +
+         (QW >= 16 ? LS_NSC * BROWS : 0);
 }
 
-// Groups of the next panel's tile loaded ahead (the prefetch): all of them,
-// except for the FP32 16-group tile, where the Gram sums leave room for 8 (a
-// full prefetch spills).  The other groups load at the start of their panel.
-template <typename TV, int NW, int QW>
-constexpr int ls_pf() {
-  return sizeof(TV) == 4 && QW == 16 ? LS_PF16 : (sizeof(TV) == 4 && QW == 8 && NW < 8 ? LS_PF8 : QW);
-}
-
-// One workgroup processes panels pstart, pstart + pstep, ... < pend of one
-// stream and writes its partial sums to slot `slot`.  Called uniformly by the
-// whole workgroup (it synchronises).
-template <typename TV, typename TX, int NW, int QW, int PF>
-__device__ __forceinline__ void ls_pass_body(const LsArgs &a, int64_t pstart, int64_t pend, int64_t pstep,
+template <typename TV, typename TX, int NW, int QW>
+__device__ __forceinline__ void ls_pass_body(const LsArgs &a, int64_t pstart, int64_t pend_, int64_t pstep_,
                                              int slot, double *lds) {
 #pragma clang fp contract(off)
   constexpr int EPL = Vec<TV>::EPL;
-  constexpr int LPC = 64 / EPL;
-  constexpr int CPW = EPL;
-  constexpr int JCAP = QW * NW * CPW;
-  constexpr int RPW = PANEL / NW;
-  constexpr int GSTRIDE = NW * CPW;
-
-  double (*s_coef)[JCAP] = reinterpret_cast<double (*)[JCAP]>(lds);
-  double (*s_red)[2][NW][PANEL] = reinterpret_cast<double (*)[2][NW][PANEL]>(lds + 2 * JCAP);
-  double *s_u = lds + 2 * JCAP + 4 * NW * PANEL;
-  double *s_x = s_u + PANEL;
-  float *s_d = reinterpret_cast<float *>(s_x + PANEL);  // rounding error of the finished column
-  double (*s_sc)[LS_NSC] = reinterpret_cast<double (*)[LS_NSC]>(s_x + 2 * PANEL);
-  // FP32 basis: the finished column's inner products with the final columns
-  // (the Gram correction of the second projection) need the sums of its
-  // rounding error against the tile; FP32 accumulation of those tiny values
-  // suffices for a correction.  An FP64 basis needs none.
+  constexpr int BROWS = 16 * EPL;
+  constexpr int UPP = PANEL / BROWS;  // units per panel
+  constexpr int JCAP = QW * NW * 4;
+  constexpr int RPW = BROWS / NW;     // update rows of a wavefront
+  constexpr int GSTRIDE = NW * 4;
   constexpr bool GRAM = sizeof(TV) == 4;
+
+  double *s_coef = lds;                               // [column][w, z]
+  double *s_red = s_coef + 2 * JCAP;                  // [parity][wavefront][row][w, z]
+  double *s_w = s_red + 2 * NW * BROWS * 2;           // [row][right-hand side]
+  TV *s_col = reinterpret_cast<TV *>(s_w + BROWS * 4);  // [finished, formed, copied][row of the unit]
+  double (*s_sc)[LS_NSC] = reinterpret_cast<double (*)[LS_NSC]>(s_w + BROWS * 4 + 3 * BROWS);
 
   const DevState *st = a.st;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int cs = lane / LPC;
-  const int rg = lane % LPC;
+  const int cl = lane & 3;
 
   // step state (uniform)
   const int q = uniform(st->q);
@@ -111,203 +103,205 @@ __device__ __forceinline__ void ls_pass_body(const LsArgs &a, int64_t pstart, in
   const double cq = hu && hf ? uniform(st->ls_cq) : 0.0;
 
   __syncthreads();  // the previous call of this workgroup may still read LDS
-  for (int k = 0; k < 2; ++k)
-    for (int c = tid; c < JCAP; c += NW * 64) s_coef[k][c] = (c < q) ? (k ? a.coefZ[c] : a.coefW[c]) : 0.0;
+  for (int c = tid; c < JCAP; c += NW * 64) {
+    s_coef[2 * c] = c < q ? a.coefW[c] : 0.0;
+    s_coef[2 * c + 1] = c < q ? a.coefZ[c] : 0.0;
+  }
   __syncthreads();
 
-  const int cbase = wave * CPW + cs;
-  const unsigned goff0 = (unsigned)((wave * CPW * PANEL + lane * EPL) * sizeof(TV));
-  constexpr unsigned GBYTES = (unsigned)(GSTRIDE * PANEL * sizeof(TV));
+  const int cbase = wave * 4 + cl;
+  const unsigned goff0 = (unsigned)(cbase * PANEL * sizeof(TV)) + (unsigned)(lane >> 2) * 16u;
+  constexpr unsigned GBYTES = (unsigned)(GSTRIDE * PANEL * sizeof(TV));  // group to group, in a scalar register
   const unsigned tile_bytes = (unsigned)(q * PANEL * sizeof(TV));
   const bool uact = lane < RPW;
-  const int urow = wave * RPW + (lane % RPW);
+  const int urow = wave * RPW + (lane & (RPW - 1));
+  const int upos = (urow % EPL) * 16 + urow / EPL;  // its place in the tile's row order
   const unsigned pan_bytes = (unsigned)((size_t)a.n_max * PANEL * sizeof(TV));
-  // per-row offsets of the pending columns inside a panel (kOOR: absent)
-  const unsigned ocu = (uact && hu) ? (unsigned)((cc * PANEL + urow) * sizeof(TV)) : kOOR;
-  const unsigned ocf = (uact && hf) ? (unsigned)((cf * PANEL + urow) * sizeof(TV)) : kOOR;
-  const unsigned ocn = (uact && hn) ? (unsigned)((cn * PANEL + urow) * sizeof(TV)) : kOOR;
+  // byte offsets of the pending columns inside a panel (kOOR: absent)
+  const unsigned ocu = hu ? (unsigned)(cc * PANEL * sizeof(TV)) : kOOR;
+  const unsigned ocf = hf ? (unsigned)(cf * PANEL * sizeof(TV)) : kOOR;
+  const unsigned ocn = hn ? (unsigned)(cn * PANEL * sizeof(TV)) : kOOR;
+  const unsigned urb = (unsigned)(urow * sizeof(TV));
 
-  double acc0[QW], acc1[QW];
-  float acc2[GRAM ? QW : 1];
+  double acc[QW];
 #pragma unroll
-  for (int g = 0; g < QW; ++g) acc0[g] = acc1[g] = 0.0;
-#pragma unroll
-  for (int g = 0; g < (GRAM ? QW : 1); ++g) acc2[g] = 0.f;
+  for (int g = 0; g < QW; ++g) acc[g] = 0.0;
+  // the scalar sums of an update row; the widest tile leaves no registers for
+  // them and keeps them in LDS (each read and written by its own lane only)
+  constexpr bool SCL = QW >= 16;
+  double *s_acc = s_w + BROWS * 4 + 3 * BROWS + NW * LS_NSC;
   double sc[LS_NSC];
 #pragma unroll
   for (int k = 0; k < LS_NSC; ++k) sc[k] = 0.0;
+  if (SCL && uact)
+    for (int k = 0; k < LS_NSC; ++k) s_acc[k * BROWS + urow] = 0.0;
 
   char *Wb = static_cast<char *>(a.W);
   const size_t pbytes = (size_t)a.n_max * PANEL * sizeof(TV);
-  TV t[QW][EPL];
-  TV tn[PF > 0 ? PF : 1][EPL];
+  TV ta[QW][EPL], tb[QW][EPL];
 
-  int64_t p = pstart;
-  if (PF > 0 && p < pend) {
-    load_tile_groups<TV, 0, PF, 0>(make_rsrc(Wb + (size_t)p * pbytes, tile_bytes), goff0, GBYTES, t);
-#pragma unroll
-    for (int g = 0; g < PF; ++g) {
-#pragma unroll
-      for (int e = 0; e < EPL; ++e) asm volatile("" : "+v"(t[g][e]));
-    }
-  }
+  // units (32-bit and scalar, see the blocked passes): u = unit * UPP + half
+  const int pend = (int)pend_ * UPP, pstep = (int)pstep_;
+  const int nfull = (int)(a.n / BROWS), nrem = (int)(a.n % BROWS);
+  // walk of the workgroup: panels pstart, + pstep, ..., both halves of each
+  auto unit_of = [&](int i) { return UPP == 1 ? (int)pstart + i * pstep : ((int)pstart + (i >> 1) * pstep) * 2 + (i & 1); };
+  auto rsrc_of = [&](int u, unsigned bytes) {
+    const int v = u < pend ? u : 0;
+    const unsigned half = UPP > 1 ? (unsigned)(v % UPP) * (unsigned)(BROWS * sizeof(TV)) : 0u;
+    return make_rsrc(Wb + (size_t)(v / UPP) * pbytes + half, u < pend && bytes > half ? bytes - half : 0u);
+  };
+  auto load_group = [&](const __amdgpu_buffer_rsrc_t &r, int g, TV (&dst)[EPL]) {
+    unpack16<TV>(__builtin_amdgcn_raw_buffer_load_b128(r, (int)goff0, (int)(g * GBYTES), kTileLoad), dst);
+  };
+  TV yu, yf;
+  TX xr;
+  auto load_rows = [&](int u) {
+    const __amdgpu_buffer_rsrc_t rp = rsrc_of(u, pan_bytes);
+    yu = buf_load_raw<TV>(rp, uact && hu ? ocu + urb : kOOR);
+    yf = buf_load_raw<TV>(rp, uact && hf ? ocf + urb : kOOR);
+    const int v = u < pend ? u : 0;
+    const int valid = u >= pend || !hn ? 0 : (u < nfull ? BROWS : (u == nfull ? nrem : 0));
+    xr = buf_load_raw<TX>(make_rsrc(static_cast<const TX *>(a.x) + (hn ? (size_t)v * BROWS : 0),
+                                    (unsigned)(BROWS * sizeof(TX))),
+                          uact && urow < valid ? (unsigned)(urow * sizeof(TX)) : kOOR);
+  };
+
   int par = 0;
-  for (; p < pend; p += pstep) {
-    // per-row inputs: pending column, snapshot copy, new snapshot (loaded at
-    // the start of their own panel: prefetching them with the tile was slower)
-    const __amdgpu_buffer_rsrc_t rp = make_rsrc(Wb + (size_t)p * pbytes, pan_bytes);
-    const double yu = buf_load_scalar<TV>(rp, ocu);
-    const double yf = buf_load_scalar<TV>(rp, ocf);
-    double xv;
-    {
-      const int64_t rem = a.n - p * PANEL;
-      const unsigned xb = hn ? (unsigned)((rem >= PANEL ? PANEL : (rem > 0 ? rem : 0)) * sizeof(TX)) : 0u;
-      const __amdgpu_buffer_rsrc_t rx = make_rsrc(static_cast<const TX *>(a.x) + (hn ? p * PANEL : 0), xb);
-      xv = buf_load_scalar<TX>(rx, uact ? (unsigned)(urow * sizeof(TX)) : kOOR);
-    }
-    if constexpr (PF < QW) {
-      // the groups not prefetched, straight into their place
-      load_tile_groups<TV, PF, QW, PF>(make_rsrc(Wb + (size_t)p * pbytes, tile_bytes), goff0, GBYTES, t);
-    }
-    if constexpr (PF > 0) {
-      const bool more = p + pstep < pend;
-      load_tile_groups<TV, 0, PF, 0>(make_rsrc(Wb + (size_t)(more ? p + pstep : p) * pbytes, more ? tile_bytes : 0u),
-                                   goff0, GBYTES, tn);
-    }
-
-    // phase 1: row sums of the tile against sigma o w and sigma o z
-    double u[2][EPL];
+  auto step = [&](int u, int u1, int u2, TV (&t)[QW][EPL]) {
+    const __amdgpu_buffer_rsrc_t rt = rsrc_of(u2, tile_bytes);
+    // phase 1
+    double s[2][EPL];
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {
+    for (int e = 0; e < EPL; ++e) s[0][e] = s[1][e] = 0.0;
+    // coefficients of group g + CD are read while group g's products run
+    constexpr int CD = QW >= 14 ? 0 : (QW >= 8 ? 1 : 2);
+    double cw[CD + 1][2];
+    auto read_cf = [&](int g) {
 #pragma unroll
-      for (int e = 0; e < EPL; ++e) u[k][e] = 0.0;
-    }
+      for (int k = 0; k < 2; ++k) cw[g % (CD + 1)][k] = s_coef[2 * (cbase + g * GSTRIDE) + k];
+    };
+#pragma unroll
+    for (int g = 0; g < (CD < QW ? CD : QW); ++g) read_cf(g);
 #pragma unroll
     for (int g = 0; g < QW; ++g) {
+      if (g + CD < QW) read_cf(g + CD);
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int k = 0; k < 2; ++k) {
-        const double cf_ = s_coef[k][cbase + g * GSTRIDE];
+      for (int k = 0; k < 2; ++k)
 #pragma unroll
-        for (int e = 0; e < EPL; ++e) u[k][e] = fma((double)t[g][e], cf_, u[k][e]);
-      }
+        for (int e = 0; e < EPL; ++e) s[k][e] = fma((double)t[g][e], cw[g % (CD + 1)][k], s[k][e]);
+      __builtin_amdgcn_sched_barrier(0);
     }
+    double *red = s_red + par * NW * BROWS * 2;
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {
-      if constexpr (LPC <= 16) {
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) u[k][e] = xor_sum<16>(u[k][e]);
-      }
-#pragma unroll
-      for (int e = 0; e < EPL; ++e) u[k][e] = xor_sum<32>(u[k][e]);
-    }
-    if (cs == 0) {
-#pragma unroll
-      for (int k = 0; k < 2; ++k) {
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) s_red[par][k][wave][rg * EPL + e] = u[k][e];
-      }
+    for (int e = 0; e < EPL; ++e) {
+      const bool b0 = cl & 1;  // lanes 0, 2 of a quad end with the sum against w, 1, 3 against z
+      double r = (b0 ? s[1][e] : s[0][e]) + dpp_mov<0xB1>(b0 ? s[0][e] : s[1][e]);
+      r += dpp_mov<0x4E>(r);
+      if (cl < 2) red[wave * BROWS * 2 + (e * 16 + (lane >> 2)) * 2 + cl] = r;
     }
     __syncthreads();
     double sw = 0.0, sz = 0.0;
 #pragma unroll
     for (int w2 = 0; w2 < NW; ++w2) {
-      sw += s_red[par][0][w2][urow];
-      sz += s_red[par][1][w2][urow];
+      sw += red[w2 * BROWS * 2 + upos * 2];
+      sz += red[w2 * BROWS * 2 + upos * 2 + 1];
     }
     // row update: finished column, formed column, snapshot copy (each rounded
     // to the storage type; the sums below use the rounded values)
-    const TV ut_s = (TV)(yu - sw);
+    const double yud = (double)yu, xv = (double)xr;
+    const TV ut_s = (TV)(yud - sw);
     const double ut = (double)ut_s;
-    const TV uf_s = (TV)((yf - sz) - ut * cq);
+    const TV uf_s = (TV)(((double)yf - sz) - ut * cq);
     const double uf = (double)uf_s;
     const TV xs_s = (TV)xv;
     const double xs = (double)xs_s;
-    buf_store_scalar<TV>(ut_s, rp, ocu);
-    buf_store_scalar<TV>(uf_s, rp, ocf);
-    buf_store_scalar<TV>(xs_s, rp, ocn);
     if (uact) {
-      sc[LS_UU] = fma(ut, ut, sc[LS_UU]);
-      sc[LS_UF] = fma(ut, uf, sc[LS_UF]);
-      sc[LS_UX] = fma(ut, xs, sc[LS_UX]);
-      sc[LS_FF] = fma(uf, uf, sc[LS_FF]);
-      sc[LS_FX] = fma(uf, xs, sc[LS_FX]);
-      sc[LS_XX] = fma(xv, xv, sc[LS_XX]);
-      s_u[urow] = uf;
-      s_x[urow] = xs;
-      if constexpr (GRAM) s_d[urow] = (float)(ut - (yu - sw));
+      auto add = [&](int k, double p, double q2) {
+        if constexpr (SCL)
+          s_acc[k * BROWS + urow] = fma(p, q2, s_acc[k * BROWS + urow]);
+        else
+          sc[k] = fma(p, q2, sc[k]);
+      };
+      add(LS_UU, ut, ut);
+      add(LS_UF, ut, uf);
+      add(LS_UX, ut, xs);
+      add(LS_FF, uf, uf);
+      add(LS_FX, uf, xs);
+      add(LS_XX, xv, xv);
+      s_w[upos * 4] = uf;
+      s_w[upos * 4 + 1] = xs;
+      s_w[upos * 4 + 2] = GRAM ? ut - (yud - sw) : 0.0;
+      s_w[upos * 4 + 3] = 0.0;
+      s_col[urow] = ut_s;
+      s_col[BROWS + urow] = uf_s;
+      s_col[2 * BROWS + urow] = xs_s;
     }
     __syncthreads();
-    // phase 2: column sums of the tile against the formed column and the snapshot
-    double wu[EPL], wx[EPL];
-    float wd[EPL];
+    // a column per wavefront (or in turn), 64 or 32 rows to a store
+    const __amdgpu_buffer_rsrc_t rp = rsrc_of(u, pan_bytes);
 #pragma unroll
-    for (int e = 0; e < EPL; ++e) {
-      wu[e] = s_u[rg * EPL + e];
-      wx[e] = s_x[rg * EPL + e];
-      wd[e] = GRAM ? s_d[rg * EPL + e] : 0.f;
+    for (int c = wave; c < 3; c += NW) {
+      const unsigned off = c == 0 ? ocu : (c == 1 ? ocf : ocn);
+      buf_store_scalar<TV>(s_col[c * BROWS + (lane & (BROWS - 1))], rp,
+                           off != kOOR && lane < BROWS ? off + (unsigned)(lane * sizeof(TV)) : kOOR);
     }
+    load_rows(u1);
+    // phase 2
     if constexpr (sizeof(TV) == 4) {
-#pragma unroll
-      for (int g = 0; g < QW; ++g) {
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) asm volatile("" : "+v"(t[g][e]));
-      }
-    }
-#pragma unroll
-    for (int g = 0; g < QW; ++g) {
-#pragma unroll
-      for (int e = 0; e < EPL; ++e) {
-        const double tv = (double)t[g][e];
-        acc0[g] = fma(tv, wu[e], acc0[g]);
-        acc1[g] = fma(tv, wx[e], acc1[g]);
-      }
-    }
-    if constexpr (GRAM) {
 #pragma unroll
       for (int g = 0; g < QW; ++g)
 #pragma unroll
-        for (int e = 0; e < EPL; ++e) acc2[g] = fmaf((float)t[g][e], wd[e], acc2[g]);
+        for (int e = 0; e < EPL; ++e) asm volatile("" : "+v"(t[g][e]));
     }
-    if constexpr (PF > 0) {
+    double we[EPL];
 #pragma unroll
-      for (int g = 0; g < PF; ++g) {
+    for (int e = 0; e < EPL; ++e) we[e] = s_w[e * 64 + lane];
 #pragma unroll
-        for (int e = 0; e < EPL; ++e) asm volatile("" : "+v"(tn[g][e]));
-      }
+    for (int g4 = 0; g4 < QW; g4 += 4) {
 #pragma unroll
-      for (int g = 0; g < PF; ++g) {
+      for (int e = 0; e < EPL; ++e)
 #pragma unroll
-        for (int e = 0; e < EPL; ++e) t[g][e] = tn[g][e];
-      }
+        for (int g = g4; g < (g4 + 4 < QW ? g4 + 4 : QW); ++g)
+          acc[g] = __builtin_amdgcn_mfma_f64_4x4x4f64((double)t[g][e], we[e], acc[g], 0, 0, 0);
+#pragma unroll
+      for (int g = g4; g < (g4 + 4 < QW ? g4 + 4 : QW); ++g) load_group(rt, g, t[g]);
+      __builtin_amdgcn_sched_barrier(0);
     }
     par ^= 1;
-  }
+  };
 
+  // number of units of this workgroup's walk
+  const int np = (int)((pend_ - pstart + pstep_ - 1) / pstep_);
+  const int nu = pstart < pend_ ? np * UPP : 0;
+  load_rows(unit_of(0));
+  {
+    const __amdgpu_buffer_rsrc_t r0 = rsrc_of(unit_of(0), tile_bytes), r1 = rsrc_of(unit_of(1), tile_bytes);
+#pragma unroll
+    for (int g = 0; g < QW; ++g) load_group(r0, g, ta[g]);
+#pragma unroll
+    for (int g = 0; g < QW; ++g) load_group(r1, g, tb[g]);
+  }
+  int i = 0;
+  for (; i + 1 < nu; i += 2) {
+    step(unit_of(i), unit_of(i + 1), unit_of(i + 2), ta);
+    step(unit_of(i + 1), unit_of(i + 2), unit_of(i + 3), tb);
+  }
+  if (i < nu) step(unit_of(i), unit_of(i + 1), unit_of(i + 2), ta);
+
+  // accumulators: lane = rhs + 4 * block + 16 * column
 #pragma unroll
   for (int g = 0; g < QW; ++g) {
-    double v0 = acc0[g], v1 = acc1[g];
-#pragma unroll
-    for (int m = 1; m < LPC; m <<= 1) {
-      v0 += xor_shfl(v0, m);
-      v1 += xor_shfl(v1, m);
-    }
-    const int c = cbase + g * GSTRIDE;
-    if (rg == 0 && c < q) {
-      a.part0[(size_t)c * a.ldg + slot] = v0;
-      a.part1[(size_t)c * a.ldg + slot] = v1;
-    }
-    if constexpr (GRAM) {
-      float v2 = acc2[g];
-#pragma unroll
-      for (int m = 1; m < LPC; m <<= 1) v2 += __shfl_xor(v2, m);
-      if (rg == 0 && c < q) a.part2[(size_t)c * a.ldg + slot] = (double)v2;
-    }
+    const int c = wave * 4 + g * GSTRIDE + (lane >> 4);
+    double v = acc[g] + dpp_mov<0x128>(acc[g]);
+    v += dpp_mov<0x124>(v);
+    if ((lane & 12) == 0 && c < q && cl < (GRAM ? 3 : 2))
+      (cl == 0 ? a.part0 : (cl == 1 ? a.part1 : a.part2))[(size_t)c * a.ldg + slot] = v;
   }
 #pragma unroll
   for (int k = 0; k < LS_NSC; ++k) {
-    double v = sc[k];
-#pragma unroll
-    for (int m = 1; m < 64; m <<= 1) v += xor_shfl(v, m);
+    if (SCL && uact) sc[k] = s_acc[k * BROWS + urow];
+    const double v = lanes_sum<64>(sc[k]);
     if (lane == 0) s_sc[wave][k] = v;
   }
   __syncthreads();
@@ -325,16 +319,10 @@ __device__ __forceinline__ bool ls_runs(const DevState *st, int flush) {
   return s == ST_ACTIVE || (flush && s == ST_NONFINITE);
 }
 
-// Register budget as waves per SIMD: tiles of up to 4 groups fit 128 VGPRs,
-// 6 and 8 groups 168, 12 and 16 groups 256 (two right-hand sides of FP64
-// accumulators, the FP32 basis's Gram sums, the current and the prefetched
-// tile; the FP32 16-group tile prefetches half of its groups).
+// Register budget as waves per SIMD: two tiles and the accumulators, no spills
 template <typename TV, int NW, int QW>
 constexpr int ls_waves() {
-  // an 8-wavefront workgroup keeps one workgroup per CU at 2 or 3 waves per
-  // SIMD, so 8-wavefront tiles of 8 groups take the larger budget (no spill of
-  // the FP32 basis's Gram sums)
-  return (NW == 16 || QW <= 4) ? 4 : ((QW <= 8 && NW < 8) || QW == 6 ? 3 : 2);
+  return NW == 16 || QW <= 4 ? 4 : (QW <= 8 ? 3 : 2);
 }
 
 template <typename TV, typename TX, int NW, int QW>
@@ -343,7 +331,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ls_wave
   if (!ls_runs(a.st, a.flush)) return;
   if (a.flush && !a.st->ls_u && !a.st->ls_x) return;
   __shared__ double lds[ls_lds_doubles<TV, NW, QW>()];
-  ls_pass_body<TV, TX, NW, QW, ls_pf<TV, NW, QW>()>(a, blockIdx.x, a.P, gridDim.x, blockIdx.x, lds);
+  ls_pass_body<TV, TX, NW, QW>(a, blockIdx.x, a.P, gridDim.x, blockIdx.x, lds);
 }
 
 // ---------------------------------------------------------------------------
@@ -376,10 +364,7 @@ __device__ inline void ls_reduce_body(const LsSmall &a, int vblock) {
   } else {
     return;
   }
-  double t = 0.0;
-  for (int g = lane; g < a.G; g += 64) t += src[g];
-#pragma unroll
-  for (int m = 1; m < 64; m <<= 1) t += xor_shfl(t, m);
+  const double t = strided_sum<false>(src, a.G, lane);
   if (lane == 0) a.red[out] = t;
 }
 
@@ -392,84 +377,87 @@ __global__ __launch_bounds__(256) void k_ls_reduce(LsSmall a) {
 // ---------------------------------------------------------------------------
 // Finalize (one workgroup of 512 threads, q <= 511 after the push).
 // ---------------------------------------------------------------------------
-template <int NT>
-__device__ inline double ls_block_sum(double v, double *sh) {
-  sh[threadIdx.x] = v;
-  __syncthreads();
-  for (int s = NT / 2; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) sh[threadIdx.x] = sh[threadIdx.x] + sh[threadIdx.x + s];
-    __syncthreads();
+// Sums of v[0 .. N) over the workgroup (wavefront sums, then over the wavefronts
+// in order), in every thread; sh: N * NT / 64 doubles.
+template <int NT, int N>
+__device__ inline void ls_block_sums(double (&v)[N], double *sh) {
+#pragma unroll
+  for (int n = 0; n < N; ++n) {
+    v[n] = lanes_sum<64>(v[n]);
+    if ((threadIdx.x & 63) == 0) sh[n * (NT / 64) + (threadIdx.x >> 6)] = v[n];
   }
-  const double r = sh[0];
   __syncthreads();
-  return r;
+#pragma unroll
+  for (int n = 0; n < N; ++n) {
+    v[n] = 0.0;
+#pragma unroll
+    for (int w = 0; w < NT / 64; ++w) v[n] += sh[n * (NT / 64) + w];
+  }
+  __syncthreads();
 }
 
-// The part of H_bar's column c-1 that the earlier columns give, for the
-// column c = q that the coming finalize finishes (eq. betacolumnupdate):
-// b_i = sum_{l = max(0, i-1)}^{c-2} H_bar[i, l] beta[l, c-1], i < c.  64 rows
-// x 4 contiguous l-slices per 256 threads, slices summed in order.
-__device__ inline void ls_hprod_body(const LsSmall &a, int rblock) {
+// Two products for the coming finalize, both 64 rows x 4 contiguous l-slices per
+// 256 threads of slice `part` of `parts` of the l range, slices summed in order,
+// one value per row to out[i] (i < c):
+//  * KIND 0: the part of H_bar's column c-1 that the earlier columns give, for the
+//    column c = q that the finalize finishes (eq. betacolumnupdate),
+//    sum_{l = max(0, i-1)}^{c-2} H_bar[i, l] beta[l, c-1];
+//  * KIND 1 (FP32 basis): E w over the earlier final columns for the column that
+//    the finalize makes pending (w_l = sigma_l * its reduced sum l, l < q), E
+//    symmetric with a zero diagonal; the terms of the column finished in the same
+//    sweep are added by the finalize.
+template <int KIND>
+__device__ inline void ls_product_body(const LsSmall &a, int rblock, int part, int parts, double *out) {
   __shared__ double sh[4][64];
-  const DevState *st = a.st;
-  const int c = st->q;
-  const int r = threadIdx.x & 63, sl = threadIdx.x >> 6;
+  const int c = a.st->q;
+  const int r = threadIdx.x & 63, sl = part * 4 + (threadIdx.x >> 6), S = 4 * parts;
   const int i = rblock * 64 + r;
   double t = 0.0;
   if (i < c) {
-    const int lo = i > 0 ? i - 1 : 0, len = c - 1 > lo ? c - 1 - lo : 0;
-    const int a0 = lo + (len * sl) / 4, a1 = lo + (len * (sl + 1)) / 4;
-    const double *bprev = a.beta + (size_t)(c - 1) * a.ldB;
+    const int lo = KIND == 0 && i > 0 ? i - 1 : 0, hi = KIND == 0 ? c - 1 : c, len = hi > lo ? hi - lo : 0;
+    const int a0 = lo + (len * sl) / S, a1 = lo + (len * (sl + 1)) / S;
+    const double *m = (KIND == 0 ? a.H : a.E) + i;
+    const size_t ld = KIND == 0 ? (size_t)a.ldH : (size_t)a.n_max;
+    const double *bprev = a.beta + (size_t)(c > 0 ? c - 1 : 0) * a.ldB;
+    auto x = [&](int l) { return KIND == 0 ? bprev[l] : a.red[l] * a.sigma[l]; };
     // four independent chains, so the loads of several columns are in flight
     double t4[4] = {0.0, 0.0, 0.0, 0.0};
     int l = a0;
     for (; l + 4 <= a1; l += 4) {
 #pragma unroll
-      for (int k = 0; k < 4; ++k) t4[k] = fma(a.H[(size_t)(l + k) * a.ldH + i], bprev[l + k], t4[k]);
+      for (int k = 0; k < 4; ++k) t4[k] = fma(m[(size_t)(l + k) * ld], x(l + k), t4[k]);
     }
-    for (; l < a1; ++l) t4[0] = fma(a.H[(size_t)l * a.ldH + i], bprev[l], t4[0]);
+    for (; l < a1; ++l) t4[0] = fma(m[(size_t)l * ld], x(l), t4[0]);
     t = (t4[0] + t4[1]) + (t4[2] + t4[3]);
   }
-  sh[sl][r] = t;
+  sh[threadIdx.x >> 6][r] = t;
   __syncthreads();
-  if (sl == 0 && i < c) a.bvec[i] = ((sh[0][r] + sh[1][r]) + sh[2][r]) + sh[3][r];
+  if (threadIdx.x < 64 && i < c) out[i] = ((sh[0][r] + sh[1][r]) + sh[2][r]) + sh[3][r];
 }
 
-// FP32 basis: E w over the earlier final columns for the column that the
-// coming finalize makes pending (w_l = sigma_l * its reduced sum l, l < q):
-// the same 64 rows x 4 slices, E symmetric with a zero diagonal.  The terms of
-// the column finished in the same sweep are added by the finalize.
-__device__ inline void ls_ew_body(const LsSmall &a, int rblock) {
-  __shared__ double sh[4][64];
-  const DevState *st = a.st;
-  const int c = st->q;
-  const int r = threadIdx.x & 63, sl = threadIdx.x >> 6;
-  const int i = rblock * 64 + r;
-  double t = 0.0;
-  if (i < c) {
-    const int a0 = (c * sl) / 4, a1 = (c * (sl + 1)) / 4;
-    const double *Ei = a.E + i;  // row i (= column i)
-    double t4[4] = {0.0, 0.0, 0.0, 0.0};
-    int l = a0;
-    for (; l + 4 <= a1; l += 4) {
-#pragma unroll
-      for (int k = 0; k < 4; ++k) t4[k] = fma(Ei[(size_t)(l + k) * a.n_max], a.red[l + k] * a.sigma[l + k], t4[k]);
-    }
-    for (; l < a1; ++l) t4[0] = fma(Ei[(size_t)l * a.n_max], a.red[l] * a.sigma[l], t4[0]);
-    t = (t4[0] + t4[1]) + (t4[2] + t4[3]);
-  }
-  sh[sl][r] = t;
-  __syncthreads();
-  if (sl == 0 && i < c) a.what[i] = ((sh[0][r] + sh[1][r]) + sh[2][r]) + sh[3][r];
-}
-
+// One stream: the l range of either product is cut into a.hs workgroups as well
+// (grid: row chunks x slices x the two products) and the finalize adds the slices:
+// a workgroup per 64 rows read H_bar and E through 8 CUs, 15.2 us at 250 columns.
 __global__ __launch_bounds__(256) void k_ls_hprod(LsSmall a) {
   if (!ls_runs(a.st, a.flush)) return;
-  if (a.st->ls_u) ls_hprod_body(a, blockIdx.x);
-  if (a.gram && a.st->ls_x) {
-    __syncthreads();
-    ls_ew_body(a, blockIdx.x);
+  double *out = a.hp + (size_t)(blockIdx.z * a.hs + blockIdx.y) * (a.n_max + 1);
+  if (blockIdx.z == 0) {
+    if (a.st->ls_u) ls_product_body<0>(a, blockIdx.x, blockIdx.y, a.hs, out);
+  } else if (a.st->ls_x) {
+    ls_product_body<1>(a, blockIdx.x, blockIdx.y, a.hs, out);
   }
+}
+
+// Row i of a product as the finalize reads it: the slices' sum, or (batched form)
+// the whole product in p.
+__device__ __forceinline__ double ls_product(const LsSmall &a, int kind, const double *p, int i) {
+  if (!a.hp) return p[i];
+  double v[8], t = 0.0;
+#pragma unroll
+  for (int s = 0; s < 8; ++s) v[s] = s < a.hs ? a.hp[(size_t)(kind * a.hs + s) * (a.n_max + 1) + i] : 0.0;
+#pragma unroll
+  for (int s = 0; s < 8; ++s) t += v[s];
+  return t;
 }
 
 // H_bar's column c-1 once beta's column c is final: h = (beta_{0:c,c} -
@@ -479,12 +467,12 @@ __device__ inline void ls_hbar_column(const LsSmall &a, int c) {
   const double *bcol = a.beta + (size_t)c * a.ldB;
   const double d = a.beta[(size_t)(c - 1) * a.ldB + (c - 1)];
   for (int i = threadIdx.x; i <= c; i += NT)
-    a.H[(size_t)(c - 1) * a.ldH + i] = (bcol[i] - (i < c ? a.bvec[i] : 0.0)) / d;
+    a.H[(size_t)(c - 1) * a.ldH + i] = (bcol[i] - (i < c ? ls_product(a, 0, a.bvec, i) : 0.0)) / d;
 }
 
 template <int NT>
 __device__ inline void ls_finalize_body(const LsSmall &a) {
-  __shared__ double sh[NT];
+  __shared__ double sh[2 * NT / 64];
   __shared__ int s_flag;
   DevState *st = a.st;
   const int tid = threadIdx.x;
@@ -566,21 +554,23 @@ __device__ inline void ls_finalize_body(const LsSmall &a) {
   if (hf) {
     const int c = q;  // 0-based index of the new pending column
     const double sk = hu ? a.sigma[q0] : 0.0;
-    // FP32 basis: E w.  k_ls_hprod left the part over the earlier final
-    // columns in what[0, q0); the finished column q0 adds w_q0 E[i, q0] to
+    // FP32 basis: E w.  the product over the earlier final
+    // columns is there; the finished column q0 adds w_q0 E[i, q0] to
     // rows i < q0 and the whole row q0, sum_l E[q0, l] w_l.
     double eq0 = 0.0;
     if (a.gram && hu) {
       double t = 0.0;
       for (int l = tid; l < q0; l += NT) t = fma(a.E[(size_t)q0 * a.n_max + l], red0[l] * a.sigma[l], t);
-      eq0 = ls_block_sum<NT>(t, sh);
+      double v1[1] = {t};
+      ls_block_sums<NT>(v1, sh);
+      eq0 = v1[0];
     }
     for (int i = tid; i < c; i += NT) {
       double wi, pi, ewi = 0.0;
       if (i < q0) {
         wi = red0[i] * a.sigma[i];
         pi = a.z[i];
-        if (a.gram) ewi = a.what[i] + (hu ? a.E[(size_t)q0 * a.n_max + i] * (sc[LS_UF] * sk) : 0.0);
+        if (a.gram) ewi = ls_product(a, 1, a.what, i) + (hu ? a.E[(size_t)q0 * a.n_max + i] * (sc[LS_UF] * sk) : 0.0);
       } else {  // i == q0: the column finished in this sweep
         wi = sc[LS_UF] * sk;
         pi = rhohat0 > 0.0 ? (rho / rhohat0) * rt0 : 0.0;
@@ -617,8 +607,10 @@ __device__ inline void ls_finalize_body(const LsSmall &a) {
       t = fma(a.w[i], a.what[i], t);
       if (nx) t2 = fma(a.what[i], a.z[i], t2);
     }
-    wn2 = ls_block_sum<NT>(t, sh);
-    wz = ls_block_sum<NT>(t2, sh);
+    double v2[2] = {t, t2};
+    ls_block_sums<NT>(v2, sh);
+    wn2 = v2[0];
+    wz = v2[1];
   }
   if (tid == 0) {
     st->q = q;
@@ -654,114 +646,76 @@ __global__ __launch_bounds__(512) void k_ls_finalize(LsSmall a) { ls_finalize_bo
 // ---------------------------------------------------------------------------
 // Launchers
 // ---------------------------------------------------------------------------
-// Tile shapes: FP32 basis 4 wavefronts up to 128 final columns, then 8
-// wavefronts (8 groups up to 256 columns, 16 groups up to 512); FP64 basis 8
-// wavefronts (up to 16 groups, 256 columns).
+// Tile shapes: the narrowest tile of 4 wavefronts that covers the final columns
+// (up to 16 groups, 256 columns), 8 wavefronts beyond; option ls_nw = 16: sixteen
+// for 129-256 columns of an FP32 basis.
 int ls_nw(bool tv_f64, int q, int nw_opt) {
-  if (tv_f64) return 8;
-  if (q <= 128) return 4;
-  return (nw_opt == 16 && q <= 256) ? 16 : 8;
+  if (!tv_f64 && nw_opt == 16 && q > 128 && q <= 256) return 16;
+  return q <= 256 ? 4 : 8;
 }
 
-// Groups per wavefront: the smallest power of two that covers q, except for
-// the FP32 sweep of eight wavefronts, which has 6- and 12-group tiles for
-// 129-192 and 257-384 columns (a power-of-two tile is a third to a half
-// empty there; measured 7-11% faster per sweep at n = 2^24).
 int ls_qw(bool tv_f64, int q, int nw_opt) {
-  if (!tv_f64 && ls_nw(tv_f64, q, nw_opt) == 8) {
-    if (q > 128 && q <= 192) return 6;
-    if (q > 256 && q <= 384) return 12;
-  }
-  return pick_qw(q > 0 ? q : 1, ls_nw(tv_f64, q, nw_opt) * (tv_f64 ? 2 : 4));
+  static const int qs[] = {1, 2, 4, 6, 8, 10, 12, 14, 16};
+  const int nw = ls_nw(tv_f64, q, nw_opt);
+  if (nw == 16) return 4;
+  for (int w : qs)
+    if (nw * w * 4 >= q && (nw == 4 || w >= 10)) return w;
+  return 16;
 }
-
 
 bool ls_supported(bool tv_f64, int q) { return tv_f64 ? q <= 256 : q <= 512; }
 
-template <typename TV, typename TX, int NW>
-static hipError_t launch_ls_q(int qw, int grid, const LsArgs &a, hipStream_t s) {
-  constexpr int NT = NW * 64;
-  switch (qw) {
-    case 1: hipLaunchKernelGGL((k_ls_pass<TV, TX, NW, 1>), dim3(grid), dim3(NT), 0, s, a); break;
-    case 2: hipLaunchKernelGGL((k_ls_pass<TV, TX, NW, 2>), dim3(grid), dim3(NT), 0, s, a); break;
-    case 4: hipLaunchKernelGGL((k_ls_pass<TV, TX, NW, 4>), dim3(grid), dim3(NT), 0, s, a); break;
-    case 8:
-      if constexpr (NW < 16) {  // the 16-wavefront tile covers at most 256 columns with 4 groups
-        hipLaunchKernelGGL((k_ls_pass<TV, TX, NW, 8>), dim3(grid), dim3(NT), 0, s, a);
-        break;
-      }
-      return hipErrorInvalidValue;
-    case 16:
-      if constexpr (NW == 8) {
-        hipLaunchKernelGGL((k_ls_pass<TV, TX, NW, 16>), dim3(grid), dim3(NT), 0, s, a);
-        break;
-      }
-      return hipErrorInvalidValue;
-    case 6:
-      if constexpr (NW == 8 && sizeof(TV) == 4) {
-        hipLaunchKernelGGL((k_ls_pass<TV, TX, NW, 6>), dim3(grid), dim3(NT), 0, s, a);
-        break;
-      }
-      return hipErrorInvalidValue;
-    case 12:
-      if constexpr (NW == 8 && sizeof(TV) == 4) {
-        hipLaunchKernelGGL((k_ls_pass<TV, TX, NW, 12>), dim3(grid), dim3(NT), 0, s, a);
-        break;
-      }
-      return hipErrorInvalidValue;
-    default: return hipErrorInvalidValue;
+template <typename TV, typename TX>
+static const void *ls_fn(int nw, int qw) {
+#define FOA_LS(NW, QW) \
+  case NW * 100 + QW: return reinterpret_cast<const void *>(&k_ls_pass<TV, TX, NW, QW>);
+  switch (nw * 100 + qw) {
+    FOA_LS(4, 1)
+    FOA_LS(4, 2)
+    FOA_LS(4, 4)
+    FOA_LS(4, 6)
+    FOA_LS(4, 8)
+    FOA_LS(4, 10)
+    FOA_LS(4, 12)
+    FOA_LS(4, 14)
+    FOA_LS(4, 16)
+    case 1604:
+      if constexpr (sizeof(TV) == 4) return reinterpret_cast<const void *>(&k_ls_pass<TV, TX, 16, 4>);
+      return nullptr;
   }
-  return hipGetLastError();
+  if constexpr (sizeof(TV) == 4) {  // an FP64 basis holds at most 256 final columns
+    switch (nw * 100 + qw) {
+      FOA_LS(8, 10)
+      FOA_LS(8, 12)
+      FOA_LS(8, 14)
+      FOA_LS(8, 16)
+    }
+  }
+#undef FOA_LS
+  return nullptr;
+}
+
+static const void *ls_kernel(bool tv_f64, bool tx_f64, int q, int nw_opt) {
+  const int nw = ls_nw(tv_f64, q, nw_opt), qw = ls_qw(tv_f64, q, nw_opt);
+  if (qw * nw * 4 < q) return nullptr;  // tile narrower than the basis
+  if (tv_f64) return tx_f64 ? ls_fn<double, double>(nw, qw) : ls_fn<double, float>(nw, qw);
+  return tx_f64 ? ls_fn<float, double>(nw, qw) : ls_fn<float, float>(nw, qw);
 }
 
 hipError_t launch_ls_pass(bool tv_f64, bool tx_f64, int q, int nw_opt, int grid, const LsArgs &a, hipStream_t s) {
   if (!ls_supported(tv_f64, q)) return hipErrorInvalidValue;
-  const int nw = ls_nw(tv_f64, q, nw_opt);
-  const int qw = ls_qw(tv_f64, q, nw_opt);
-  if (qw * nw * (tv_f64 ? 2 : 4) < q) return hipErrorInvalidValue;
-  if (tv_f64) return tx_f64 ? launch_ls_q<double, double, 8>(qw, grid, a, s) : launch_ls_q<double, float, 8>(qw, grid, a, s);
-  if (nw == 4) return tx_f64 ? launch_ls_q<float, double, 4>(qw, grid, a, s) : launch_ls_q<float, float, 4>(qw, grid, a, s);
-  if (nw == 16)
-    return tx_f64 ? launch_ls_q<float, double, 16>(qw, grid, a, s) : launch_ls_q<float, float, 16>(qw, grid, a, s);
-  return tx_f64 ? launch_ls_q<float, double, 8>(qw, grid, a, s) : launch_ls_q<float, float, 8>(qw, grid, a, s);
-}
-
-template <typename TV, typename TX, int NW, int QW>
-static int ls_occ_q() {
-  int nb = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, reinterpret_cast<const void *>(&k_ls_pass<TV, TX, NW, QW>),
-                                                   NW * 64, 0) != hipSuccess)
-    return 1;
-  return nb > 0 ? nb : 1;
-}
-
-template <typename TV, typename TX, int NW>
-static int ls_occ_m(int qw) {
-  switch (qw) {
-    case 1: return ls_occ_q<TV, TX, NW, 1>();
-    case 2: return ls_occ_q<TV, TX, NW, 2>();
-    case 4: return ls_occ_q<TV, TX, NW, 4>();
-    case 8:
-      if constexpr (NW < 16) return ls_occ_q<TV, TX, NW, 8>();
-      return 1;
-    case 6:
-      if constexpr (NW == 8 && sizeof(TV) == 4) return ls_occ_q<TV, TX, NW, 6>();
-      return 1;
-    case 12:
-      if constexpr (NW == 8 && sizeof(TV) == 4) return ls_occ_q<TV, TX, NW, 12>();
-      return 1;
-    default:
-      if constexpr (NW == 8) return ls_occ_q<TV, TX, NW, 16>();
-      return 1;
-  }
+  const void *f = ls_kernel(tv_f64, tx_f64, q, nw_opt);
+  if (!f) return hipErrorInvalidValue;
+  void *args[] = {const_cast<LsArgs *>(&a)};
+  return hipLaunchKernel(f, dim3(grid), dim3(64 * ls_nw(tv_f64, q, nw_opt)), args, 0, s);
 }
 
 int ls_occupancy(bool tv_f64, bool tx_f64, int q, int nw_opt) {
-  const int nw = ls_nw(tv_f64, q, nw_opt), qw = ls_qw(tv_f64, q, nw_opt);
-  if (tv_f64) return tx_f64 ? ls_occ_m<double, double, 8>(qw) : ls_occ_m<double, float, 8>(qw);
-  if (nw == 4) return tx_f64 ? ls_occ_m<float, double, 4>(qw) : ls_occ_m<float, float, 4>(qw);
-  if (nw == 16) return tx_f64 ? ls_occ_m<float, double, 16>(qw) : ls_occ_m<float, float, 16>(qw);
-  return tx_f64 ? ls_occ_m<float, double, 8>(qw) : ls_occ_m<float, float, 8>(qw);
+  int nb = 0;
+  const void *f = ls_kernel(tv_f64, tx_f64, q, nw_opt);
+  if (!f || hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, f, 64 * ls_nw(tv_f64, q, nw_opt), 0) != hipSuccess)
+    return 1;
+  return nb > 0 ? nb : 1;
 }
 
 hipError_t launch_ls_reduce(const LsSmall &a, hipStream_t s) {
@@ -774,7 +728,7 @@ hipError_t launch_ls_finalize(const LsSmall &a, hipStream_t s) {
   // the H_bar product for the column the finalize finishes (1 <= q <= nt;
   // for q = 1 it writes the empty product 0)
   if (a.nt >= 1) {
-    hipLaunchKernelGGL(k_ls_hprod, dim3((a.nt + 63) / 64), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(k_ls_hprod, dim3((a.nt + 63) / 64, a.hs, a.gram ? 2 : 1), dim3(256), 0, s, a);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
@@ -852,7 +806,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ls_wave
     a.n_max = uniform(d.n_max);
     a.ldg = uniform(d.ldg);
     a.flush = flush;
-    ls_pass_body<TV, TX, NW, QW, ls_pf<TV, NW, QW>()>(a, lo - ps, e - ps, 1, (int)blockIdx.x - uniform(st->seg0), lds);
+    ls_pass_body<TV, TX, NW, QW>(a, lo - ps, e - ps, 1, (int)blockIdx.x - uniform(st->seg0), lds);
     lo = e;
     ++i;
   }
@@ -871,11 +825,8 @@ __global__ __launch_bounds__(256) void k_ls_hprod_batch(BatchArgs b) {
   const LsSmall a = ls_small_of(d, b.ls_mode == 2);
   if (!d.st->act || !(d.st->ls_u || (a.gram && d.st->ls_x))) return;
   if ((int)blockIdx.x * 64 >= d.st->q && blockIdx.x > 0) return;
-  if (d.st->ls_u) ls_hprod_body(a, blockIdx.x);
-  if (a.gram && d.st->ls_x) {
-    __syncthreads();
-    ls_ew_body(a, blockIdx.x);
-  }
+  if (d.st->ls_u) ls_product_body<0>(a, blockIdx.x, 0, 1, a.bvec);
+  if (a.gram && d.st->ls_x) ls_product_body<1>(a, blockIdx.x, 0, 1, a.what);
 }
 
 __global__ __launch_bounds__(512) void k_ls_finalize_batch(BatchArgs b) {
@@ -896,23 +847,16 @@ __global__ __launch_bounds__(512) void k_ls_finalize_batch(BatchArgs b) {
 }
 
 // Kernel shape of bucket k (basis sizes up to 32, 64, 128, 256, 512 final
-// columns; k = 0 for an empty basis takes the shape of k = 1).  FP32 basis:
-// 1, 2, 4, 8, 8 wavefronts with 8, 8, 8, 8, 16 groups; FP64 basis: 8
-// wavefronts with 2, 4, 8, 16 groups (at most 256 columns).
+// columns; k = 0 for an empty basis takes the shape of k = 1): 1, 2, 4, 8, 8
+// wavefronts with 8, 8, 8, 8, 16 groups (an FP64 basis at most 256 columns).
 bool ls_batch_supported(bool tv_f64, int k) { return !tv_f64 || k <= 4; }
 
 template <typename TV, typename TX, int BK>
 static const void *ls_batch_fn(int *nt) {
-  if constexpr (sizeof(TV) == 4) {
-    constexpr int NW = BK <= 1 ? 1 : (BK == 2 ? 2 : (BK == 3 ? 4 : 8));
-    constexpr int QW = BK == 5 ? 16 : 8;
-    *nt = NW * 64;
-    return reinterpret_cast<const void *>(&k_ls_pass_batch<TV, TX, NW, QW, BK>);
-  } else {
-    constexpr int QW = BK <= 1 ? 2 : (BK == 2 ? 4 : (BK == 3 ? 8 : 16));
-    *nt = 8 * 64;
-    return reinterpret_cast<const void *>(&k_ls_pass_batch<TV, TX, 8, QW, BK>);
-  }
+  constexpr int NW = BK <= 1 ? 1 : (BK == 2 ? 2 : (BK == 3 ? 4 : 8));
+  constexpr int QW = BK == 5 ? 16 : 8;
+  *nt = NW * 64;
+  return reinterpret_cast<const void *>(&k_ls_pass_batch<TV, TX, NW, QW, BK>);
 }
 
 template <typename TV, typename TX>
