@@ -120,6 +120,20 @@ def test_svd_left(shim):
         assert np.allclose(np.linalg.norm(U.T @ R, axis=1), S, rtol=1e-8, atol=1e-12 * ref[0])
 
 
+@pytest.mark.parametrize("m", [15, 16, 17, 31, 33])
+def test_svd_left_remainders(shim, m):
+    """Orders around multiples of the 16 sums of the dot product: singular
+    values within m eps of the largest (backward stability), U orthogonal."""
+    A = np.asfortranarray(np.random.default_rng(m).standard_normal((m, m)))
+    U = np.zeros((m, m), order="F")
+    S = np.zeros(m)
+    assert shim.shim_svd(m, _p(A), _p(U), _p(S)) == 0
+    ref = np.linalg.svd(A, compute_uv=False)
+    assert np.abs(S - ref).max() <= 10 * m * EPS * ref[0]
+    assert np.linalg.norm(U.T @ U - np.eye(m), 2) <= 100 * m * EPS
+    assert np.allclose(np.linalg.norm(U.T @ A, axis=1), S, rtol=0, atol=100 * m * EPS * ref[0])
+
+
 def test_solve_complex(shim):
     rng = np.random.default_rng(9)
     m = 37
