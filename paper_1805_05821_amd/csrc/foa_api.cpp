@@ -227,11 +227,14 @@ void release_events(foa_ctx_s *c) {
 
 // Enqueue one push of snapshot x (Algorithm 1: the first-snapshot
 // normalisation for q = 0, else one iteration of its snapshot loop).
-foa_status enqueue_push(foa_ctx_s *c, const void *x, bool x_f64) {
-  if (c->form == 1) return enqueue_ls_push(c, x, x_f64);
-  const bool v64 = c->prec == FOA_PREC_F64;
-  const int j = c->q_host;
-  const int G = pass_grid(c, j, x_f64);
+// Pushes that one launch takes from here on (0: the kernels of enqueue_push): a
+// small stream with no kernel shape or grid asked for and no timing of the passes.
+static int small_run(const foa_ctx_s *c, int rem) {
+  if (c->form != 0 || c->nw > 0 || c->grid_opt > 0 || !c->prefetch || c->profile) return 0;
+  return small_push_run(c->prec == FOA_PREC_F64, c->L.P, c->q_host, rem);
+}
+
+static PassArgs pass_args(const foa_ctx_s *c, const void *x, int j) {
   PassArgs pa{};
   pa.W = c->W;
   pa.x = x;
@@ -247,6 +250,30 @@ foa_status enqueue_push(foa_ctx_s *c, const void *x, bool x_f64) {
   pa.j = j;
   pa.n_max = c->n_max;
   pa.ldg = c->L.ldg;
+  return pa;
+}
+
+static foa_status enqueue_small_run(foa_ctx_s *c, const void *x, int64_t ld, int count, bool x_f64) {
+  const int j = c->q_host;
+  SmallArgs sa = c->sa;
+  sa.G = (int)c->L.P;  // a slot per panel
+  sa.j = j;
+  c->mirror_valid = false;
+  c->dmd.valid = false;
+  const hipError_t e =
+      launch_push_small(c->prec == FOA_PREC_F64, x_f64, pass_args(c, x, j), sa, ld, count, c->stream);
+  if (e != hipSuccess) return hip_err(c, e, "small pushes");
+  c->q_host = j + count;
+  return FOA_OK;
+}
+
+foa_status enqueue_push(foa_ctx_s *c, const void *x, bool x_f64) {
+  if (c->form == 1) return enqueue_ls_push(c, x, x_f64);
+  if (small_run(c, 1)) return enqueue_small_run(c, x, 0, 1, x_f64);
+  const bool v64 = c->prec == FOA_PREC_F64;
+  const int j = c->q_host;
+  const int G = pass_grid(c, j, x_f64);
+  PassArgs pa = pass_args(c, x, j);
   SmallArgs sa = c->sa;
   sa.G = G;
   sa.j = j;
@@ -490,11 +517,14 @@ foa_status foa_push_block(foa_ctx c, const void *d_X, int64_t ld, int32_t p, foa
     return set_err(c, FOA_E_ARG, "bad block arguments");
   const size_t es = x_dtype == FOA_F64 ? 8 : 4;
   if (c->q_host + p > c->n_max) return set_err(c, FOA_E_CAPACITY, "block exceeds capacity");
-  for (int k = 0; k < p; ++k) {
+  for (int k = 0; k < p;) {
     foa_status r = push_checks(c);
     if (r != FOA_OK) return r;
-    r = enqueue_push(c, static_cast<const char *>(d_X) + (size_t)k * ld * es, x_dtype == FOA_F64);
+    const void *x = static_cast<const char *>(d_X) + (size_t)k * ld * es;
+    const int run = small_run(c, p - k);
+    r = run ? enqueue_small_run(c, x, ld, run, x_dtype == FOA_F64) : enqueue_push(c, x, x_dtype == FOA_F64);
     if (r != FOA_OK) return r;
+    k += run ? run : 1;
   }
   return FOA_OK;
 }

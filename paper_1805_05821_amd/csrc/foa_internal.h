@@ -283,6 +283,11 @@ int pass_occupancy(bool tv_f64, bool tx_f64, bool prefetch, int nw, int qw);
 hipError_t launch_reduce(int mode, const SmallArgs &a, hipStream_t s);
 hipError_t launch_finalize(const SmallArgs &a, hipStream_t s);
 hipError_t launch_finalize_next(const SmallArgs &a, hipStream_t s);
+// Small streams (foa_small.hip): how many of the next rem pushes from basis size j
+// one launch takes (0: none), and that launch (snapshot k at x + k * ldx).
+int small_push_run(bool tv_f64, int64_t P, int j, int rem);
+hipError_t launch_push_small(bool tv_f64, bool tx_f64, const PassArgs &a, const SmallArgs &sa, int64_t ldx, int count,
+                             hipStream_t s);
 hipError_t launch_finalize_init(const SmallArgs &a, hipStream_t s);
 hipError_t launch_nextb(const SmallArgs &a, hipStream_t s);
 hipError_t launch_copy_basis(bool tv_f64, const void *W, const double *sigma, int64_t r0,

@@ -327,3 +327,47 @@ def test_small_stream_reductions(prec, n, N):
     orth = np.linalg.norm(np.eye(g["q"]) - g["V"].T @ g["V"], 2)
     announce(f"{n} x {N}: kappa={kap:.2e} relH2={eH:.2e} orth={orth:.2e}")
     assert g["q"] == N and eH <= 10 * EPS32 * kap and orth <= 10 * np.sqrt(N) * EPS32
+
+
+@pytest.mark.parametrize("prec,n,N", [
+    ("f32", 1, 1), ("f32", 65, 30), ("f32", 1024, 70), ("f32", 1025, 40), ("f32", 2048, 34), ("f32", 2049, 12),
+    ("f64", 64, 20), ("f64", 1000, 40), ("f64", 2047, 20),
+])
+@pytest.mark.parametrize("stop", [None, "nan", "rank"])
+def test_small_stream_runs(prec, n, N, stop):
+    """Streams whose pushes go through one workgroup (every tile width, the
+    pushes beyond the widest, rows on both sides of the limits), in runs and
+    one at a time, full or stopped by a NaN or a dependent snapshot: bitwise
+    the results of the general kernels with a workgroup per panel."""
+    import torch
+
+    from paper_1805_05821_amd import foa as F
+    from paper_1805_05821_amd.stream import FOAStream
+
+    X = np.random.default_rng(n + N).standard_normal((N, n + 3))
+    if stop == "nan" and N > 2:
+        X[2 * N // 3, n // 2] = np.nan
+    if stop == "rank" and N > 2:
+        X[2 * N // 3] = X[0]
+    for dt in (torch.float32, torch.float64):
+        Xd = torch.from_numpy(X).to(device="cuda", dtype=dt)[:, :n]
+        out = []
+        for grid, each in ((0, False), (0, True), ((n + 63) // 64, False)):
+            s = FOAStream(n, N, prec=prec, breakdown_tol=1e-6 if stop == "rank" else 0.0, ws_fill=0xFF)
+            s.set_option("grid", grid)
+            if each:
+                s.push_all(Xd)
+            else:
+                s.push_block(Xd)
+            try:
+                st, q = s.sync()
+            except F.FOAError as e:
+                st = e.code
+            H, B, q, m = s.state()
+            out.append((st, q, m, H, B, s.basis(q).cpu().numpy()))
+            s.close()
+        announce(f"{prec} {n} x {N} {stop} {dt}: status {out[0][0]} q {out[0][1]}")
+        for o in out[:2]:
+            assert o[:3] == out[2][:3]
+            for a, b in zip(o[3:], out[2][3:]):
+                assert np.array_equal(a, b)
