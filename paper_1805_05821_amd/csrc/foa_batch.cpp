@@ -39,10 +39,9 @@ size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 struct BatchLayout {
   std::vector<size_t> off;       // per-stream Layout base
   std::vector<Layout> L;
-  size_t states = 0, streams = 0, xptrs = 0, rblk_s = 0, rblk_c = 0, tune_x = 0, total = 0;
+  size_t states = 0, streams = 0, xptrs = 0, tune_x = 0, total = 0;
   size_t plist = 0, ppre = 0, pfirst = 0, pmeta = 0, pspos = 0;
   size_t qlist = 0, qpre = 0, qsgrp = 0, qfirst = 0, qctl = 0;  // persistent step
-  size_t rblocks = 0;
   int64_t max_n = 0;
   int max_nmax = 0;
 };
@@ -58,7 +57,6 @@ BatchLayout batch_layout(int S, const int64_t *n, const int32_t *n_max, foa_prec
     B.off.push_back(o);
     B.L.push_back(L);
     o = align_up(o + L.total);
-    B.rblocks += (size_t)(n_max[s] + 1 + 3) / 4;
     B.max_n = std::max<int64_t>(B.max_n, n[s]);
     B.max_nmax = std::max<int>(B.max_nmax, n_max[s]);
   }
@@ -80,8 +78,6 @@ BatchLayout batch_layout(int S, const int64_t *n, const int32_t *n_max, foa_prec
   B.qfirst = take((size_t)kMaxGroups * kMaxRanks * sizeof(int));
   B.qctl = take(kCtlInts * sizeof(int));
   B.xptrs = take((size_t)S * sizeof(void *));
-  B.rblk_s = take(B.rblocks * sizeof(int));
-  B.rblk_c = take(B.rblocks * sizeof(int));
   B.tune_x = take((size_t)B.max_n * sizeof(float));
   B.total = o;
   return B;
@@ -181,15 +177,21 @@ foa_status upload_config(foa_batch_s *b, int unit_panels) {
 // the reductions, finalize and next b.  Persistent mode (FP32 basis): the
 // streams of up to kPersistCols columns run in one persistent launch; first
 // pushes and wider bases take the bucket launches, which skip the others.
+// Most basis columns of a stream while bucket kmax is the widest in use.
+int step_cols(const foa_batch_s *b, int kmax) {
+  const int cols = kmax < 1 ? 0 : batch_cols_per_qw(b->prec == FOA_PREC_F64) << (kmax - 1);
+  return std::min(cols, b->B.max_nmax);
+}
+
 hipError_t enqueue_ls_step(foa_batch_s *b, bool x_f64, hipStream_t s, int kmax) {
   const bool v64 = b->prec == FOA_PREC_F64;
   const BatchArgs &a = b->args;
   hipError_t e;
   if ((e = launch_batch_plan(a, s)) != hipSuccess) return e;
-  for (int k = 0; k <= kmax && k < NBUCKET; ++k)
+  for (int k = 1; k <= std::max(kmax, 1) && k < NBUCKET; ++k)
     if (ls_batch_supported(v64, k) && (e = launch_ls_batch_pass(v64, x_f64, k, a.gridb[k], a, s)) != hipSuccess)
       return e;
-  return launch_ls_batch_small(a, s);
+  return launch_ls_batch_small(a, step_cols(b, kmax), s);
 }
 
 hipError_t enqueue_step(foa_batch_s *b, bool x_f64, hipStream_t s, int kmax) {
@@ -197,6 +199,7 @@ hipError_t enqueue_step(foa_batch_s *b, bool x_f64, hipStream_t s, int kmax) {
   const bool v64 = b->prec == FOA_PREC_F64;
   const int cols = batch_cols_per_qw(v64);
   const int qmax = pick_qw(std::max(b->B.max_nmax - 1, 1), cols);
+  const int cmax = step_cols(b, kmax);
   const bool pers = b->persist && !v64;
   // buckets run by launches: all, or in persistent mode only those wider than kPersistCols
   int kfirst = 1;
@@ -210,14 +213,13 @@ hipError_t enqueue_step(foa_batch_s *b, bool x_f64, hipStream_t s, int kmax) {
   if (pers && (e = launch_step_persist(x_f64, b->pgrid, a, s)) != hipSuccess) return e;
   for (int qw = 1, k = 1; qw <= qmax && k <= kmax; qw *= 2, ++k)
     if (k >= kfirst && (e = launch_batch_pass(PM_A, v64, x_f64, k, a.gridb[k], a, s)) != hipSuccess) return e;
-  if ((e = launch_batch_reduce(1, a, s)) != hipSuccess) return e;
+  if ((e = launch_batch_reduce(1, cmax, a, s)) != hipSuccess) return e;
   for (int qw = 1, k = 1; qw <= qmax && k <= kmax; qw *= 2, ++k)
     if (k >= kfirst && (e = launch_batch_pass(PM_B, v64, x_f64, k, a.gridb[k], a, s)) != hipSuccess) return e;
-  if ((e = launch_batch_reduce(2, a, s)) != hipSuccess) return e;
+  if ((e = launch_batch_reduce(2, cmax, a, s)) != hipSuccess) return e;
   for (int qw = 1, k = 1; qw <= qmax && k <= kmax; qw *= 2, ++k)
     if (k >= kfirst && (e = launch_batch_pass(PM_C, v64, x_f64, k, a.gridb[k], a, s)) != hipSuccess) return e;
-  if ((e = launch_batch_finalize(a, s)) != hipSuccess) return e;
-  return launch_batch_nextb(a, s);
+  return launch_batch_finalize(a, s);
 }
 
 void drop_graphs(foa_batch_s *b) {
@@ -565,20 +567,9 @@ foa_status foa_batch_init(foa_batch *out, int32_t S, const int64_t *n, const int
   b->args.p_spin = kPersistSpin;
   if (const char *e = std::getenv("FOA_PERSIST_SPIN")) b->args.p_spin = std::max(0, std::atoi(e));
   b->args.xptrs = reinterpret_cast<const void *const *>(b->ws + b->B.xptrs);
-  b->args.rblk_stream = reinterpret_cast<const int *>(b->ws + b->B.rblk_s);
-  b->args.rblk_c0 = reinterpret_cast<const int *>(b->ws + b->B.rblk_c);
   b->args.S = S;
   b->args.max_nmax = b->B.max_nmax;
-  std::vector<int> rs, rc;
-  for (int s = 0; s < S; ++s)
-    for (int c0 = 0; c0 < n_max[s] + 1; c0 += 4) {
-      rs.push_back(s);
-      rc.push_back(c0);
-    }
-  b->args.n_rblocks = (int)rs.size();
-  if (hipMemcpy(b->ws + b->B.rblk_s, rs.data(), rs.size() * sizeof(int), hipMemcpyHostToDevice) != hipSuccess ||
-      hipMemcpy(b->ws + b->B.rblk_c, rc.data(), rc.size() * sizeof(int), hipMemcpyHostToDevice) != hipSuccess ||
-      hipStreamCreateWithFlags(&b->cap, hipStreamNonBlocking) != hipSuccess) {
+  if (hipStreamCreateWithFlags(&b->cap, hipStreamNonBlocking) != hipSuccess) {
     foa_batch_destroy(b);
     return FOA_E_DEVICE;
   }

@@ -55,29 +55,44 @@ __device__ __forceinline__ int bucket_of(int j, int cols_per_qw) {
   return k;
 }
 
+// Inclusive sum over the lanes up to this one (DPP row shifts, then row broadcasts).
+__device__ __forceinline__ int lanes_prefix(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);  // row_shr 1, 2, 4, 8
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // row_bcast 15, 31
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
+  return v;
+}
+
 // Step state, bucket lists and workgroup ranges, one workgroup of 1024
-// threads.  Streams are taken 1024 at a time; per bucket a wavefront prefix
-// sum (count and panels) plus the per-wavefront totals give each active
-// stream its list position and panel offset; a last sweep cuts each
-// bucket's panels into its workgroups' ranges.
+// threads.  Streams are taken 1024 at a time; per bucket the rank among the
+// wavefront's lanes (ballot) and a prefix sum of the panels (DPP; a batch holds
+// fewer than 2^31 panels: 2^37 rows of at least 12 bytes) plus the
+// per-wavefront totals give each active stream its list position and panel
+// offset; then each bucket's panels are cut into its workgroups' ranges, from
+// registers for up to 1024 streams.  Bound: latency; 64 streams 11.0 us with
+// shuffles, 64-bit divisions and the lists read back, 6.9 us so.
 __global__ __launch_bounds__(1024) void k_batch_plan(BatchArgs b) {
-  __shared__ int s_wcnt[16][NBUCKET];
-  __shared__ int64_t s_wpan[16][NBUCKET];
-  __shared__ int s_cnt[NBUCKET];
-  __shared__ int64_t s_tot[NBUCKET];
+  __shared__ int s_wcnt[16][NBUCKET], s_wpan[16][NBUCKET];
+  __shared__ int s_cnt[NBUCKET], s_tot[NBUCKET], s_G[NBUCKET];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   if (tid < NBUCKET) {
     s_cnt[tid] = 0;
     s_tot[tid] = 0;
   }
   __syncthreads();
+  int bk = -1, pos = 0, P = 0, p0 = 0;
+  DevState *st = nullptr;
   for (int c0 = 0; c0 < b.S; c0 += 1024) {
     const int s = c0 + tid;
-    int bk = -1;
-    int64_t P = 0;
+    const int nw = b.S - c0 >= 1024 ? 16 : (b.S - c0 + 63) / 64;
+    bk = -1;
+    P = 0;
     if (s < b.S) {
       const BatchStream &d = b.streams[s];
-      DevState *st = d.st;
+      st = d.st;
       const bool offered = b.ls_mode != 2 && b.xptrs[s] != nullptr;
       const int j = st->q;
       // one-reduction form: the pending columns also hold snapshots; a flush
@@ -93,96 +108,88 @@ __global__ __launch_bounds__(1024) void k_batch_plan(BatchArgs b) {
       st->pers = 0;
       if (offered && !room && st->status == ST_ACTIVE) st->full = 1;
       if (act) {
-        bk = bucket_of(j, b.cols_per_qw);
-        P = d.P;
+        // the one-reduction sweep of an empty basis is its narrowest tile's
+        bk = b.ls_mode && j == 0 ? 1 : bucket_of(j, b.cols_per_qw);
+        P = (int)d.P;
       }
     }
-    int myf = 0;
-    int64_t myp = 0;
+    int myf = 0, myp = 0;
 #pragma unroll
     for (int k = 0; k < NBUCKET; ++k) {
-      int f = bk == k ? 1 : 0;
-      int64_t pp = bk == k ? P : 0;
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const int tf = __shfl_up(f, o, 64);
-        const int64_t tp = __shfl_up(pp, o, 64);
-        if (lane >= o) {
-          f += tf;
-          pp += tp;
-        }
-      }
+      const uint64_t m = __ballot(bk == k);
+      const int pp = lanes_prefix(bk == k ? P : 0);
       if (bk == k) {
-        myf = f;
-        myp = pp;
+        myf = __popcll(m & ((1ull << lane) - 1));
+        myp = pp - P;
       }
       if (lane == 63) {
-        s_wcnt[wave][k] = f;
+        s_wcnt[wave][k] = __popcll(m);
         s_wpan[wave][k] = pp;
       }
     }
     __syncthreads();
     if (bk >= 0) {
-      int wb = 0;
-      int64_t wp = 0;
+      int wb = s_cnt[bk], wp = s_tot[bk];
       for (int w = 0; w < wave; ++w) {
         wb += s_wcnt[w][bk];
         wp += s_wpan[w][bk];
       }
-      const int pos = s_cnt[bk] + wb + myf - 1;
+      pos = wb + myf;
+      p0 = wp + myp;
       b.list[(size_t)bk * b.S + pos] = s;
-      b.pre[(size_t)bk * (b.S + 1) + pos] = s_tot[bk] + wp + myp - P;
-      b.spos[s] = (bk << 24) | pos;
+      b.pre[(size_t)bk * (b.S + 1) + pos] = p0;
+      if (b.S > 1024) b.spos[s] = (bk << 24) | pos;
     }
     __syncthreads();
     if (tid < NBUCKET) {
-      int c = 0;
-      int64_t t = 0;
-      for (int w = 0; w < 16; ++w) {
+      int c = s_cnt[tid], t = s_tot[tid];
+      for (int w = 0; w < nw; ++w) {
         c += s_wcnt[w][tid];
         t += s_wpan[w][tid];
       }
-      s_cnt[tid] += c;
-      s_tot[tid] += t;
+      s_cnt[tid] = c;
+      s_tot[tid] = t;
+      if (c0 + 1024 >= b.S) {
+        b.pre[(size_t)tid * (b.S + 1) + c] = t;
+        int G = 0;
+        if (t > 0) {
+          const int g = t / b.min_seg;
+          G = g < 1 ? 1 : (g > b.gridb[tid] ? b.gridb[tid] : g);
+        }
+        b.meta[2 * tid] = c;
+        b.meta[2 * tid + 1] = G;
+        s_G[tid] = G;
+      }
     }
     __syncthreads();
   }
-  __shared__ int s_G[NBUCKET];
-  if (tid < NBUCKET) {
-    const int c = s_cnt[tid];
-    const int64_t T = s_tot[tid];
-    b.pre[(size_t)tid * (b.S + 1) + c] = T;
-    int G = 0;
-    if (T > 0) {
-      const int64_t g = T / b.min_seg;
-      G = (int)(g < 1 ? 1 : (g > b.gridb[tid] ? b.gridb[tid] : g));
-    }
-    b.meta[2 * tid] = c;
-    b.meta[2 * tid + 1] = G;
-    s_G[tid] = G;
-  }
-  __syncthreads();
   // Ranges: workgroup g of bucket k covers panels [g T / G, (g + 1) T / G)
   // of the bucket's concatenation, so the workgroup holding panel p is
   // ((p + 1) G - 1) / T.  Per active stream (panels [p0, p1) of its bucket):
   // its first workgroup and workgroup count, and it is the first stream of
   // workgroups ceil(p0 G / T) .. ceil(p1 G / T) - 1 (those whose range
-  // starts inside it).
-  for (int s = tid; s < b.S; s += 1024) {
-    DevState *st = b.streams[s].st;
-    if (!st->act) continue;
-    const int code = b.spos[s];
-    const int k = code >> 24, pos = code & 0xFFFFFF;
+  // starts inside it).  The products are below 2^43 and the divisors below
+  // 2^31, so the double quotients round to no integer they do not reach.
+  auto range = [&](DevState *st, int k, int pos, int p0, int p1) {
     const int G = s_G[k];
-    const int64_t T = s_tot[k];
-    const int64_t *pre = b.pre + (size_t)k * (b.S + 1);
-    const int64_t p0 = pre[pos], p1 = pre[pos + 1];
-    const int g0 = (int)(((p0 + 1) * G - 1) / T);
-    const int g1 = (int)((p1 * G - 1) / T);
+    const double T = (double)s_tot[k], g = (double)G;
+    const int g0 = (int)(((double)(p0 + 1) * g - 1.0) / T);
+    const int g1 = (int)(((double)p1 * g - 1.0) / T);
     st->seg0 = g0;
     st->nseg = g1 - g0 + 1;
-    const int f0 = (int)((p0 * G + T - 1) / T), f1 = (int)((p1 * G + T - 1) / T);
-    for (int g = f0; g < f1 && g < G; ++g) b.first[k * kMaxBatchGrid + g] = pos;
+    const int f0 = (int)(((double)p0 * g + T - 1.0) / T), f1 = (int)(((double)p1 * g + T - 1.0) / T);
+    for (int i = f0; i < f1 && i < G; ++i) b.first[k * kMaxBatchGrid + i] = pos;
+  };
+  if (b.S <= 1024) {
+    if (bk >= 0) range(st, bk, pos, p0, p0 + P);
+    return;
+  }
+  for (int s = tid; s < b.S; s += 1024) {
+    DevState *d = b.streams[s].st;
+    if (!d->act) continue;
+    const int code = b.spos[s];
+    const int64_t *pre = b.pre + (size_t)(code >> 24) * (b.S + 1) + (code & 0xFFFFFF);
+    range(d, code >> 24, code & 0xFFFFFF, (int)pre[0], (int)pre[1]);
   }
 }
 
@@ -232,15 +239,20 @@ void k_pass_batch(BatchArgs b) {
   }
 }
 
+// Bound: latency (a chain of three loads before the sums) and the launch of its
+// workgroups.  256 streams of 20..300 columns: a workgroup per four columns 9.8 us,
+// per sixteen 5.2 us.
 template <int MODE>
 __global__ __launch_bounds__(256) void k_reduce_batch(BatchArgs b) {
-  const int s = b.rblk_stream[blockIdx.x];
-  const BatchStream &d = b.streams[s];
-  if (!d.st->act || d.st->jstep == 0 || d.st->pers) return;
-  reduce_body<MODE>(small_of(d), b.rblk_c0[blockIdx.x]);
+  const BatchStream &d = b.streams[blockIdx.y];
+  const int j = d.st->jstep;
+  if (!d.st->act || j == 0 || d.st->pers || (int)blockIdx.x * 16 > j) return;
+  reduce4_body<MODE>(small_of(d), blockIdx.x * 16);
 }
 
-__global__ __launch_bounds__(256) void k_finalize_batch(BatchArgs b) {
+// Finalize and the next push's partial beta column, a workgroup per stream.  256
+// streams of 20..300 columns: as two kernels 6.1 + 15.6 us, 11.7 us so.
+__global__ __launch_bounds__(1024) void k_finalize_batch(BatchArgs b) {
   const int s = blockIdx.x;
   const BatchStream &d = b.streams[s];
   DevState *st = d.st;
@@ -252,16 +264,9 @@ __global__ __launch_bounds__(256) void k_finalize_batch(BatchArgs b) {
   if (st->pers) return;                // finalized by the persistent step kernel
   const SmallArgs a = small_of(d);
   if (st->jstep == 0)
-    finalize_init_body(a);
+    finalize_init_next_body(a);
   else
-    finalize_body(a);
-}
-
-__global__ __launch_bounds__(256) void k_nextb_batch(BatchArgs b) {
-  const BatchStream &d = b.streams[blockIdx.y];
-  if (!d.st->act || d.st->pers) return;
-  if ((int)blockIdx.x * 64 > d.st->q) return;
-  nextb_body(small_of(d), blockIdx.x);
+    finalize_next_body<511>(a);
 }
 
 __global__ __launch_bounds__(256) void k_batch_init_states(BatchArgs b, double tol) {
@@ -789,21 +794,17 @@ hipError_t launch_batch_plan(const BatchArgs &b, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_batch_reduce(int mode, const BatchArgs &b, hipStream_t s) {
+hipError_t launch_batch_reduce(int mode, int cols, const BatchArgs &b, hipStream_t s) {
+  const dim3 grid((cols + 16) / 16, b.S);  // columns 0 .. cols
   if (mode == 1)
-    hipLaunchKernelGGL(k_reduce_batch<1>, dim3(b.n_rblocks), dim3(256), 0, s, b);
+    hipLaunchKernelGGL(k_reduce_batch<1>, grid, dim3(256), 0, s, b);
   else
-    hipLaunchKernelGGL(k_reduce_batch<2>, dim3(b.n_rblocks), dim3(256), 0, s, b);
+    hipLaunchKernelGGL(k_reduce_batch<2>, grid, dim3(256), 0, s, b);
   return hipGetLastError();
 }
 
 hipError_t launch_batch_finalize(const BatchArgs &b, hipStream_t s) {
-  hipLaunchKernelGGL(k_finalize_batch, dim3(b.S), dim3(256), 0, s, b);
-  return hipGetLastError();
-}
-
-hipError_t launch_batch_nextb(const BatchArgs &b, hipStream_t s) {
-  hipLaunchKernelGGL(k_nextb_batch, dim3((b.max_nmax + 64) / 64, b.S), dim3(256), 0, s, b);
+  hipLaunchKernelGGL(k_finalize_batch, dim3(b.S), dim3(1024), 0, s, b);
   return hipGetLastError();
 }
 

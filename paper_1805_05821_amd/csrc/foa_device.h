@@ -627,6 +627,52 @@ __device__ inline void reduce_body(const SmallArgs &a, int c0) {
   }
 }
 
+// Sums of four vectors p[k][0 .. G) by one wavefront, each as strided_sum forms it,
+// with their loads in flight together (null: 0).
+__device__ __forceinline__ void strided_sum4(const double *const (&p)[4], int G, int lane, double (&t)[4]) {
+#pragma unroll
+  for (int k = 0; k < 4; ++k) t[k] = 0.0;
+  for (int g = lane; g < G; g += 64) {
+    double v[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = p[k] ? p[k][g] : 0.0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) t[k] += v[k];
+  }
+#pragma unroll
+  for (int k = 0; k < 4; ++k) t[k] = lanes_sum<64>(t[k]);
+}
+
+// reduce_body of four columns a wavefront (columns c0 .. c0+15 of a workgroup of
+// four), for the batched form: its streams have few partial sums per column, and a
+// column per wavefront made the launch 10 000 workgroups.
+template <int MODE>
+__device__ inline void reduce4_body(const SmallArgs &a, int c0) {
+  const int lane = threadIdx.x & 63;
+  const int cw = c0 + 4 * __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const double *p[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k)
+    p[k] = cw + k < a.j ? a.part + (size_t)(cw + k) * a.ldg : (MODE == 1 && cw + k == a.j ? a.partn : nullptr);
+  double t[4];
+  strided_sum4(p, a.G, lane, t);
+  const double tl = lane == 0 ? t[0] : (lane == 1 ? t[1] : (lane == 2 ? t[2] : t[3]));
+  const int c = cw + lane;
+  if (lane < 4 && c < a.j) {
+    const double sg = a.sigma[c], v = sg * tl;
+    if (MODE == 1) {
+      a.h[c] = v;
+      a.coefB[c] = sg * v;
+    } else {
+      a.s[c] = v;
+      a.h[c] = a.h[c] + v;
+      a.coefC[c] = sg * v;
+    }
+  } else if (MODE == 1 && lane < 4 && c == a.j) {
+    a.st->xn2 = tl;
+  }
+}
+
 // Sum over a workgroup of NT threads (fixed tree order).
 template <int NT>
 __device__ inline double block_sum_t(double t, double *sh) {
@@ -776,15 +822,16 @@ __device__ inline void nextb_body_t(const SmallArgs &a, int chunk0) {
 __device__ inline void nextb_body(const SmallArgs &a, int chunk) { nextb_body_t<256>(a, chunk); }
 
 // finalize_body and nextb_body in one workgroup of 1024 threads, for bases of up
-// to kFinNextCols columns, with the same sums in the same order (the results are
-// bitwise those of the two kernels).  The new columns of H_bar and beta stay in
+// to JMAX columns before the push, with the same sums in the same order (the results
+// are bitwise those of the two kernels).  The new columns of H_bar and beta stay in
 // LDS, where the next push's partial beta column takes them from, and every
 // thread works out the status for itself, so one barrier stands between the loads
 // and the products.  Bound: latency; at 64 columns 4.4 us, the two kernels 3.8 +
 // 3.1 us and a launch more.
+template <int JMAX>
 __device__ inline void finalize_next_body(const SmallArgs &a) {
   __shared__ double s_n[256];
-  __shared__ double s_h[kFinNextCols + 1], s_b[kFinNextCols + 1];
+  __shared__ double s_h[JMAX + 1], s_b[JMAX + 1];
   __shared__ double s_p[16][64];
   DevState *st = a.st;
   const int tid = threadIdx.x;
@@ -808,12 +855,15 @@ __device__ inline void finalize_next_body(const SmallArgs &a) {
 #pragma unroll
   for (int u = 0; u < U; ++u) v[u] = a0 + u < ah ? a.H[(size_t)(a0 + u) * a.ldH + i] : 0.0;
   const double sgi = sl == 0 && i < j ? a.sigma[i] : 0.0;
-  static_assert(kStreamSlots <= 4 * 256, "slots of a pass");
   double pn[4];
 #pragma unroll
   for (int u = 0; u < 4; ++u) pn[u] = tid < 256 && tid + 256 * u < a.G ? a.partn[tid + 256 * u] : 0.0;
   int bad = 0;
-  if (tid < 256) s_n[tid] = ((pn[0] + pn[1]) + pn[2]) + pn[3];
+  if (tid < 256) {
+    double t = ((pn[0] + pn[1]) + pn[2]) + pn[3];
+    for (int g = tid + 1024; g < a.G; g += 256) t += a.partn[g];
+    s_n[tid] = t;
+  }
   if (tid < j) {
     const double hi = a.h[tid];
     bad = !isfinite(hi);
@@ -879,6 +929,72 @@ __device__ inline void finalize_next_body(const SmallArgs &a) {
     const double b = ((s_p[wave][lane] + s_p[wave + 1][lane]) + s_p[wave + 2][lane]) + s_p[wave + 3][lane];
     a.bvec[i] = b;
     a.coefA[i] = (i < j ? sgi : 1.0 / hn) * b;
+  }
+  if constexpr (JMAX > 255) {  // rows 256 and up
+    for (int r0 = 256; r0 < J; r0 += 256) {
+      __syncthreads();
+      const int i2 = r0 + i, lo2 = i2 - 1, len2 = i2 < J ? j - lo2 : 0;
+      const int b0 = lo2 + (len2 * sl) / 4, b1 = lo2 + (len2 * (sl + 1)) / 4;
+      double t = 0.0;
+      int m = b0;
+      for (; m + U <= b1 && m + U < j; m += U) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = a.H[(size_t)(m + u) * a.ldH + i2];
+#pragma unroll
+        for (int u = 0; u < U; ++u) t = fma(v[u], s_b[m + u], t);
+      }
+      for (; m < b1; ++m)
+        t = fma(m < j - 1 ? a.H[(size_t)m * a.ldH + i2] : (i2 < j ? s_h[i2] : hn), s_b[m], t);
+      s_p[wave][lane] = t;
+      __syncthreads();
+      if (sl == 0 && i2 < J) {
+        const double b = ((s_p[wave][lane] + s_p[wave + 1][lane]) + s_p[wave + 2][lane]) + s_p[wave + 3][lane];
+        a.bvec[i2] = b;
+        a.coefA[i2] = (i2 < j ? a.sigma[i2] : 1.0 / hn) * b;
+      }
+    }
+  }
+}
+
+// finalize_init_body and nextb_body (whose sums are empty) in one workgroup of at
+// least 256 threads.
+__device__ inline void finalize_init_next_body(const SmallArgs &a) {
+  __shared__ double s_n[256];
+  DevState *st = a.st;
+  const int tid = threadIdx.x;
+  if (st->status != ST_ACTIVE) {
+    if (tid == 0) st->pushes += 1;
+    return;
+  }
+  if (tid < 256) {
+    double t = 0.0;
+    for (int g = tid; g < a.G; g += 256) t += a.partn[g];
+    s_n[tid] = t;
+  }
+  __syncthreads();
+  const int lane = tid & 63;
+  double x2 = (s_n[lane] + s_n[lane + 128]) + (s_n[lane + 64] + s_n[lane + 192]);
+  x2 = xor_sum<16>(xor_sum<32>(x2));
+  x2 += dpp_mov<0x128>(x2);
+  x2 += dpp_mov<0x124>(x2);
+  x2 += dpp_mov<0x122>(x2);
+  x2 += dpp_mov<0x121>(x2);
+  if (tid == 0) {
+    const double b11 = sqrt(x2);
+    if (!isfinite(b11)) {
+      st->status = ST_NONFINITE;
+    } else if (b11 == 0.0) {
+      st->status = ST_ZERO;
+    } else {
+      a.beta[0] = b11;
+      a.sigma[0] = 1.0 / b11;
+      a.bvec[0] = 0.0;
+      a.coefA[0] = 0.0;
+      st->xfro2 = x2;
+      st->scaleA = 1.0 / b11;
+      st->q = 1;
+    }
+    st->pushes += 1;
   }
 }
 

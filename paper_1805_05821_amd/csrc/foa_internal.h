@@ -135,14 +135,12 @@ constexpr int kStreamSlots = 1024;
 struct BatchArgs {
   const BatchStream *streams;
   const void *const *xptrs;  // device array of S snapshot pointers (NULL: idle)
-  const int *rblk_stream;    // reduce blocks: stream of block b
-  const int *rblk_c0;        // reduce blocks: first column of block b
   int *list;                 // NBUCKET x S
   int64_t *pre;              // NBUCKET x (S + 1)
   int *first;                // NBUCKET x kMaxBatchGrid
   int *meta;                 // NBUCKET x 2: streams in the bucket, workgroups in use
-  int *spos;                 // S: bucket (high 8 bits) and list position of each active stream
-  int S, n_rblocks, max_nmax;
+  int *spos;                 // S: bucket (high 8 bits) and list position of each active stream (S > 1024)
+  int S, max_nmax;
   int ls_mode;               // 0: three-sweep form; one-reduction form: 1 push step, 2 flush step
   int cols_per_qw;           // basis columns per unit of tile width
   int gridb[NBUCKET];        // workgroups of the row-pass launches of bucket k
@@ -330,7 +328,7 @@ hipError_t launch_ls_finalize(const LsSmall &a, hipStream_t s);
 bool ls_batch_supported(bool tv_f64, int k);
 int ls_batch_occupancy(bool tv_f64, int k);
 hipError_t launch_ls_batch_pass(bool tv_f64, bool tx_f64, int k, int grid, const BatchArgs &b, hipStream_t s);
-hipError_t launch_ls_batch_small(const BatchArgs &b, hipStream_t s);
+hipError_t launch_ls_batch_small(const BatchArgs &b, int cols, hipStream_t s);
 
 // batched form (one call per kernel of a step; all captured in one graph)
 hipError_t launch_batch_plan(const BatchArgs &b, hipStream_t s);
@@ -343,9 +341,8 @@ hipError_t launch_xcc_probe(unsigned *mask, int blocks, hipStream_t s);
 // row pass of bucket k (0: the first push of a stream, PM_INIT)
 hipError_t launch_batch_pass(int mode, bool tv_f64, bool tx_f64, int k, int grid, const BatchArgs &b,
                              hipStream_t s);
-hipError_t launch_batch_reduce(int mode, const BatchArgs &b, hipStream_t s);
+hipError_t launch_batch_reduce(int mode, int cols, const BatchArgs &b, hipStream_t s);
 hipError_t launch_batch_finalize(const BatchArgs &b, hipStream_t s);
-hipError_t launch_batch_nextb(const BatchArgs &b, hipStream_t s);
 hipError_t launch_batch_init_states(const BatchArgs &b, double tol, hipStream_t s);
 // fills out[0..n) with a deterministic pseudo-random sequence of tuning input k
 hipError_t launch_fill_random(float *out, int64_t n, uint32_t k, hipStream_t s);

@@ -51,7 +51,10 @@ __global__ __launch_bounds__(256) void k_reduce(SmallArgs a) {
 
 __global__ __launch_bounds__(256) void k_finalize(SmallArgs a) { finalize_body(a); }
 __global__ __launch_bounds__(256) void k_finalize_init(SmallArgs a) { finalize_init_body(a); }
-__global__ __launch_bounds__(1024) void k_finalize_next(SmallArgs a) { finalize_next_body(a); }
+__global__ __launch_bounds__(1024) void k_finalize_next(SmallArgs a) {
+  static_assert(kStreamSlots <= 4 * 256, "slots of a pass: one round of loads");
+  finalize_next_body<kFinNextCols>(a);
+}
 __global__ __launch_bounds__(256) void k_nextb(SmallArgs a) { nextb_body(a, blockIdx.x); }
 
 __global__ __launch_bounds__(256) void k_init_state(SmallArgs a, double tol) { init_state_body(a, tol); }

@@ -338,32 +338,29 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ls_wave
 // Reduction: one wavefront per value (part0 columns, part1 columns, scalars),
 // lane-strided sums over the slots, then a butterfly: a fixed association.
 // ---------------------------------------------------------------------------
+// Where value v's partial sums lie (null: nothing to sum), and its place in red.
+__device__ __forceinline__ const double *ls_reduce_src(const LsSmall &a, int v, int q, int *out) {
+  if (v < a.nt) {
+    *out = v;
+    return v < q ? a.part0 + (size_t)v * a.ldg : nullptr;
+  }
+  if (v < 2 * a.nt) {
+    *out = a.n_max + (v - a.nt);
+    return v - a.nt < q ? a.part1 + (size_t)(v - a.nt) * a.ldg : nullptr;
+  }
+  const int sc = v - 2 * a.nt;
+  *out = 2 * a.n_max + sc;
+  if (sc < LS_NSC) return a.part1 + (size_t)(a.n_max + sc) * a.ldg;
+  const int c = sc - LS_NSC;
+  return a.gram && c < q && a.st->ls_u ? a.part2 + (size_t)c * a.ldg : nullptr;
+}
+
 // one wavefront per value; vblock selects four consecutive values
 __device__ inline void ls_reduce_body(const LsSmall &a, int vblock) {
   const int lane = threadIdx.x & 63;
-  const int v = vblock * 4 + (threadIdx.x >> 6);
-  const int q = a.st->q;
-  const double *src;
   int out;
-  if (v < a.nt) {
-    if (v >= q) return;
-    src = a.part0 + (size_t)v * a.ldg;
-    out = v;
-  } else if (v < 2 * a.nt) {
-    if (v - a.nt >= q) return;
-    src = a.part1 + (size_t)(v - a.nt) * a.ldg;
-    out = a.n_max + (v - a.nt);
-  } else if (v < 2 * a.nt + LS_NSC) {
-    src = a.part1 + (size_t)(a.n_max + v - 2 * a.nt) * a.ldg;
-    out = 2 * a.n_max + (v - 2 * a.nt);
-  } else if (a.gram && v < 3 * a.nt + LS_NSC) {
-    const int c = v - 2 * a.nt - LS_NSC;
-    if (c >= q || !a.st->ls_u) return;
-    src = a.part2 + (size_t)c * a.ldg;
-    out = 2 * a.n_max + LS_NSC + c;
-  } else {
-    return;
-  }
+  const double *src = ls_reduce_src(a, vblock * 4 + (threadIdx.x >> 6), a.st->q, &out);
+  if (!src) return;
   const double t = strided_sum<false>(src, a.G, lane);
   if (lane == 0) a.red[out] = t;
 }
@@ -396,9 +393,9 @@ __device__ inline void ls_block_sums(double (&v)[N], double *sh) {
   __syncthreads();
 }
 
-// Two products for the coming finalize, both 64 rows x 4 contiguous l-slices per
-// 256 threads of slice `part` of `parts` of the l range, slices summed in order,
-// one value per row to out[i] (i < c):
+// Two products for the coming finalize, both 64 rows x a contiguous l-slice per
+// wavefront (NT / 64 of them) of slice `part` of `parts` of the l range, slices
+// summed in order, one value per row to out[i] (i < c):
 //  * KIND 0: the part of H_bar's column c-1 that the earlier columns give, for the
 //    column c = q that the finalize finishes (eq. betacolumnupdate),
 //    sum_{l = max(0, i-1)}^{c-2} H_bar[i, l] beta[l, c-1];
@@ -406,11 +403,12 @@ __device__ inline void ls_block_sums(double (&v)[N], double *sh) {
 //    the finalize makes pending (w_l = sigma_l * its reduced sum l, l < q), E
 //    symmetric with a zero diagonal; the terms of the column finished in the same
 //    sweep are added by the finalize.
-template <int KIND>
+template <int KIND, int NT>
 __device__ inline void ls_product_body(const LsSmall &a, int rblock, int part, int parts, double *out) {
-  __shared__ double sh[4][64];
+  constexpr int NS = NT / 64;
+  __shared__ double sh[NS][64];
   const int c = a.st->q;
-  const int r = threadIdx.x & 63, sl = part * 4 + (threadIdx.x >> 6), S = 4 * parts;
+  const int r = threadIdx.x & 63, sl = part * NS + (threadIdx.x >> 6), S = NS * parts;
   const int i = rblock * 64 + r;
   double t = 0.0;
   if (i < c) {
@@ -432,7 +430,12 @@ __device__ inline void ls_product_body(const LsSmall &a, int rblock, int part, i
   }
   sh[threadIdx.x >> 6][r] = t;
   __syncthreads();
-  if (threadIdx.x < 64 && i < c) out[i] = ((sh[0][r] + sh[1][r]) + sh[2][r]) + sh[3][r];
+  if (threadIdx.x < 64 && i < c) {
+    double o = sh[0][r];
+#pragma unroll
+    for (int k = 1; k < NS; ++k) o += sh[k][r];
+    out[i] = o;
+  }
 }
 
 // One stream: the l range of either product is cut into a.hs workgroups as well
@@ -442,9 +445,9 @@ __global__ __launch_bounds__(256) void k_ls_hprod(LsSmall a) {
   if (!ls_runs(a.st, a.flush)) return;
   double *out = a.hp + (size_t)(blockIdx.z * a.hs + blockIdx.y) * (a.n_max + 1);
   if (blockIdx.z == 0) {
-    if (a.st->ls_u) ls_product_body<0>(a, blockIdx.x, blockIdx.y, a.hs, out);
+    if (a.st->ls_u) ls_product_body<0, 256>(a, blockIdx.x, blockIdx.y, a.hs, out);
   } else if (a.st->ls_x) {
-    ls_product_body<1>(a, blockIdx.x, blockIdx.y, a.hs, out);
+    ls_product_body<1, 256>(a, blockIdx.x, blockIdx.y, a.hs, out);
   }
 }
 
@@ -812,21 +815,38 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ls_wave
   }
 }
 
+// Four values a wavefront, their loads in flight together: a stream has few partial
+// sums per value, and a value per wavefront made the launch 14 000 workgroups (64
+// streams of 20..300 columns: 8.2 us, 5.5 us so).
 __global__ __launch_bounds__(256) void k_ls_reduce_batch(BatchArgs b) {
   const BatchStream &d = b.streams[blockIdx.y];
   if (!d.st->act) return;
   const LsSmall a = ls_small_of(d, b.ls_mode == 2);
-  if ((int)blockIdx.x * 4 >= (a.gram ? 3 : 2) * a.nt + LS_NSC) return;
-  ls_reduce_body(a, blockIdx.x);
+  const int v0 = blockIdx.x * 16 + 4 * __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  if (v0 >= (a.gram ? 3 : 2) * a.nt + LS_NSC) return;
+  const int lane = threadIdx.x & 63, q = a.st->q;
+  const double *p[4];
+  int out[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) p[k] = ls_reduce_src(a, v0 + k, q, &out[k]);
+  double t[4];
+  strided_sum4(p, a.G, lane, t);
+#pragma unroll
+  for (int k = 0; k < 4; ++k)
+    if (lane == k && p[k]) a.red[out[k]] = t[k];
 }
 
-__global__ __launch_bounds__(256) void k_ls_hprod_batch(BatchArgs b) {
+// A workgroup of 16 l-slices per 64 rows and product (64 streams of 20..300 columns:
+// 4 slices and both products in a workgroup 12.5 us, 7.8 us so).
+__global__ __launch_bounds__(1024) void k_ls_hprod_batch(BatchArgs b) {
   const BatchStream &d = b.streams[blockIdx.y];
   const LsSmall a = ls_small_of(d, b.ls_mode == 2);
-  if (!d.st->act || !(d.st->ls_u || (a.gram && d.st->ls_x))) return;
-  if ((int)blockIdx.x * 64 >= d.st->q && blockIdx.x > 0) return;
-  if (d.st->ls_u) ls_product_body<0>(a, blockIdx.x, 0, 1, a.bvec);
-  if (a.gram && d.st->ls_x) ls_product_body<1>(a, blockIdx.x, 0, 1, a.what);
+  if (!d.st->act || ((int)blockIdx.x * 64 >= d.st->q && blockIdx.x > 0)) return;
+  if (blockIdx.z == 0) {
+    if (d.st->ls_u) ls_product_body<0, 1024>(a, blockIdx.x, 0, 1, a.bvec);
+  } else if (a.gram && d.st->ls_x) {
+    ls_product_body<1, 1024>(a, blockIdx.x, 0, 1, a.what);
+  }
 }
 
 __global__ __launch_bounds__(512) void k_ls_finalize_batch(BatchArgs b) {
@@ -847,9 +867,9 @@ __global__ __launch_bounds__(512) void k_ls_finalize_batch(BatchArgs b) {
 }
 
 // Kernel shape of bucket k (basis sizes up to 32, 64, 128, 256, 512 final
-// columns; k = 0 for an empty basis takes the shape of k = 1): 1, 2, 4, 8, 8
+// columns; an empty basis is in bucket 1): 1, 2, 4, 8, 8
 // wavefronts with 8, 8, 8, 8, 16 groups (an FP64 basis at most 256 columns).
-bool ls_batch_supported(bool tv_f64, int k) { return !tv_f64 || k <= 4; }
+bool ls_batch_supported(bool tv_f64, int k) { return k >= 1 && (!tv_f64 || k <= 4); }
 
 template <typename TV, typename TX, int BK>
 static const void *ls_batch_fn(int *nt) {
@@ -862,7 +882,6 @@ static const void *ls_batch_fn(int *nt) {
 template <typename TV, typename TX>
 static const void *ls_batch_fn_k(int k, int *nt) {
   switch (k) {
-    case 0: return ls_batch_fn<TV, TX, 0>(nt);
     case 1: return ls_batch_fn<TV, TX, 1>(nt);
     case 2: return ls_batch_fn<TV, TX, 2>(nt);
     case 3: return ls_batch_fn<TV, TX, 3>(nt);
@@ -893,12 +912,12 @@ hipError_t launch_ls_batch_pass(bool tv_f64, bool tx_f64, int k, int grid, const
   return hipLaunchKernel(f, dim3(grid), dim3(nt), args, 0, s);
 }
 
-hipError_t launch_ls_batch_small(const BatchArgs &b, hipStream_t s) {
-  const int vblocks = (3 * b.max_nmax + LS_NSC + 3) / 4;
+hipError_t launch_ls_batch_small(const BatchArgs &b, int cols, hipStream_t s) {
+  const int vblocks = (3 * cols + LS_NSC + 15) / 16;
   hipLaunchKernelGGL(k_ls_reduce_batch, dim3(vblocks, b.S), dim3(256), 0, s, b);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_ls_hprod_batch, dim3((b.max_nmax + 63) / 64, b.S), dim3(256), 0, s, b);
+  hipLaunchKernelGGL(k_ls_hprod_batch, dim3(std::max((cols + 63) / 64, 1), b.S, 2), dim3(1024), 0, s, b);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   hipLaunchKernelGGL(k_ls_finalize_batch, dim3(b.S), dim3(512), 0, s, b);
   return hipGetLastError();

@@ -367,3 +367,43 @@ def test_batch_persistent_wait_bound_reports_error(tmp_path, monkeypatch):
     bt, q, st = _run_batch(Xs, "f32", tune=table)
     assert list(q) == [X.shape[1] for X in Xs] and not any(st)
     bt.close()
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+def test_batch_small_kernel_edges(prec):
+    """Bases around the rows and columns at which the batch's reduction (16
+    columns a workgroup) and finalize (256 rows a round) split: Gaussian
+    snapshots (kappa_2 < 20) against the oracle; a first push beside streams
+    that are further on."""
+    Xs = [np.random.default_rng(N).standard_normal((n, N))
+          for n, N in ((64, 1), (65, 2), (300, 16), (301, 17), (1500, 256), (1501, 257), (1400, 258), (1600, 512))]
+    bt, q, st = _run_batch(Xs, prec)
+    for s, X in enumerate(Xs):
+        ref = oracle.foa_batch(X)
+        H, B, qq, m, V = _view_state(bt, s)
+        assert qq == q[s] == ref.q
+        eps = EPS64 if prec == "f64" else EPS32
+        kap = kappa_of(ref.beta[:m, :m]) if m else 1.0
+        eH = np.linalg.norm(H[:m, :m] - ref.H[:m, :m], 2) / np.linalg.norm(ref.H[:m, :m], 2) if m else 0.0
+        orth = np.linalg.norm(np.eye(qq) - V.T @ V, 2)
+        announce(f"stream {s}: q={qq} kappa={kap:.1e} relH2={eH:.1e} orth={orth:.1e}")
+        assert eH <= 10 * eps * kap and orth <= 10 * np.sqrt(qq) * eps
+    bt.close()
+
+
+def test_batch_more_streams_than_the_plan_takes_at_once():
+    """1100 streams: the plan takes them in two rounds (1024, then 76)."""
+    r = np.random.default_rng(5)
+    Xs = [r.standard_normal((70 + s % 90, 2 + s % 4)) for s in range(1100)]
+    bt, q, st = _run_batch(Xs, "f64")
+    for s in (0, 1, 500, 1023, 1024, 1025, 1098, 1099):
+        ref = oracle.foa_batch(Xs[s])
+        H, B, qq, m, V = _view_state(bt, s)
+        assert qq == q[s] == ref.q
+        kap = kappa_of(ref.beta[:m, :m])
+        eH = np.abs(H[:qq, :m] - ref.H[:qq, :m]).max() / np.abs(ref.H[:qq, :m]).max()
+        eV = np.abs(V - ref.V[:, :qq]).max()
+        announce(f"stream {s}: q={qq} relH={eH:.1e} V={eV:.1e}")
+        assert max(eH, eV) <= 100 * EPS64 * kap * qq
+    assert (q == np.array([X.shape[1] for X in Xs])).all()
+    bt.close()

@@ -317,3 +317,30 @@ def test_f32_noise_floor_gram_correction(n, N):
     announce(f"  batched: q={qb[0]} status={sb[0]} ||I-V^TV||={orth_b:.2e}")
     assert qb[0] == N and sb[0] == 0 and orth_b <= b
     bt.close()
+
+
+@pytest.mark.parametrize("prec,n,N", [
+    ("f64", 33, 20),      # the last unit (32 rows of an FP64 basis) holds one row
+    ("f64", 97, 60),
+    ("f64", 1100, 257),   # every width of an FP64 basis
+    ("f32", 65, 40),
+    ("f32", 127, 60),
+    ("f32", 1500, 512),   # 4 wavefronts up to 256 columns, 8 beyond, the widest full
+])
+def test_sweep_tiles(prec, n, N):
+    """Every tile width of the sweep and ragged last units: Gaussian snapshots
+    (kappa_2 < 20) against the sequential oracle."""
+    X = np.random.default_rng(n + N).standard_normal((n, N)).astype(np.float32).astype(np.float64)
+    g = run_gpu(X, prec, tol=0.0, form="one_reduction")
+    st = oracle.foa_batch(X, tol=0.0)
+    q, m = g["q"], g["m"]
+    assert q == st.q == N
+    eps = EPS64 if prec == "f64" else EPS32
+    kap = kappa_of(st.beta[:m, :m])
+    eH = np.linalg.norm(g["H"][:m, :m] - st.H[:m, :m], 2) / np.linalg.norm(st.H[:m, :m], 2)
+    orth = np.linalg.norm(np.eye(q) - g["V"].T @ g["V"], 2)
+    announce(f"{prec} {n} x {N}: kappa={kap:.1e} relH2={eH:.1e} orth={orth:.1e}")
+    # one reduction: the second projection is applied a push later, orthogonality
+    # is eps kappa at worst for these data
+    assert eH <= 10 * eps * kap * np.sqrt(q) and orth <= 10 * np.sqrt(q) * eps * kap
+    g["stream"].close()

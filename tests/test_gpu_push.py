@@ -371,3 +371,30 @@ def test_small_stream_runs(prec, n, N, stop):
             assert o[:3] == out[2][:3]
             for a, b in zip(o[3:], out[2][3:]):
                 assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("prec", ["f32", "f64"])
+def test_basis_copies_at_any_alignment(prec):
+    """Rows copied 16 bytes of the basis at a time where r0, ld and the address
+    allow it and one by one elsewhere: bitwise the same values, and nothing
+    written outside the rows asked for."""
+    import torch
+
+    from paper_1805_05821_amd import foa as F
+
+    n, N = 333, 23
+    g = run_gpu(np.random.default_rng(1).standard_normal((n, N)), prec, tol=0.0)
+    ctx = g["stream"].ctx
+    for dt, code in ((torch.float32, F.FOA_F32), (torch.float64, F.FOA_F64)):
+        for ncols in (1, 4, 5, 16, 17, N):
+            full = g["stream"].basis(ncols, dtype=dt)
+            assert np.array_equal(full.cpu().numpy(), g["V"].T[:ncols].astype(full.cpu().numpy().dtype))
+            for r0, nr, ld, off in ((0, n, n + 3, 0), (0, 64, 64, 4), (4, 320, 320, 0), (1, 300, 300, 0), (64, 269, 272, 1),
+                                    (2, 130, 130, 2), (n - 1, 1, 4, 0)):
+                buf = torch.full((off + ncols * ld + 8,), 7.0, dtype=dt, device="cuda")
+                F.foa_copy_basis_rows(ctx, r0, nr, buf[off:], ld, code, ncols)
+                torch.cuda.synchronize()
+                want = torch.full_like(buf, 7.0)
+                want[off:off + ncols * ld].view(ncols, ld)[:, :nr] = full[:, r0:r0 + nr]
+                assert torch.equal(buf, want), (dt, ncols, r0, nr, ld, off)
+    g["stream"].close()
