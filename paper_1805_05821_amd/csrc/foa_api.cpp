@@ -168,13 +168,14 @@ hipEvent_t take_event(foa_ctx_s *c) {
 // kernel between: by the number of sums a lane then adds up (columns in chunks
 // of 64 lanes, the other wavefronts split the rows).  Measured, us per push
 // fused / with reduce kernels: FP32, 4 wavefronts, 4133 x 64 (17 sums) 19.4 /
-// 21.8, 16384 x 100 (up to 128, fused to 32) 23.3 / 23.4; FP64, 16 wavefronts,
-// 4096 x 64 (4) 20.9 / 22.4, 16384 x 100 (32) 25.8 / 24.9, to 16 24.5 / 24.9.
+// 21.8, 16384 x 100 (up to 128, fused to 32) 23.3 / 23.4; FP64, 4 and 8 wavefronts,
+// 4096 x 64 (16) 18.6 / 20.6, 8192 x 128 (32) 21.4 / 22.7, 16384 x 128 (64) 26.7 /
+// 24.5.
 static bool pass_reduces(int nw, int G, int j) {
   const int R = (j + 63) / 64;
   if (R > nw) return false;
   const int S = nw / R;
-  return (G + S - 1) / S <= (nw == 4 ? 32 : 16);
+  return (G + S - 1) / S <= (nw == 16 ? 16 : 32);
 }
 
 // Launch one row pass, bracketed by timing events when profiling is on.

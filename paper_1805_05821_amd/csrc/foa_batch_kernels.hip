@@ -309,19 +309,21 @@ int batch_cols_per_qw(bool tv_f64) { return tv_f64 ? 16 * 2 : 8 * 4; }
 // wavefronts with 8 groups for k = 3, then 8 wavefronts with 8 and 16 groups
 // (16 wavefronts of 8 groups, the single push's choice above 320 columns,
 // measured 0.5-1.5% slower here over the whole run);
-// FP64 basis: 16 wavefronts with 1 .. 16 groups, 16 groups without prefetch.
+// FP64 basis: 4 wavefronts with 4 and 8 groups, 8 with 8 and 16, 16 with 16 (without
+// prefetch), as pass_nw has them.
 // Up to 32 columns a panel carries too little data to pay for the
 // cross-wavefront reduction and barriers of a wider workgroup: one-wavefront
 // workgroups (16 per CU) keep many more panels in flight (single-stream
 // passes at 4, 8, 16 and 32 columns: 1.85, 1.49, 1.24 and 1.08 times the
 // rate of 4-wavefront workgroups); at 33-64 columns 2-wavefront workgroups of
 // 8 groups took the batched run's steps there from 55.4 to 51.6 ms.
+constexpr int batch_nw64(int k) { return k <= 2 ? 4 : (k <= 4 ? 8 : 16); }
+
 template <typename TV, typename TX, int MODE, int BK>
 static hipError_t launch_bucket(int grid, const BatchArgs &b, hipStream_t s) {
   if constexpr (sizeof(TV) == 8) {
-    constexpr int QW = 1 << (BK - 1);
-    constexpr bool PREF = QW < 16;
-    hipLaunchKernelGGL((k_pass_batch<TV, TX, 16, QW, MODE, PREF, BK>), dim3(grid), dim3(16 * 64), 0, s, b);
+    constexpr int NW = batch_nw64(BK), QW = (32 << (BK - 1)) / (2 * NW);
+    hipLaunchKernelGGL((k_pass_batch<TV, TX, NW, QW, MODE, (NW < 16), BK>), dim3(grid), dim3(NW * 64), 0, s, b);
   } else if constexpr (BK == 1) {
     hipLaunchKernelGGL((k_pass_batch<TV, TX, 1, 8, MODE, true, BK>), dim3(grid), dim3(64), 0, s, b);
   } else if constexpr (BK == 2) {
@@ -350,7 +352,7 @@ static hipError_t launch_bucket_k(int k, int grid, const BatchArgs &b, hipStream
 
 template <typename TV, typename TX>
 static hipError_t launch_batch_t(int mode, int k, int grid, const BatchArgs &b, hipStream_t s) {
-  constexpr int NWI = sizeof(TV) == 8 ? 16 : 8;
+  constexpr int NWI = sizeof(TV) == 8 ? 4 : 8;
   switch (mode) {
     case PM_INIT:
       hipLaunchKernelGGL((k_pass_batch<TV, TX, NWI, 1, PM_INIT, false, 0>), dim3(grid), dim3(NWI * 64), 0, s, b);
@@ -741,8 +743,8 @@ static int occ_of(F f, int threads) {
 template <typename TV, int BK>
 static int occ_bucket() {
   if constexpr (sizeof(TV) == 8) {
-    constexpr int QW = 1 << (BK - 1);
-    return occ_of(&k_pass_batch<TV, float, 16, QW, PM_A, (QW < 16), BK>, 16 * 64);
+    constexpr int NW = batch_nw64(BK), QW = (32 << (BK - 1)) / (2 * NW);
+    return occ_of(&k_pass_batch<TV, float, NW, QW, PM_A, (NW < 16), BK>, NW * 64);
   } else if constexpr (BK == 1) {
     return occ_of(&k_pass_batch<TV, float, 1, 8, PM_A, true, BK>, 64);
   } else if constexpr (BK == 2) {
@@ -756,7 +758,7 @@ static int occ_bucket() {
 
 template <typename TV>
 static int occ_batch_k(int k) {
-  constexpr int NWI = sizeof(TV) == 8 ? 16 : 8;
+  constexpr int NWI = sizeof(TV) == 8 ? 4 : 8;
   switch (k) {
     case 0: return occ_of(&k_pass_batch<TV, float, NWI, 1, PM_INIT, false, 0>, NWI * 64);
     case 1: return occ_bucket<TV, 1>();

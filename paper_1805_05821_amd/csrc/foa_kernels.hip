@@ -126,37 +126,38 @@ int tile_slot(int qw) {
 int pass_qw(bool tv_f64, int nw, int j) {
   if (!tv_f64 && ((nw == 8 && j > 128 && j <= 192) || (nw == 16 && j > 320 && j <= 384))) return 6;
   if (!tv_f64 && nw == 8 && j > 256 && j <= 320) return 12;
-  return pick_qw(j > 0 ? j : 1, tv_f64 ? 32 : nw * 4);
+  return pick_qw(j > 0 ? j : 1, nw * (tv_f64 ? 2 : 4));
+}
+
+// Tile widths QW that a workgroup of NW wavefronts is launched with: an FP64 basis
+// takes each workgroup over its own range of basis sizes (pass_nw), an FP32 basis
+// may be asked for any (option nw).
+template <typename TV, int NW, int QW>
+constexpr bool pass_shape() {
+  if (sizeof(TV) == 8) return NW == 4 ? QW <= 8 && QW != 6 : (NW == 8 ? QW == 8 || QW == 16 : QW == 16);
+  return QW == 6 ? NW >= 8 : (QW == 12 ? NW == 8 : NW * QW * 4 <= 512);
+}
+
+template <typename TV, typename TX, int NW, int QW, int MODE, bool PREF, bool RED>
+static hipError_t launch_pass_s(int grid, const PassArgs &a, hipStream_t s) {
+  if constexpr (MODE == PM_INIT || pass_shape<TV, NW, QW>()) {
+    hipLaunchKernelGGL((k_pass<TV, TX, NW, QW, MODE, PREF, RED>), dim3(grid), dim3(NW * 64), 0, s, a);
+    return hipGetLastError();
+  }
+  return hipErrorInvalidValue;
 }
 
 template <typename TV, typename TX, int NW, int MODE, bool PREF, bool RED>
 static hipError_t launch_pass_q(int qw, int grid, const PassArgs &a, hipStream_t s) {
-  constexpr int NT = NW * 64;
   switch (qw) {
-    case 1: hipLaunchKernelGGL((k_pass<TV, TX, NW, 1, MODE, PREF, RED>), dim3(grid), dim3(NT), 0, s, a); break;
-    case 2: hipLaunchKernelGGL((k_pass<TV, TX, NW, 2, MODE, PREF, RED>), dim3(grid), dim3(NT), 0, s, a); break;
-    case 4: hipLaunchKernelGGL((k_pass<TV, TX, NW, 4, MODE, PREF, RED>), dim3(grid), dim3(NT), 0, s, a); break;
-    case 8: hipLaunchKernelGGL((k_pass<TV, TX, NW, 8, MODE, PREF, RED>), dim3(grid), dim3(NT), 0, s, a); break;
-    case 6:
-      if constexpr (sizeof(TV) == 4 && NW >= 8) {
-        hipLaunchKernelGGL((k_pass<TV, TX, NW, 6, MODE, PREF, RED>), dim3(grid), dim3(NT), 0, s, a);
-        break;
-      }
-      return hipErrorInvalidValue;
-    case 12:
-      if constexpr (sizeof(TV) == 4 && NW == 8) {
-        hipLaunchKernelGGL((k_pass<TV, TX, NW, 12, MODE, PREF, RED>), dim3(grid), dim3(NT), 0, s, a);
-        break;
-      }
-      return hipErrorInvalidValue;
-    default:
-      if constexpr (NW * 16 * Vec<TV>::EPL <= 512)
-        hipLaunchKernelGGL((k_pass<TV, TX, NW, 16, MODE, PREF, RED>), dim3(grid), dim3(NT), 0, s, a);
-      else
-        return hipErrorInvalidValue;
-      break;
+    case 1: return launch_pass_s<TV, TX, NW, 1, MODE, PREF, RED>(grid, a, s);
+    case 2: return launch_pass_s<TV, TX, NW, 2, MODE, PREF, RED>(grid, a, s);
+    case 4: return launch_pass_s<TV, TX, NW, 4, MODE, PREF, RED>(grid, a, s);
+    case 6: return launch_pass_s<TV, TX, NW, 6, MODE, PREF, RED>(grid, a, s);
+    case 8: return launch_pass_s<TV, TX, NW, 8, MODE, PREF, RED>(grid, a, s);
+    case 12: return launch_pass_s<TV, TX, NW, 12, MODE, PREF, RED>(grid, a, s);
+    default: return launch_pass_s<TV, TX, NW, 16, MODE, PREF, RED>(grid, a, s);
   }
-  return hipGetLastError();
 }
 
 // Register budget: a 16-group FP64 tile (64 VGPRs) cannot be double buffered
@@ -180,42 +181,48 @@ static hipError_t launch_pass_m(int mode, bool pref, int grid, const PassArgs &a
                 : launch_pass_q<TV, TX, NW, M, false, false>(qw, grid, a, s);
   };
   switch (mode) {
-    case PM_INIT: return launch_pass_q<TV, TX, NW, PM_INIT, false, false>(1, grid, a, s);
+    case PM_INIT: return launch_pass_s<TV, TX, NW, 1, PM_INIT, false, false>(grid, a, s);
     case PM_A: return go(std::integral_constant<int, PM_A>{});
     case PM_B: return go(std::integral_constant<int, PM_B>{});
     default: return go(std::integral_constant<int, PM_C>{});
   }
 }
 
-// Wavefronts per row-pass workgroup.  An FP64 basis always uses 16.  For an
-// FP32 basis nw_opt (4, 8 or 16) if set, else 4 up to 128 columns, 8 up to
-// 320 and 16 beyond: at small basis sizes a panel carries little data and
-// the pass is bound by the per-panel barrier and LDS round trips, which
-// smaller, independent workgroups overlap better; above 320 columns 16
-// wavefronts of 8 groups (128 VGPRs, 4 wavefronts per SIMD) beat 8 of 16
-// groups (one workgroup of 8 per CU).  Between 257 and 320 columns the
+// Wavefronts per row-pass workgroup: an FP64 basis 4 up to 64 columns, 8 up to 256
+// and 16 beyond; an FP32 basis nw_opt (4, 8 or 16) if set, else 4 up to 128
+// columns, 8 up to 320 and 16 beyond.  At small basis sizes a panel carries little
+// data and the pass is bound by the per-panel barriers and LDS round trips, which
+// smaller, independent workgroups overlap better.  FP64, us per push, 16
+// wavefronts at every size / so: 2^20 x 32 163 / 98, 2^20 x 64 200 / 162, 2^18 x
+// 64 62 / 50, 100037 x 200 66 / 60, 4096 x 64 20.5 / 18.9, 2^20 x 256 538 / 521
+// (with 4 up to 128 columns 2^20 x 128 takes 293 instead of 288).  FP32 above 320
+// columns: 16 wavefronts of 8 groups (128 VGPRs, 4 wavefronts per SIMD) beat 8 of
+// 16 groups (one workgroup of 8 per CU).  Between 257 and 320 columns the
 // 8-group tile is half empty and the n = 1e8 run was 2.5% slower with it.
 int pass_nw(bool tv_f64, int nw_opt, int j) {
-  if (tv_f64) return 16;
+  if (tv_f64) return j <= 64 ? 4 : (j <= 256 ? 8 : 16);
   if (nw_opt == 4 && j > 256) return 8;  // 4 wavefronts cover at most 256 columns
   if (nw_opt > 0) return nw_opt;
   return j <= 128 ? 4 : (j <= 320 ? 8 : 16);
 }
 
+template <typename TV>
+static hipError_t launch_pass_v(int mode, bool tx_f64, bool prefetch, int nw, int grid, const PassArgs &a,
+                                hipStream_t s) {
+  if (nw == 4)
+    return tx_f64 ? launch_pass_m<TV, double, 4>(mode, prefetch, grid, a, s)
+                  : launch_pass_m<TV, float, 4>(mode, prefetch, grid, a, s);
+  if (nw == 8)
+    return tx_f64 ? launch_pass_m<TV, double, 8>(mode, prefetch, grid, a, s)
+                  : launch_pass_m<TV, float, 8>(mode, prefetch, grid, a, s);
+  return tx_f64 ? launch_pass_m<TV, double, 16>(mode, prefetch, grid, a, s)
+                : launch_pass_m<TV, float, 16>(mode, prefetch, grid, a, s);
+}
+
 hipError_t launch_pass(int mode, bool tv_f64, bool tx_f64, bool prefetch, int nw, int grid,
                        const PassArgs &a, hipStream_t s) {
-  if (tv_f64) {
-    return tx_f64 ? launch_pass_m<double, double, 16>(mode, prefetch, grid, a, s)
-                  : launch_pass_m<double, float, 16>(mode, prefetch, grid, a, s);
-  }
-  if (nw == 4)
-    return tx_f64 ? launch_pass_m<float, double, 4>(mode, prefetch, grid, a, s)
-                  : launch_pass_m<float, float, 4>(mode, prefetch, grid, a, s);
-  if (nw == 8)
-    return tx_f64 ? launch_pass_m<float, double, 8>(mode, prefetch, grid, a, s)
-                  : launch_pass_m<float, float, 8>(mode, prefetch, grid, a, s);
-  return tx_f64 ? launch_pass_m<float, double, 16>(mode, prefetch, grid, a, s)
-                : launch_pass_m<float, float, 16>(mode, prefetch, grid, a, s);
+  return tv_f64 ? launch_pass_v<double>(mode, tx_f64, prefetch, nw, grid, a, s)
+                : launch_pass_v<float>(mode, tx_f64, prefetch, nw, grid, a, s);
 }
 
 // Resident workgroups per CU of the pass-A kernel for tile width qw (the
@@ -223,9 +230,11 @@ hipError_t launch_pass(int mode, bool tv_f64, bool tx_f64, bool prefetch, int nw
 template <typename TV, typename TX, int NW, int QW>
 static int occ_q(bool pref) {
   int nb = 0;
-  const void *f = pref ? reinterpret_cast<const void *>(&k_pass<TV, TX, NW, QW, PM_A, true, false>)
-                       : reinterpret_cast<const void *>(&k_pass<TV, TX, NW, QW, PM_A, false, false>);
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, f, NW * 64, 0) != hipSuccess) return 1;
+  if constexpr (pass_shape<TV, NW, QW>()) {
+    const void *f = pref ? reinterpret_cast<const void *>(&k_pass<TV, TX, NW, QW, PM_A, true, false>)
+                         : reinterpret_cast<const void *>(&k_pass<TV, TX, NW, QW, PM_A, false, false>);
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, f, NW * 64, 0) != hipSuccess) return 1;
+  }
   return nb > 0 ? nb : 1;
 }
 
@@ -236,24 +245,22 @@ static int occ_m(int qw, bool pref) {
     case 1: return occ_q<TV, TX, NW, 1>(pref);
     case 2: return occ_q<TV, TX, NW, 2>(pref);
     case 4: return occ_q<TV, TX, NW, 4>(pref);
+    case 6: return occ_q<TV, TX, NW, 6>(pref);
     case 8: return occ_q<TV, TX, NW, 8>(pref);
-    case 6:
-      if constexpr (sizeof(TV) == 4 && NW >= 8) return occ_q<TV, TX, NW, 6>(pref);
-      return 1;
-    case 12:
-      if constexpr (sizeof(TV) == 4 && NW == 8) return occ_q<TV, TX, NW, 12>(pref);
-      return 1;
-    default:
-      if constexpr (NW * 16 * Vec<TV>::EPL <= 512) return occ_q<TV, TX, NW, 16>(pref);
-      return 1;
+    case 12: return occ_q<TV, TX, NW, 12>(pref);
+    default: return occ_q<TV, TX, NW, 16>(pref);
   }
 }
 
+template <typename TV, typename TX>
+static int occ_v(bool prefetch, int nw, int qw) {
+  if (nw == 4) return occ_m<TV, TX, 4>(qw, prefetch);
+  return nw == 8 ? occ_m<TV, TX, 8>(qw, prefetch) : occ_m<TV, TX, 16>(qw, prefetch);
+}
+
 int pass_occupancy(bool tv_f64, bool tx_f64, bool prefetch, int nw, int qw) {
-  if (tv_f64) return tx_f64 ? occ_m<double, double, 16>(qw, prefetch) : occ_m<double, float, 16>(qw, prefetch);
-  if (nw == 4) return tx_f64 ? occ_m<float, double, 4>(qw, prefetch) : occ_m<float, float, 4>(qw, prefetch);
-  if (nw == 8) return tx_f64 ? occ_m<float, double, 8>(qw, prefetch) : occ_m<float, float, 8>(qw, prefetch);
-  return tx_f64 ? occ_m<float, double, 16>(qw, prefetch) : occ_m<float, float, 16>(qw, prefetch);
+  if (tv_f64) return tx_f64 ? occ_v<double, double>(prefetch, nw, qw) : occ_v<double, float>(prefetch, nw, qw);
+  return tx_f64 ? occ_v<float, double>(prefetch, nw, qw) : occ_v<float, float>(prefetch, nw, qw);
 }
 
 hipError_t launch_reduce(int mode, const SmallArgs &a, hipStream_t s) {

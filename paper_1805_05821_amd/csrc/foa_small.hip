@@ -15,8 +15,7 @@
 // (H_bar, the coefficients) live as well, so nothing stored is read back.
 //
 // Every sum is formed in the order of the kernels this replaces (one workgroup per
-// panel there: 4 wavefronts with an FP32, 16 with an FP64 basis), so H_bar, beta
-// and the basis are bitwise theirs.
+// panel of 4 wavefronts there), so H_bar, beta and the basis are bitwise theirs.
 #include "foa_device.h"
 
 namespace foa {
@@ -72,7 +71,7 @@ template <typename TV, typename TX, int NP, int QB>
 __global__ __launch_bounds__(1024) void k_push_small(PassArgs a, SmallArgs sa, int64_t ldx, int count) {
 #pragma clang fp contract(off)  // as in row_pass_body
   constexpr int EPL = Vec<TV>::EPL, LPC = 64 / EPL, CPW = EPL, JC = QB * CPW;
-  constexpr int NWO = sizeof(TV) == 8 ? 16 : 4;  // wavefronts of a workgroup of k_pass
+  constexpr int NWO = 4;                         // wavefronts of a workgroup of k_pass at these sizes
   constexpr int LP = 16 * NP;                    // lanes of a column in the reductions
   static_assert(NP * QB <= 16 && 16 * (64 / LP) >= JC && JC <= 64, "register tile, one reduction step");
   __shared__ double s_coef[JC + 1], s_sig[JC + 1], s_bv[JC + 1], s_h[JC + 1], s_b[JC + 1];
@@ -171,7 +170,7 @@ __global__ __launch_bounds__(1024) void k_push_small(PassArgs a, SmallArgs sa, i
         us += row_scatter(u);
         // a few at a time: interleaved, the chains and coefficients of all of them
         // outgrow the 128 VGPRs
-        if (w2 % (EPL == 4 ? 2 : 4) == 1) __builtin_amdgcn_sched_barrier(0);
+        if (w2 % 2 == 1) __builtin_amdgcn_sched_barrier(0);
       }
       return w[i] - us;
     };
@@ -197,7 +196,8 @@ __global__ __launch_bounds__(1024) void k_push_small(PassArgs a, SmallArgs sa, i
       if constexpr (EPL == 4) v = xor_sum<16>(v);
       v = xor_sum<32>(v);
       v += dpp_mov<0xB1>(v);
-      if constexpr (EPL == 4) v += dpp_mov<0x4E>(v);
+      v += dpp_mov<0x4E>(v);
+      if constexpr (EPL == 2) v += dpp_mov<0x141>(v);
       constexpr int LG = LPC / NWO;  // lanes of one such sum
       const u32x2 c = __builtin_bit_cast(u32x2, v);
       double s = 0.0;
@@ -362,8 +362,8 @@ static int small_np(int64_t P) { return P <= 16 ? 1 : (P <= 32 ? 2 : 0); }
 // the tile (8 groups a wavefront) that pays from one push on, with all of it from a
 // run of kWideRun on.  us per push, this / the kernels: FP32, 1000 x 24, a run 7.2 /
 // 17.6, one launch each 10.9 / 17.6; 1024 rows, 48..64 columns, a run 12.5 / 17.2,
-// each 18.9 / 17.2; FP64, 1000 x 24, a run 10.0 / 21.3; 1024 rows, 24..32 columns,
-// a run 16.2 / 18.1, each 24.7 / 18.1.
+// each 18.9 / 17.2; FP64, 1024 x 32, a run 7.9 / 18.3, each (kernels beyond 16
+// columns) 12.9 / 18.5.
 constexpr int kWideRun = 8;
 
 int small_push_run(bool tv_f64, int64_t P, int j, int rem) {
