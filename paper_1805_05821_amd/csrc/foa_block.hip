@@ -37,7 +37,6 @@
 
 #include "foa.h"
 #include "foa_device.h"
-#include "foa_tile.h"
 
 // Block workspace of foa_push_blocked_static, for callers that cannot
 // allocate device memory: one copy per device the library runs on, held
@@ -385,15 +384,14 @@ __device__ __forceinline__ void wg_sums(const double (&v)[N], double *sh) {
 
 template <typename TV, typename TX, int MODE>
 __global__ __launch_bounds__(256) void k_zgram(BlockArgs a) {
-  if (a.st->status != ST_ACTIVE || *a.flag || (a.gate && !*a.gate)) return;
   __shared__ double sh[5 * (BPK + BPK * BPK)];
   __shared__ double sT[3 * BPK * BPK];
   const int tid = threadIdx.x;
   const int tlev = a.tlev;
-  if (MODE != ZG_YNORM && MODE != ZG_YNQ && tlev > 0) {
-    if (tid < tlev * BPK * BPK) sT[tid] = a.sm[SM_T + tid];
-    __syncthreads();
-  }
+  // Whether the block still runs is fetched with the rows and looked at before
+  // anything is stored (the rows are there either way): a round trip of its own
+  // costs each of these latency-bound passes most of a microsecond.
+  const int status = a.st->status, rejected = *a.flag;
   // Z's order: units of BROWS rows (see k_bpass), row chunk * EPL + e of a
   // unit at e * 16 + chunk
   constexpr int EPL = Vec<TV>::EPL, BROWS = 16 * EPL;
@@ -440,6 +438,7 @@ __global__ __launch_bounds__(256) void k_zgram(BlockArgs a) {
     for (; r + (R - 1) * stride < a.n; r += R * stride) rows(r, std::integral_constant<int, R>{});
     for (; r < a.n; r += stride) rows(r, std::integral_constant<int, 1>{});
     wg_sums(s, sh);
+    if (status != ST_ACTIVE || rejected) return;
     if (tid < BPK) a.partg[(size_t)blockIdx.x * GSLOT + tid * BPK + tid] = sh[tid];
     if (Q && tid < GSLOT) a.partq[(size_t)blockIdx.x * GSLOT + tid] = sh[BPK + tid];
     return;
@@ -463,17 +462,35 @@ __global__ __launch_bounds__(256) void k_zgram(BlockArgs a) {
       for (int l = 0; l < BPK; ++l) z[l] = o[l];
     }
   };
-  for (int64_t r = (int64_t)blockIdx.x * 256 + tid; r < npad; r += 2 * stride) {
-    // two rows in flight (the second past the end reads the first again)
-    double z[2][BPK];
-    const bool two = r + stride < npad;
+  // two rows at a time, the next two in flight (a second past the end reads the
+  // first again)
+  double z[2][BPK];
+  auto load = [&](int64_t r) {
+    if (r >= npad) return;
+    const int64_t r2 = r + stride < npad ? r + stride : r;
+#pragma unroll
+    for (int k = 0; k < BPK; ++k) {
+      z[0][k] = a.Z[r * BPK + k];
+      z[1][k] = a.Z[r2 * BPK + k];
+    }
+  };
+  int64_t r = (int64_t)blockIdx.x * 256 + tid;
+  const double tv = tid < tlev * BPK * BPK ? a.sm[SM_T + tid] : 0.0;
+  load(r);
+  if (tid < tlev * BPK * BPK) sT[tid] = tv;
+  __syncthreads();
+  if (MODE == ZG_WRITEV && (status != ST_ACTIVE || rejected)) return;
+  for (; r < npad; r += 2 * stride) {
+    double y[2][BPK];
 #pragma unroll
     for (int u = 0; u < 2; ++u)
 #pragma unroll
-      for (int k = 0; k < BPK; ++k) z[u][k] = a.Z[(r + (u && two ? stride : 0)) * BPK + k];
+      for (int k = 0; k < BPK; ++k) y[u][k] = z[u][k];
+    const bool two = r + stride < npad;
+    load(r + 2 * stride);
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
-      transform(z[u]);
+      transform(y[u]);
       if (u && !two) break;
       if (MODE == ZG_WRITEV) {
         const int64_t ru = r + u * stride;
@@ -481,18 +498,19 @@ __global__ __launch_bounds__(256) void k_zgram(BlockArgs a) {
         TV *vc = static_cast<TV *>(a.W) + (size_t)(ru / PANEL) * a.n_max * PANEL + (size_t)a.j * PANEL + (rr - ri) +
                  (ri % 16) * EPL + ri / 16;
 #pragma unroll
-        for (int k = 0; k < BPK; ++k) vc[k * PANEL] = (TV)z[u][k];
+        for (int k = 0; k < BPK; ++k) vc[k * PANEL] = (TV)y[u][k];
         continue;
       }
       int m = 0;
 #pragma unroll
       for (int k = 0; k < BPK; ++k)
 #pragma unroll
-        for (int l = k; l < BPK; ++l, ++m) g[m] = fma(z[u][k], z[u][l], g[m]);
+        for (int l = k; l < BPK; ++l, ++m) g[m] = fma(y[u][k], y[u][l], g[m]);
     }
   }
   if (MODE == ZG_WRITEV) return;
   wg_sums(g, sh);
+  if (status != ST_ACTIVE || rejected) return;
   if (tid < GSLOT) {
     const int k = min(tid / BPK, tid % BPK), l = max(tid / BPK, tid % BPK);
     a.partg[(size_t)blockIdx.x * GSLOT + tid] = sh[k * BPK - k * (k - 1) / 2 + l - k];
@@ -524,7 +542,8 @@ __device__ __forceinline__ double slot_sum(const double *p, int G, int lane) {
 
 template <int MODE>
 __global__ __launch_bounds__(256) void k_breduce(BlockArgs a) {
-  if (a.st->status != ST_ACTIVE || *a.flag || (a.gate && !*a.gate)) return;
+  if (a.gate && !*a.gate) return;
+  const bool run = a.st->status == ST_ACTIVE && !*a.flag;  // looked at before anything is stored
   const int lane = threadIdx.x & 63;
   const int wv = blockIdx.x * 4 + (threadIdx.x >> 6);
   const int npairs = a.j * BPK;
@@ -540,10 +559,10 @@ __global__ __launch_bounds__(256) void k_breduce(BlockArgs a) {
       t = strided_sum<false>(a.partb + (size_t)wv * a.ldg, a.G, lane);
     }
     if (MODE == 4) {
-      if (lane == 0) a.dnext[wv] = t;
+      if (lane == 0 && run) a.dnext[wv] = t;
       return;
     }
-    if (lane == 0) {
+    if (lane == 0 && run) {
       const double r = a.sigma[c] * t;
       const size_t idx = (size_t)c * BPK + k;
       if (MODE == 1) {
@@ -557,7 +576,7 @@ __global__ __launch_bounds__(256) void k_breduce(BlockArgs a) {
   } else if (MODE == 1 && wv < npairs + BPK) {
     const int k = wv - npairs;
     const double t = slot_sum(a.partg + k * BPK + k, a.Gz, lane);
-    if (lane == 0) a.sm[SM_YN2 + k] = t;
+    if (lane == 0 && run) a.sm[SM_YN2 + k] = t;
   }
 }
 
@@ -600,15 +619,25 @@ __device__ inline void gram_reduce(const BlockArgs &a, int tid, double *sh, doub
 // ---------------------------------------------------------------------------
 template <int ROUND>
 __global__ __launch_bounds__(kGramThreads) void k_bchol(BlockArgs a) {
-  if (a.st->status != ST_ACTIVE || *a.flag) return;
   __shared__ double sh[256];
   __shared__ double sG[GSLOT];
   const int tid = threadIdx.x;
+  // all of it is fetched at once; nothing is stored for a block that has stopped
+  const int status = a.st->status, rejected = *a.flag;
+  double Stot[BPK * BPK] = {};
+  if (ROUND > 0 && tid == 0) {
+#pragma unroll
+    for (int k = 0; k < BPK * BPK; ++k) Stot[k] = a.sm[SM_S + k];
+  }
   gram_reduce(a, tid, sh, sG);
-  if (tid != 0) return;
-  double G[BPK][BPK], S[BPK][BPK], T[BPK][BPK];
+  if (tid != 0 || status != ST_ACTIVE || rejected) return;
+  // every loop unrolled, the matrices in registers (indexed at run time they lived
+  // in scratch memory: 7.5 us a step, 4.9 us so)
+  double G[BPK][BPK], S[BPK][BPK] = {}, T[BPK][BPK] = {};
   bool ok = true;
+#pragma unroll
   for (int k = 0; k < BPK; ++k)
+#pragma unroll
     for (int l = 0; l < BPK; ++l) {
       // symmetric part (the two triangles are sums of the same products)
       G[k][l] = 0.5 * (sG[k * BPK + l] + sG[l * BPK + k]);
@@ -616,23 +645,25 @@ __global__ __launch_bounds__(kGramThreads) void k_bchol(BlockArgs a) {
     }
   if (ROUND == 0) {
     double tr = 0.0;
+#pragma unroll
     for (int k = 0; k < BPK; ++k) tr += G[k][k];
     const double s = 11.0 * ((double)a.n * BPK + BPK * (BPK + 1)) * 0x1p-53 * tr;
+#pragma unroll
     for (int k = 0; k < BPK; ++k) G[k][k] += s;
   }
-  // G = S^T S, S upper triangular with a positive diagonal
-  for (int k = 0; k < BPK; ++k)
-    for (int l = 0; l < BPK; ++l) S[k][l] = 0.0;
-  for (int k = 0; k < BPK && ok; ++k) {
+  // G = S^T S, S upper triangular with a positive diagonal (a bad pivot goes on with
+  // values that nothing stores)
+#pragma unroll
+  for (int k = 0; k < BPK; ++k) {
     double d = G[k][k];
+#pragma unroll
     for (int i = 0; i < k; ++i) d -= S[i][k] * S[i][k];
-    if (!(d > 0.0) || !isfinite(d)) {
-      ok = false;
-      break;
-    }
+    ok = ok && d > 0.0 && isfinite(d);
     S[k][k] = sqrt(d);
+#pragma unroll
     for (int l = k + 1; l < BPK; ++l) {
       double v = G[k][l];
+#pragma unroll
       for (int i = 0; i < k; ++i) v -= S[i][k] * S[i][l];
       S[k][l] = v / S[k][k];
     }
@@ -642,28 +673,29 @@ __global__ __launch_bounds__(kGramThreads) void k_bchol(BlockArgs a) {
     return;
   }
   // T = S^{-1} (upper triangular), column by column: S T_{:,l} = e_l
+#pragma unroll
   for (int l = 0; l < BPK; ++l) {
+#pragma unroll
     for (int k = BPK - 1; k >= 0; --k) {
+      if (k > l) continue;
       double v = (k == l) ? 1.0 : 0.0;
+#pragma unroll
       for (int i = k + 1; i <= l; ++i) v -= S[k][i] * T[i][l];
-      T[k][l] = (k <= l) ? v / S[k][k] : 0.0;
+      T[k][l] = v / S[k][k];
     }
   }
-  double *Stot = a.sm + SM_S;
-  double P[BPK][BPK];
+#pragma unroll
   for (int k = 0; k < BPK; ++k)
+#pragma unroll
     for (int l = 0; l < BPK; ++l) {
       double v = 0.0;
       if (ROUND == 0) {
         v = S[k][l];
       } else {
+#pragma unroll
         for (int i = k; i <= l; ++i) v += S[k][i] * Stot[i * BPK + l];
       }
-      P[k][l] = v;
-    }
-  for (int k = 0; k < BPK; ++k)
-    for (int l = 0; l < BPK; ++l) {
-      Stot[k * BPK + l] = P[k][l];
+      a.sm[SM_S + k * BPK + l] = v;
       a.sm[SM_T + ROUND * GSLOT + k * BPK + l] = T[k][l];
     }
 }
