@@ -300,9 +300,11 @@ hipError_t launch_init_state(const SmallArgs &a, double tol, hipStream_t s);
 enum { MODES_F64 = 0, MODES_F32 = 1, MODES_SPLIT = 2 };
 int modes_path(bool tv_f64, bool out_f64);  // MODES_F64 or MODES_F32
 bool modes_split_ok(const float *B, int k, int r, size_t ldp);  // B as packed for MODES_F32
+bool modes_split_pays(int64_t n, int k, int r);
+size_t modes_split_bytes(int k, int r);  // MODES_SPLIT: where the FP32 coefficients go, in bytes from the start
 int modes_rpad(int r);
 size_t modes_coef_bytes(int n_max);  // largest packed size for k, r <= n_max
-void modes_pack(int path, const double *B, int k, int r, std::vector<char> &out);  // B: column-major k x r
+void modes_pack(int path, const double *B, int k, int r, std::vector<char> &out);  // MODES_F64 or MODES_F32; B: column-major k x r
 hipError_t launch_modes_gemm(int path, bool tv_f64, const void *W, int64_t n, int n_max, int k,
                              const void *B, int r, void *out, int64_t ld, bool out_f64,
                              hipStream_t s);

@@ -24,8 +24,9 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 // wavefronts share the coefficients, staged through LDS 16 basis columns at a
 // time.  The basis goes straight from memory to the operand registers, the next
 // stage's columns one stage ahead: each is used by its own wavefront alone.
-// Coefficients come as operand fragments, [k / 4][mode / 16][lane]: mode lane %
-// 16, column lane / 16 (D: row = lane % 16, mode 4 t + lane / 16).
+// Coefficients are k-major without padding (a copy to the device beyond 16 KiB
+// costs 4 us more), read as operand fragments: mode lane % 16, column lane / 16 (D:
+// row = lane % 16, mode 4 t + lane / 16).
 // Bound: the FP64 matrix rate (78.6 TFLOP/s); 2 n k r flops.  One thread per row
 // with 16 modes' sums in registers (each reading the basis again, every product
 // behind an LDS read) ran 2^18 x 149 x 60 in 438 us, 10.7 TFLOP/s.
@@ -33,7 +34,7 @@ constexpr int M64_K = 16, M64_MB = 8;
 
 template <typename TV, typename TO, int MB>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_modes_mfma64(
-    const TV *W, int64_t n, int64_t P, int n_max, int kdim, const double *Bf, int rblocks, int r, TO *out, int64_t ld) {
+    const TV *W, int64_t n, int64_t P, int n_max, int kdim, const double *Bk, int r, TO *out, int64_t ld) {
   constexpr int KS = M64_K / 4;      // MFMA steps of a stage
   constexpr int FR = KS * MB;        // fragments of a stage (512 bytes each)
   constexpr int NL = (FR + 3) / 4;   // loads per wavefront
@@ -52,6 +53,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
   for (int a = 0; a < 2; ++a)
 #pragma unroll
     for (int b = 0; b < MB; ++b) acc[a][b] = f64x4{0.0, 0.0, 0.0, 0.0};
+  // coefficient rows beyond kdim and modes beyond r read as 0
+  const __amdgpu_buffer_rsrc_t rb = make_rsrc(Bk, (unsigned)(kdim * r * 8));
   TV w[KS][2];
   double bn[NL];
   auto load_w = [&](int k0) {
@@ -75,7 +78,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 #pragma unroll
     for (int i = 0; i < NL; ++i) {
       const int f = wave + 4 * i;  // fragment of the stage: step f / MB, mode block f % MB
-      if (f < FR) bn[i] = Bf[((size_t)(k0 / 4 + f / MB) * rblocks + mb0 + f % MB) * 64 + lane];
+      const int mode = (mb0 + f % MB) * 16 + (lane & 15), l = k0 + f / MB * 4 + (lane >> 4);
+      if (f < FR)
+        bn[i] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(
+                                               rb, mode < r ? (l * r + mode) * 8 : (int)kOOR, 0, 0));
     }
   };
   load_b(0);
@@ -126,7 +132,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 // FP32 basis and FP32 output on the bf16 matrix units: every FP32 value is the
 // sum of three bf16 values exactly, w = w1 + w2 + w3 (w1 by truncation, which
 // cannot overflow; w2 the rest rounded to nearest; w3 what is left) and b likewise
-// (split by the caller, each piece to nearest), and the six products
+// (split by k_modes_split_coefs, each piece to nearest), and the six products
 //   b1 w1 + (b1 w2 + b2 w1) + (b1 w3 + b2 w2 + b3 w1)
 // are accumulated in FP32; what is left out is below 2^-24 |b w|.  The products
 // are exact and 16 columns enter an accumulator at once, so the error against 64
@@ -138,7 +144,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 // the coefficients are staged through LDS as operand fragments, [k / 16][mode /
 // 32][piece][lane][8].
 // Bound: HBM (n k + n r values of 4 bytes) up to about 200 modes per pass, the
-// bf16 rate beyond.
+// bf16 rate beyond.  2^22 x 160 modes 1.48 ms, 1e8 rows x 299 columns x 158 modes
+// 61 ms; on the FP32 matrix units (k_modes_mfma) 2.06 and 85 ms.
 constexpr int MS_K = 32;
 
 template <int NB>
@@ -151,7 +158,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
   __shared__ u32x4 sB[FR * 64];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-const int64_t m0 = (int64_t)blockIdx.x * 128 + wave * 32;
+  const int64_t m0 = (int64_t)blockIdx.x * 128 + wave * 32;
   const int64_t p = m0 / PANEL;
   const int rb0 = blockIdx.y * NB;
   const __amdgpu_buffer_rsrc_t rw =
@@ -293,11 +300,20 @@ static int m64_blocks(int r) {
   return (all + mb - 1) / mb * mb;
 }
 
+// Rule for the split products of an FP32 basis and output: from 2^31 multiply-adds
+// on, the splitting launch (3 us) is less than they save (5e-15 s each against the
+// FP32 units).
+bool modes_split_pays(int64_t n, int k, int r) { return (double)n * k * r >= 0x1p31; }
+
+// Where the FP32 coefficients lie that k_modes_split_coefs splits: behind the split
+// ones.
+size_t modes_split_bytes(int k, int r) { return (size_t)modes_kpad(k) * modes_rpad(r) * 6; }
+
 // An upper bound of every path's packed size: splitting the blocks evenly over
 // up to 2 (32-mode) or 4 (16-mode) workgroups adds at most 1 or 3 blocks.
 size_t modes_coef_bytes(int n_max) {
   const size_t k = (size_t)modes_kpad(n_max);
-  return std::max(k * ((n_max + 31) / 32 + 1) * 32 * 6, k * ((n_max + 15) / 16 + 3) * 16 * 8);
+  return std::max(k * ((n_max + 31) / 32 + 1) * 32 * (6 + 4), k * ((n_max + 15) / 16 + 3) * 16 * 8);
 }
 
 // The range in which three bf16 pieces carry an FP32 coefficient and the basis
@@ -320,45 +336,37 @@ bool modes_split_ok(const float *B, int k, int r, size_t ldp) {
 
 int modes_path(bool tv_f64, bool out_f64) { return !tv_f64 && !out_f64 ? MODES_F32 : MODES_F64; }
 
-// FP32 value to three bf16 values, each to nearest even (finite, |v| <= 2^60)
-static void split3(float v, uint16_t (&o)[3]) {
-  for (int i = 0; i < 3; ++i) {
-    uint32_t u;
-    std::memcpy(&u, &v, 4);
-    u = (u + 0x7fffu + ((u >> 16) & 1u)) & 0xffff0000u;
-    o[i] = (uint16_t)(u >> 16);
-    float f;
-    std::memcpy(&f, &u, 4);
-    v -= f;
-  }
-}
 
 void modes_pack(int path, const double *B, int k, int r, std::vector<char> &out) {
   if (path == MODES_F64) {
-    const int ks = (k + M64_K - 1) / M64_K * (M64_K / 4), rb = m64_blocks(r);
-    out.assign((size_t)ks * rb * 64 * 8, 0);
+    out.resize((size_t)k * r * 8);
     double *o = reinterpret_cast<double *>(out.data());
     for (int c = 0; c < r; ++c)
-      for (int l = 0; l < k; ++l) o[((size_t)(l / 4) * rb + c / 16) * 64 + (l % 4) * 16 + c % 16] = B[(size_t)c * k + l];
+      for (int l = 0; l < k; ++l) o[(size_t)l * r + c] = B[(size_t)c * k + l];
     return;
   }
   const int kp = modes_kpad(k), rp = modes_rpad(r);
-  if (path == MODES_F32) {
-    out.assign((size_t)kp * rp * 4, 0);
-    float *o = reinterpret_cast<float *>(out.data());
-    for (int c = 0; c < r; ++c)
-      for (int l = 0; l < k; ++l) o[(size_t)l * rp + c] = (float)B[(size_t)c * k + l];
-    return;
-  }
-  out.assign((size_t)kp * rp * 6, 0);
-  uint16_t *o = reinterpret_cast<uint16_t *>(out.data());
+  out.assign((size_t)kp * rp * 4, 0);
+  float *o = reinterpret_cast<float *>(out.data());
   for (int c = 0; c < r; ++c)
-    for (int l = 0; l < k; ++l) {
-      uint16_t q[3];
-      split3((float)B[(size_t)c * k + l], q);
-      for (int i = 0; i < 3; ++i)
-        o[((((size_t)(l / 16) * (rp / 32) + c / 32) * 3 + i) * 64 + (l % 16) / 8 * 32 + c % 32) * 8 + l % 8] = q[i];
-    }
+    for (int l = 0; l < k; ++l) o[(size_t)l * rp + c] = (float)B[(size_t)c * k + l];
+}
+
+// The coefficients Bt (k-major, padded) as the operand fragments of k_modes_split:
+// three bf16 pieces of each, to nearest even (finite, at most 2^60 in size).
+__global__ __launch_bounds__(256) void k_modes_split_coefs(const float *Bt, int kp, int rp, uint16_t *o) {
+  const int e = blockIdx.x * 256 + threadIdx.x;
+  if (e >= kp * rp) return;
+  const int l = e / rp, c = e - l * rp;
+  float v = Bt[e];
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    unsigned u = __builtin_bit_cast(unsigned, v);
+    u = (u + 0x7fffu + ((u >> 16) & 1u)) & 0xffff0000u;
+    o[((((size_t)(l / 16) * (rp / 32) + c / 32) * 3 + i) * 64 + (l % 16) / 8 * 32 + c % 32) * 8 + l % 8] =
+        (uint16_t)(u >> 16);
+    v -= __builtin_bit_cast(float, u);
+  }
 }
 
 // Up to NB = 5 the registers fit three wavefronts per SIMD (three workgroups
@@ -508,8 +516,8 @@ static void launch_m64_mb(const TV *W, int64_t n, int n_max, int k, const double
                           hipStream_t s) {
   const int rb = m64_blocks(r);
   dim3 g((unsigned)((n + 127) / 128), (unsigned)(rb / MB));
-  hipLaunchKernelGGL((k_modes_mfma64<TV, TO, MB>), g, dim3(256), 0, s, W, n, (n + PANEL - 1) / PANEL, n_max, k, Bf, rb, r,
-                     out, ld);
+  hipLaunchKernelGGL((k_modes_mfma64<TV, TO, MB>), g, dim3(256), 0, s, W, n, (n + PANEL - 1) / PANEL, n_max, k, Bf, r, out,
+                     ld);
 }
 
 template <typename TV, typename TO>
@@ -517,7 +525,14 @@ static void launch_m64(const void *W, int64_t n, int n_max, int k, const double 
                        hipStream_t s) {
   const TV *w = (const TV *)W;
   TO *o = (TO *)out;
-  switch (m64_mb(r)) {
+  // few rows: fewer mode blocks a workgroup rather than idle CUs
+  int mb = m64_mb(r);
+  while (mb > 1 && (n + 127) / 128 * (m64_blocks(r) / mb) < 256) {
+    int d = mb - 1;
+    while (mb % d) --d;
+    mb = d;
+  }
+  switch (mb) {
     case 1: launch_m64_mb<TV, TO, 1>(w, n, n_max, k, Bf, r, o, ld, s); break;
     case 2: launch_m64_mb<TV, TO, 2>(w, n, n_max, k, Bf, r, o, ld, s); break;
     case 3: launch_m64_mb<TV, TO, 3>(w, n, n_max, k, Bf, r, o, ld, s); break;
@@ -533,9 +548,15 @@ hipError_t launch_modes_gemm(int path, bool tv_f64, const void *W, int64_t n, in
                              void *out, int64_t ld, bool out_f64, hipStream_t s) {
   if (r <= 0 || k <= 0) return hipSuccess;
   if (k > 512 || k > n_max) return hipErrorInvalidValue;
-  if (path == MODES_SPLIT && !tv_f64 && !out_f64)
+  if (path == MODES_SPLIT && !tv_f64 && !out_f64) {
+    const int kp = modes_kpad(k), rp = modes_rpad(r);
+    char *b = static_cast<char *>(const_cast<void *>(Bv));
+    hipLaunchKernelGGL(k_modes_split_coefs, dim3((kp * rp + 255) / 256), dim3(256), 0, s,
+                       (const float *)(b + modes_split_bytes(k, r)), kp, rp, (uint16_t *)b);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
     launch_split((const float *)W, n, n_max, k, (const u32x4 *)Bv, r, (float *)out, ld, s);
-  else if (path == MODES_F32 && !tv_f64 && !out_f64)
+  } else if (path == MODES_F32 && !tv_f64 && !out_f64)
     launch_mfma((const float *)W, n, n_max, k, (const float *)Bv, r, (float *)out, ld, s);
   else if (path != MODES_F64)
     return hipErrorInvalidValue;

@@ -263,12 +263,13 @@ foa_status foa_modes(foa_ctx c, int32_t m_max, double *h_lambda, int8_t *h_kind,
   int path = modes_path(v64, o64);
   std::vector<char> packed;
   modes_pack(path, Bp.data(), m, ncols, packed);
-  if (path == MODES_F32 &&
+  size_t at = 0;
+  if (path == MODES_F32 && modes_split_pays(c->n, m, ncols) &&
       modes_split_ok(reinterpret_cast<const float *>(packed.data()), m, ncols, (size_t)modes_rpad(ncols))) {
     path = MODES_SPLIT;
-    modes_pack(path, Bp.data(), m, ncols, packed);
+    at = modes_split_bytes(m, ncols);
   }
-  hipError_t e = hipMemcpy(dB, packed.data(), packed.size(), hipMemcpyHostToDevice);
+  hipError_t e = hipMemcpy(static_cast<char *>(dB) + at, packed.data(), packed.size(), hipMemcpyHostToDevice);
   if (e != hipSuccess) return hip_err(c, e, "hipMemcpy mode coefficients");
   hipEvent_t e0 = nullptr, e1 = nullptr;
   if (c->profile) {

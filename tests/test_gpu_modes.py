@@ -314,3 +314,13 @@ def test_mode_kernels(prec, n, N, scale):
         announce(f"FP32 output err {e.max():.2e}")
         assert e.max() <= (m + 2) * np.sqrt(m) * 2.0 ** -24
     s.close()
+
+
+@pytest.mark.parametrize("n,N,scale", [
+    (64 * 32768 + 33, 34, 1.0),    # 33 modes: two blocks, the last one nearly empty
+    (800001, 53, 1.0), (90000, 161, 1.0), (33007, 258, 1.0),   # 52, 160 and 257 modes
+    (90000, 161, 2.0 ** 70),      # beyond the range of the split
+])
+def test_mode_split_kernel(n, N, scale):
+    """FP32 products large enough for the bf16 units (2^31 multiply-adds)."""
+    test_mode_kernels("f32", n, N, scale)
