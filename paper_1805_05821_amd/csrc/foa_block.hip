@@ -9,8 +9,8 @@
 //   Z = Q S by shifted CholeskyQR3 (Fukaya et al., SIAM J. Sci. Comput. 2020)
 //   beta's new columns [R1 + R2 (+ R3); S], V's new columns Q, and H_bar's new
 //   columns from the recurrence above solved column by column.
-// So the basis is swept three times per block instead of three times per
-// snapshot.  The third projection: a stored FP32 basis is orthonormal only to
+// So the basis is swept three times per block (twice within a run, where a block's
+// last sweep forms the next one's R1) instead of three times per snapshot.  The third projection: a stored FP32 basis is orthonormal only to
 // E = V^T V - I, the part of Z left along V after two passes is about E R2,
 // and where the block's new directions are as small as ||E|| ||Y|| (noise-
 // floor snapshots at small n) that part is as large as Z itself.  The test
@@ -23,15 +23,15 @@
 //
 // Kernels (all on the context stream, all no-ops once the block is rejected):
 //   k_bpass   : the block row passes over V (FP64 accumulation, BPK right-hand
-//               sides; same panel walk and tile layout as the single push);
-//   k_zgram   : passes over the n x BPK block (||y||^2, Z^T Z, Z <- Z T with
-//               its Gram matrix, the final Q written into V);
+//               sides, column sums on FP64 MFMA);
+//   k_zgram   : passes over the n x BPK block (||y||^2, the Gram matrix of Z T,
+//               the final Q written into V);
 //   k_breduce : fixed-order reduction of the pass partials into R1 / R2 and
 //               the next pass's coefficients;
 //   k_bthird  : the test for the third projection (sets the gate of its
-//               BP_D pass, reduction, BP_Z2 pass and Gram pass);
+//               BP_D pass, reduction and BP_Z2 pass);
 //   k_bchol   : Gram reduction, (shifted) Cholesky and triangular inverse;
-//   k_bcommit : breakdown test, beta, H_bar, sigma and the scalar state.
+//   k_bcommit, k_bcommit_h : breakdown test, beta, sigma and the scalar state; H_bar.
 #include <mutex>
 #include <type_traits>
 
