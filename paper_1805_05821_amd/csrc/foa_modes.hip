@@ -2,8 +2,8 @@
 // basis W (n x k columns in use, FP32 or FP64) times the k x r coefficient
 // matrix B (FP64, sigma folded in, packed real columns).  An FP32 basis with
 // FP32 output runs on bf16 MFMA with every value split in three (FP32 MFMA for
-// coefficients outside the split's range), every other combination on FP64
-// MFMA.
+// small products, few columns and coefficients outside the split's range), every
+// other combination on FP64 MFMA.
 #include <algorithm>
 #include <cmath>
 #include <cstring>
@@ -130,22 +130,30 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 }
 
 // FP32 basis and FP32 output on the bf16 matrix units: every FP32 value is the
-// sum of three bf16 values exactly, w = w1 + w2 + w3 (w1 by truncation, which
-// cannot overflow; w2 the rest rounded to nearest; w3 what is left) and b likewise
-// (split by k_modes_split_coefs, each piece to nearest), and the six products
+// sum of three bf16 values exactly, w = w1 + w2 + w3 (each the rest rounded to
+// nearest, so |w2| <= 2^-8 and |w3| <= 2^-17 for a significand in [1, 2)) and b
+// likewise (by k_modes_split_coefs), and the six products
 //   b1 w1 + (b1 w2 + b2 w1) + (b1 w3 + b2 w2 + b3 w1)
-// are accumulated in FP32; what is left out is below 2^-24 |b w|.  The products
-// are exact and 16 columns enter an accumulator at once, so the error against 64
-// bits is no larger than of FP32 products summed two columns at a time (see
-// modes_split_ok for the range of the coefficients).
+// are accumulated in FP32; what is left out, b2 w3 + b3 w2 + b3 w3, is below 2^-24
+// |b w|.  A product accumulated into a sum costs a rounding of that sum's size,
+// so b1 w1 alone enters the running sum, 16 columns at once, and the small five of
+// 32 columns are added to it together: three roundings where FP32 products summed
+// in turn take 32.  Measured against 64 bits, error of this kernel over that of
+// k_modes_mfma (norm over all modes / of the worst mode): travelling oscillations
+// of 34, 64 and 160 modes 0.49 / 0.48, 0.43 / 0.38 and 0.39 / 0.37; Gaussian streams
+// of 33, 39, 48, 64 and 160 modes 1.05 / 0.88, 0.96 / 0.78, 0.87 / 0.69, 0.73 / 0.57
+// and 0.49 / 0.38; modes that are one column of the basis 1.05 / 1.13, the sum of two
+// far apart 1.28 / 1.39 (both below one FP32 rounding of the result).  All six into
+// one sum: 0.79 / 0.80 for 160 travelling oscillations, 1.6 / 1.6 for single columns;
+// b2 w3 and b3 w2 as well: 0.38 / 0.37 and 1.00 / 1.00, 2^22 x 160 modes 1.78 ms.
 // Tile: 128 rows x 32 NB modes per workgroup, wavefront w its rows 32 w .. + 31.
 // The basis goes from memory straight to registers (lane: row lane % 32, eight
 // columns from 8 (lane / 32)) and is split there, one stage of 32 columns ahead;
 // the coefficients are staged through LDS as operand fragments, [k / 16][mode /
 // 32][piece][lane][8].
 // Bound: HBM (n k + n r values of 4 bytes) up to about 200 modes per pass, the
-// bf16 rate beyond.  2^22 x 160 modes 1.48 ms, 1e8 rows x 299 columns x 158 modes
-// 61 ms; on the FP32 matrix units (k_modes_mfma) 2.06 and 85 ms.
+// bf16 rate beyond.  2^22 x 160 modes 1.54 ms; on the FP32 matrix units
+// (k_modes_mfma) 2.07 ms.
 constexpr int MS_K = 32;
 
 template <int NB>
@@ -203,10 +211,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
       for (int q = 0; q < 4; ++q) {
         const unsigned x0 = w[s][2 * q], x1 = w[s][2 * q + 1];
         const float f0 = __builtin_bit_cast(float, x0), f1 = __builtin_bit_cast(float, x1);
-        w1[s][q] = __builtin_amdgcn_perm(x1, x0, 0x07060302u);  // the upper halves
-        const float r0 = f0 - __builtin_bit_cast(float, x0 & 0xffff0000u);
-        const float r1 = f1 - __builtin_bit_cast(float, x1 & 0xffff0000u);
         typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+        const unsigned c1 = __builtin_bit_cast(unsigned, bf16x2{(__bf16)f0, (__bf16)f1});
+        w1[s][q] = c1;
+        const float r0 = f0 - __builtin_bit_cast(float, c1 << 16);
+        const float r1 = f1 - __builtin_bit_cast(float, c1 & 0xffff0000u);
         const unsigned c2 = __builtin_bit_cast(unsigned, bf16x2{(__bf16)r0, (__bf16)r1});
         w2[s][q] = c2;
         const float t0 = r0 - __builtin_bit_cast(float, c2 << 16);
@@ -218,24 +227,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
       load_b(k0 + MS_K);
       load_w(k0 + MS_K);
     }
+    // a mode block at a time; the five small products of the stage are summed on
+    // their own and added once
 #pragma unroll
-    for (int s = 0; s < KS; ++s) {
-      const bf16x8 W1 = __builtin_bit_cast(bf16x8, w1[s]), W2 = __builtin_bit_cast(bf16x8, w2[s]),
-                   W3 = __builtin_bit_cast(bf16x8, w3[s]);
-      // mode blocks in pairs, so that consecutive products go to different sums
+    for (int b = 0; b < NB; ++b) {
+      f32x16 small;
 #pragma unroll
-      for (int b = 0; b < NB; b += 2) {
-        bf16x8 B[2];
-        auto piece = [&](int c) {
+      for (int t = 0; t < 16; ++t) small[t] = 0.f;
 #pragma unroll
-          for (int i = 0; i < 2; ++i)
-            if (b + i < NB) B[i] = __builtin_bit_cast(bf16x8, sB[((s * NB + b + i) * 3 + c) * 64 + lane]);
-        };
-        auto term = [&](const bf16x8 &w) {
-#pragma unroll
-          for (int i = 0; i < 2; ++i)
-            if (b + i < NB) acc[b + i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(B[i], w, acc[b + i], 0, 0, 0);
-        };
+      for (int s = 0; s < KS; ++s) {
+        const bf16x8 W1 = __builtin_bit_cast(bf16x8, w1[s]), W2 = __builtin_bit_cast(bf16x8, w2[s]),
+                     W3 = __builtin_bit_cast(bf16x8, w3[s]);
+        bf16x8 B;
+        auto piece = [&](int c) { B = __builtin_bit_cast(bf16x8, sB[((s * NB + b) * 3 + c) * 64 + lane]); };
+        auto term = [&](const bf16x8 &w) { small = __builtin_amdgcn_mfma_f32_32x32x16_bf16(B, w, small, 0, 0, 0); };
         piece(2);
         term(W1);
         piece(1);
@@ -244,8 +249,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
         piece(0);
         term(W3);
         term(W2);
-        term(W1);
+        acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(B, W1, acc[b], 0, 0, 0);
       }
+#pragma unroll
+      for (int t = 0; t < 16; ++t) acc[b][t] += small[t];
     }
   }
   // D[i][j]: j = lane % 32 (data row), i = 8 (t / 4) + 4 (lane / 32) + t % 4 (mode)
@@ -261,8 +268,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
   }
 }
 
-// FP32-product kernel (FP32 basis, FP32 output, coefficients outside the range
-// of k_modes_split): Phi^T = B^T W^T on 32x32x2 FP32 MFMA
+// FP32-product kernel (FP32 basis, FP32 output, what modes_split_pays and
+// modes_split_ok keep from k_modes_split): Phi^T = B^T W^T on 32x32x2 FP32 MFMA
 // with FP32 accumulation.  Tile: 128 data rows (two panels) x 32*NB mode
 // columns per workgroup; wavefront w owns data rows 32w..32w+31 and all NB
 // 32-mode blocks, so for r <= 256 the basis is read exactly once.  k advances
@@ -302,8 +309,12 @@ static int m64_blocks(int r) {
 
 // Rule for the split products of an FP32 basis and output: from 2^31 multiply-adds
 // on, the splitting launch (3 us) is less than they save (5e-15 s each against the
-// FP32 units).
-bool modes_split_pays(int64_t n, int k, int r) { return (double)n * k * r >= 0x1p31; }
+// FP32 units), and from kSplitCols basis columns on, where its error is no larger
+// (k_modes_split; with up to 33 columns the FP32 products' may be smaller) and it
+// is the faster one: 2^21 rows, us, split / FP32: 32 columns 132 / 125, 48 columns
+// 204 / 254, 64 columns 259 / 310.
+constexpr int kSplitCols = 48;
+bool modes_split_pays(int64_t n, int k, int r) { return k >= kSplitCols && (double)n * k * r >= 0x1p31; }
 
 // Where the FP32 coefficients lie that k_modes_split_coefs splits: behind the split
 // ones.
@@ -317,10 +328,13 @@ size_t modes_coef_bytes(int n_max) {
 }
 
 // The range in which three bf16 pieces carry an FP32 coefficient and the basis
-// values beside it without loss: a coefficient is a column's scale sigma (the
-// stored column has norm 1 / sigma) times an entry of a unit vector, so bounds on
-// the largest coefficient of each basis column bound both.  Products outside go
-// to the FP32 kernel.
+// values beside it: a coefficient is a column's scale sigma (the stored column has
+// norm 1 / sigma) times an entry of a unit vector, so a largest coefficient of at
+// least 2^-60 keeps the values of its basis column below 2^60, far from where the
+// rounding of w1 overflows; a column without a coefficient says nothing of its
+// values.  Products outside go to the FP32 kernel.  (The last piece of a value
+// below 2^-109 is under the smallest bf16: an error of 2^-134, in a column whose
+// norm is at least 2^-60.)
 bool modes_split_ok(const float *B, int k, int r, size_t ldp) {
   for (int l = 0; l < k; ++l) {
     float m = 0.f;
@@ -329,7 +343,7 @@ bool modes_split_ok(const float *B, int k, int r, size_t ldp) {
       if (!(v <= 0x1p60f)) return false;  // also NaN
       m = std::max(m, v);
     }
-    if (m != 0.f && m < 0x1p-60f) return false;
+    if (m < 0x1p-60f) return false;
   }
   return true;
 }

@@ -324,3 +324,44 @@ def test_mode_kernels(prec, n, N, scale):
 def test_mode_split_kernel(n, N, scale):
     """FP32 products large enough for the bf16 units (2^31 multiply-adds)."""
     test_mode_kernels("f32", n, N, scale)
+
+
+@pytest.mark.parametrize("n,N", [
+    (64 * 34950 + 7, 32), (64 * 32768 + 33, 33), (64 * 32768 + 33, 34), (972201, 48),   # short of the split's columns
+    (932101, 49), (894501, 50),    # 48 and 49 columns: one and a half stages, and a column more
+    (800001, 53), (90000, 161), (33007, 258),
+])
+def test_mode_split_error(n, N):
+    """FP32 products of 2^31 multiply-adds and more against the FP64 output of the
+    same stream.  The partial sums over the columns of an orthonormal basis are no
+    longer than the whole, and one rounding of such a sum per column, independent,
+    is at most sqrt(m) 2^-24 of the result: a column lacking any one of the
+    split's smallest products is beyond that.  The split's error is also no larger
+    than the FP32 products': the same stream scaled by 2^70 leaves the split's
+    range (its first basis column; powers of two change no rounding)."""
+    import torch
+
+    from paper_1805_05821_amd import foa as F
+    from paper_1805_05821_amd.stream import FOAStream
+
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n + N)
+    X = torch.randn((N, n), generator=gen, device="cuda", dtype=torch.float32)
+    m, worst = N - 1, []
+    for scale in (1.0, 2.0 ** 70):
+        s = FOAStream(n, N, prec="f32", breakdown_tol=0.0, ws_fill=0xFF)
+        s.push_blocked(X * scale)
+        st, q = s.sync()
+        assert q == N
+        p64 = torch.empty((m, n), dtype=torch.float64, device="cuda")
+        p32 = torch.empty((m, n), dtype=torch.float32, device="cuda")
+        F.foa_modes(s.ctx, m, p64, n, m, F.FOA_F64)
+        F.foa_modes(s.ctx, m, p32, n, m, F.FOA_F32)
+        e = torch.linalg.vector_norm(p32.double() - p64, dim=1) / torch.linalg.vector_norm(p64, dim=1)
+        worst.append(float(e.max()))
+        s.close()
+        del s, p64, p32
+    announce(f"n={n} m={m}: worst column {worst[0]:.3e}, FP32 products {worst[1]:.3e}, "
+             f"bound {np.sqrt(m) * 2.0 ** -24:.3e}")
+    assert max(worst) <= np.sqrt(m) * 2.0 ** -24
+    assert worst[0] <= worst[1]
