@@ -131,6 +131,16 @@ foa_status push_blocked_impl(foa_ctx_s *c, const void *d_X, int64_t ld, int32_t 
 
 }  // namespace
 
+namespace foa {
+
+// The block passes address a block through one 32-bit buffer range
+// (block_x_bytes); an access at its end does not wrap either.
+bool block_range_ok(int64_t ld, int es) { return (double)(BPK * ld + PANEL) * es < 4294967295.0; }
+
+unsigned block_x_range(int64_t ld, int rows, int es) { return block_x_bytes(ld, rows, es); }
+
+}  // namespace foa
+
 extern "C" {
 
 foa_status foa_block_workspace_bytes(int64_t n, int32_t n_max, foa_prec prec, size_t *bytes) {
@@ -186,8 +196,7 @@ foa_status push_blocked_impl(foa_ctx_s *c, const void *d_X, int64_t ld, int32_t 
   const size_t es = x64 ? 8 : 4;
   const char *X = static_cast<const char *>(d_X);
   int *flag = reinterpret_cast<int *>(bws + L.flag);
-  // the block passes address a block through one 32-bit buffer range
-  const bool range_ok = (double)(BPK * ld + PANEL) * es < 4294967295.0;
+  const bool range_ok = block_range_ok(ld, (int)es);
   auto push_one = [&](int k) -> foa_status {
     foa_status rr = enqueue_push(c, X + (size_t)k * ld * es, x64);
     return rr;

@@ -180,15 +180,16 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(QW >= 1
   auto load_group = [&](const __amdgpu_buffer_rsrc_t &r, int g, TV (&dst)[EPL]) {
     unpack16<TV>(__builtin_amdgcn_raw_buffer_load_b128(r, (int)goff0, (int)(g * GBYTES), kTileLoad), dst);
   };
-  // snapshot rows of a unit: snapshot k's row r at byte (k * ldx + r) * sizeof(TX)
+  // snapshot rows of a unit: snapshot k's row r at byte (k * ldx + r) * sizeof(TX);
+  // rows past the end are masked with the range itself, which may pass kOOR
+  const unsigned xbytes = block_x_bytes(a.ldx, BROWS, sizeof(TX));
   const unsigned xoff0 = (unsigned)((uk * a.ldx + urow) * sizeof(TX));
   const int nfull = (int)(a.n / BROWS), nrem = (int)(a.n % BROWS);  // whole units, rows of the one after
   auto load_xs = [&](const void *x, int u) {
     const int v = u < pend ? u : 0;
     const int valid = u < nfull ? BROWS : (u == nfull ? nrem : 0);
-    return buf_load_raw<TX>(make_rsrc(static_cast<const TX *>(x) + (size_t)v * BROWS,
-                                      (unsigned)(((BPK - 1) * a.ldx + BROWS) * sizeof(TX))),
-                            uact && urow < valid ? xoff0 : kOOR);
+    return buf_load_raw<TX>(make_rsrc(static_cast<const TX *>(x) + (size_t)v * BROWS, xbytes),
+                            uact && urow < valid ? xoff0 : xbytes);
   };
   typedef typename std::conditional<SRC_X, TX, double>::type TY;
   auto load_y = [&](int u) -> TY {

@@ -12,7 +12,7 @@ namespace foa {
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 constexpr int kRsrcWord3 = 0x00020000;   // raw buffer, 32-bit data format (CDNA)
-constexpr unsigned kOOR = 0x80000000u;   // offset beyond every range used with it
+constexpr unsigned kOOR = 0x80000000u;   // offset beyond every range used with it (ranges below 2^31)
 // Cache policy of the basis-tile loads: non-temporal (the "nt" bit).  A tile
 // is streamed once per sweep and the basis is far larger than the caches; on
 // MI355X this policy raises a read-mostly panel walk from about 6.3 to about

@@ -186,6 +186,14 @@ constexpr int SM_S = SM_YN2 + BPK;
 constexpr int SM_T = SM_S + BPK * BPK;       // T_0, T_1, T_2: the Cholesky steps' inverses
 constexpr int SM_R2 = SM_T + 3 * BPK * BPK;
 constexpr int SM_TOTAL = SM_R2 + 512 * BPK;
+// The 32-bit buffer range through which a block pass reads the BPK snapshots, from
+// row r of the first to row r + rows - 1 of the last (bytes; es: element size).  It
+// may pass 2^31, so lanes without a row mask their offset with the range itself.
+__host__ __device__ constexpr unsigned block_x_bytes(int64_t ldx, int rows, int es) {
+  return (unsigned)(((BPK - 1) * ldx + rows) * es);
+}
+bool block_range_ok(int64_t ld, int es);  // whether it holds them
+unsigned block_x_range(int64_t ld, int rows, int es);  // block_x_bytes for callers without this header
 struct BlockArgs {
   void *W;          // stored basis (panel layout)
   const void *x;    // first snapshot of the block; snapshot k at x + k * ldx (elements)

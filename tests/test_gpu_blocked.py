@@ -257,3 +257,32 @@ def test_block_tiles(prec, n, N):
     kap, orth = _compare(g, seq, 10.0, eps, f"{prec} {n} x {N}")
     assert orth <= 10 * np.sqrt(q) * eps
     s.close()
+
+
+@pytest.mark.parametrize("prec,dtype,ld", [("f64", "float64", 95_000_000), ("f32", "float32", 190_000_000),
+                                           ("f32", "float64", 95_000_000)])
+def test_blocked_rows_far_apart(prec, dtype, ld):
+    """Snapshots so far apart that a block's buffer range passes 2^31 bytes, with
+    values between them that must not be read as the rows past the end of a
+    ragged stream: bitwise the results of the same snapshots side by side."""
+    import torch
+
+    n, p = 1000, 9
+    dt = getattr(torch, dtype)
+    X = np.random.default_rng(ld % 97).standard_normal((n, p))
+    ref = _run_blocked(X, prec, snap_dtype=dt)
+    from paper_1805_05821_amd.stream import FOAStream
+
+    far = torch.full((p, ld), 1e3, dtype=dt, device="cuda")
+    far[:, :n] = torch.from_numpy(np.ascontiguousarray(X.T)).to(device="cuda", dtype=dt)
+    s = FOAStream(n, p, prec=prec, ws_fill=0xFF)
+    s.push_blocked(far[:, :n])
+    st, q = s.sync()
+    H, B, q, m = s.state()
+    assert q == ref["q"] == p
+    assert np.array_equal(H, ref["H"]) and np.array_equal(B, ref["beta"])
+    assert np.array_equal(s.basis(q).cpu().numpy().T, ref["V"])
+    s.close()
+    ref["stream"].close()
+    del far
+    torch.cuda.empty_cache()
