@@ -755,11 +755,14 @@ __device__ inline void bcommit_products(const BlockArgs &a, int wg) {
 
 __global__ __launch_bounds__(256) void k_bcommit(BlockArgs a) {
   DevState *st = a.st;
-  if (st->status != ST_ACTIVE || *a.flag) return;
+  if (st->status != ST_ACTIVE) return;
+  // without a look at the flag, which workgroup 0 may be setting: nothing reads the
+  // products of a rejected block
   if (blockIdx.x > 0) {
     bcommit_products(a, (int)blockIdx.x - 1);
     return;
   }
+  if (*a.flag) return;
   __shared__ int s_ok;
   const int tid = threadIdx.x;
   const int j = a.j;

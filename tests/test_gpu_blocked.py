@@ -286,3 +286,32 @@ def test_blocked_rows_far_apart(prec, dtype, ld):
     ref["stream"].close()
     del far
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("j0,pos", [(200, 2), (329, 0), (472, 3)])
+def test_blocked_rejected_commit(j0, pos):
+    """A dependent snapshot inside a block of a wide basis, blocks following in the
+    run: the commit's breakdown test rejects the block while the commit's other
+    workgroups form the H_bar products, nothing of it is kept and the sequential
+    kernels stop the stream at that snapshot.  The same state every time, and the
+    oracle's within the blocked bound."""
+    n, N = 1300, 496
+    X = np.random.default_rng(j0).standard_normal((n, N))
+    d = j0 + pos
+    X[:, d] = X[:, :d] @ np.random.default_rng(d).standard_normal(d) / np.sqrt(d)
+    ref = oracle.foa_batch(X)
+    assert ref.q == d
+    m = d - 1
+    kap = kappa_of(ref.beta[:m, :m])
+    first = None
+    for _ in range(3):
+        g = _run_blocked(X, "f64")
+        assert g["q"] == d and g["m"] == d
+        eH = rel(g["H"][:d, :d], ref.H[:d, :d])
+        announce(f"rejected at {d}: relH={eH:.2e}, kappa={kap:.2e}")
+        assert eH <= 10.0 * EPS64 * kap * d
+        if first is None:
+            first = g
+        assert np.array_equal(g["H"], first["H"]) and np.array_equal(g["beta"], first["beta"])
+        assert np.array_equal(g["V"], first["V"])
+        g["stream"].close()
