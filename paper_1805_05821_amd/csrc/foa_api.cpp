@@ -170,12 +170,15 @@ hipEvent_t take_event(foa_ctx_s *c) {
 // fused / with reduce kernels: FP32, 4 wavefronts, 4133 x 64 (17 sums) 19.4 /
 // 21.8, 16384 x 100 (up to 128, fused to 32) 23.3 / 23.4; FP64, 4 and 8 wavefronts,
 // 4096 x 64 (16) 18.6 / 20.6, 8192 x 128 (32) 21.4 / 22.7, 16384 x 128 (64) 26.7 /
-// 24.5.
-static bool pass_reduces(int nw, int G, int j) {
+// 24.5; 16 wavefronts, FP64 streams of 500 columns, 2111 rows (17) 36.9 / 37.3,
+// 2560 (20) 37.3 / 37.5, 3072 (24) 38.2 / 37.7, 4096 (32) 39.4 / 38.0, FP32 2111
+// rows 34.7 / 35.1, 3072 35.5 / 35.2, 4096 36.3 / 35.5; up to 320 columns the line
+// is later (3072 x 320 FP64, 24 sums for the last 64 pushes, 28.7 / 28.8).
+bool pass_reduces(int nw, int G, int j) {
   const int R = (j + 63) / 64;
   if (R > nw) return false;
-  const int S = nw / R;
-  return (G + S - 1) / S <= (nw == 16 ? 16 : 32);
+  const int S = red_slices(nw, R);
+  return (G + S - 1) / S <= (nw == 16 ? (j <= 320 ? 24 : 20) : 32);
 }
 
 // Launch one row pass, bracketed by timing events when profiling is on.

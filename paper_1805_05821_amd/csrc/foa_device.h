@@ -247,7 +247,7 @@ __device__ __forceinline__ void reduce_prologue(const PassArgs &a, double *s_c, 
   const int R = (j + 63) / 64;  // column chunks, at most NW
   // row slices: a power of two; slice sl takes the rows g with g % 64 in
   // [sl * 64 / S, (sl + 1) * 64 / S), summed as reduce_body's butterfly sums them
-  const int S = NW >= 16 * R ? 16 : (NW >= 8 * R ? 8 : (NW >= 4 * R ? 4 : (NW >= 2 * R ? 2 : 1)));
+  const int S = red_slices(NW, R);
   const int sl = wave / R, c = (wave - sl * R) * 64 + lane;
   const int width = 64 / S;
   double t = 0.0;

@@ -84,6 +84,12 @@ struct PassArgs {
   double *xn2;          // pass B: ||psi||^2
 };
 
+// Passes that reduce the preceding pass's sums: row slices of nw wavefronts over R
+// chunks of 64 columns (a power of two, at most 16).
+__host__ __device__ constexpr int red_slices(int nw, int R) {
+  return nw >= 16 * R ? 16 : (nw >= 8 * R ? 8 : (nw >= 4 * R ? 4 : (nw >= 2 * R ? 2 : 1)));
+}
+bool pass_reduces(int nw, int G, int j);
 // Widest basis (columns before the push) of the one-workgroup finalize that
 // also forms the next push's partial beta column.
 constexpr int kFinNextCols = 255;

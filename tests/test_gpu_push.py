@@ -398,3 +398,19 @@ def test_basis_copies_at_any_alignment(prec):
                 want[off:off + ncols * ld].view(ncols, ld)[:, :nr] = full[:, r0:r0 + nr]
                 assert torch.equal(buf, want), (dt, ncols, r0, nr, ld, off)
     g["stream"].close()
+
+
+@pytest.mark.parametrize("prec,n,N", [
+    # FP64: workgroups up to which the passes reduce: 128 (4 wavefronts to 64
+    # columns, 8 to 128), 64 to 256 columns, 48 to 320, 40 beyond
+    ("f64", 64 * 128 - 3, 66), ("f64", 64 * 129 + 1, 40),
+    ("f64", 64 * 64, 140), ("f64", 64 * 65 - 1, 140),
+    ("f64", 64 * 48 - 5, 262), ("f64", 64 * 49, 262), ("f64", 64 * 41, 326),
+    # FP32: 128 to 64 columns, 64 to 256, 32 to 320, 40 beyond
+    ("f32", 64 * 64 + 1, 70), ("f32", 64 * 32, 262), ("f32", 64 * 33 - 7, 262),
+    ("f32", 64 * 40 - 5, 326), ("f32", 64 * 41, 326),
+])
+def test_reduction_lines(prec, n, N):
+    """Both sides of every line between sums reduced in the passes and reduce
+    kernels, against the oracle as above."""
+    test_small_stream_reductions(prec, n, N)
