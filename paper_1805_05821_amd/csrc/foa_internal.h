@@ -331,11 +331,12 @@ int pass_qw(bool tv_f64, int nw, int j);
 int tile_slot(int qw);
 
 // one-reduction form
-// wavefronts per sweep workgroup (nw_opt 16: sixteen above 128 columns, FP32 basis)
-int ls_nw(bool tv_f64, int q, int nw_opt);
-int ls_qw(bool tv_f64, int q, int nw_opt);
+// wavefronts per sweep workgroup at q final columns and P panels (nw_opt 16: sixteen
+// above 128 columns, FP32 basis), column groups of each
+int ls_nw(bool tv_f64, int q, int nw_opt, int64_t P);
+int ls_qw(bool tv_f64, int q, int nw_opt, int64_t P);
 bool ls_supported(bool tv_f64, int q);
-int ls_occupancy(bool tv_f64, bool tx_f64, int q, int nw_opt);
+int ls_occupancy(bool tv_f64, bool tx_f64, int q, int nw_opt, int64_t P);
 hipError_t launch_ls_pass(bool tv_f64, bool tx_f64, int q, int nw_opt, int grid, const LsArgs &a, hipStream_t s);
 hipError_t launch_ls_reduce(const LsSmall &a, hipStream_t s);
 hipError_t launch_ls_finalize(const LsSmall &a, hipStream_t s);

@@ -65,10 +65,10 @@ int ls_grid(foa_ctx_s *c, int q, bool x64) {
   int g = c->grid_opt;
   if (g <= 0) {
     const bool v64 = c->prec == FOA_PREC_F64;
-    const int nw = ls_nw(v64, q, c->ls_nw_opt), qw = ls_qw(v64, q, c->ls_nw_opt);
+    const int nw = ls_nw(v64, q, c->ls_nw_opt, c->L.P), qw = ls_qw(v64, q, c->ls_nw_opt, c->L.P);
     const int ni = nw == 4 ? 0 : (nw == 8 ? 1 : 2);
     int &occ = c->ls_occ[v64 ? 1 : 0][x64 ? 1 : 0][ni][qw];
-    if (occ <= 0) occ = ls_occupancy(v64, x64, q, c->ls_nw_opt);
+    if (occ <= 0) occ = ls_occupancy(v64, x64, q, c->ls_nw_opt, c->L.P);
     g = std::max(c->grid_auto, occ * c->cus);
   }
   g = std::min<int64_t>({(int64_t)g, (int64_t)c->L.ldg, c->L.P});

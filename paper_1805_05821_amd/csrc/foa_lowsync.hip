@@ -59,20 +59,29 @@ namespace foa {
 // prefetch half; a tile's registers are refilled for the unit after next as
 // phase 2 is done with them, the next unit's row inputs ahead of them.  The three
 // columns go out 64 rows at a time.
-// Bound: HBM, with three column writes per panel in the read stream.
+// Bound: HBM, with three column writes per panel in the read stream.  FP32 basis,
+// capacity 500, us per push at 2^21 / 2^22 rows: 225-256 columns 378 / 732, 449-480
+// 664 / 1302 (with a 16-group tile 697 / 1357).
 // ---------------------------------------------------------------------------
+// 16-byte loads of a lane per column group and unit: two for the narrow tiles of an
+// FP64 basis, whose units are then whole panels (fewer barriers per row, columns
+// written 512 bytes at a time; 2^22 rows, 1-16 columns 175 -> 114 us per push, 17-32
+// 219 -> 189; the 4-group tile has no registers for it).
+template <typename TV, int NW, int QW>
+constexpr int ls_loads() {
+  return sizeof(TV) == 8 && QW <= 2 ? 2 : 1;
+}
 template <typename TV, int NW, int QW>
 constexpr int ls_lds_doubles() {
-  constexpr int BROWS = 16 * Vec<TV>::EPL;
+  constexpr int BROWS = 16 * Vec<TV>::EPL * ls_loads<TV, NW, QW>();
   return 2 * QW * NW * 4 + 2 * NW * BROWS * 2 + BROWS * 4 + 3 * BROWS + NW * LS_NSC +
          (QW >= 16 ? LS_NSC * BROWS : 0);
 }
-
 template <typename TV, typename TX, int NW, int QW>
 __device__ __forceinline__ void ls_pass_body(const LsArgs &a, int64_t pstart, int64_t pend_, int64_t pstep_,
                                              int slot, double *lds) {
 #pragma clang fp contract(off)
-  constexpr int EPL = Vec<TV>::EPL;
+  constexpr int LPL = Vec<TV>::EPL, EPL = LPL * ls_loads<TV, NW, QW>();  // elements of a load, of a lane
   constexpr int BROWS = 16 * EPL;
   constexpr int UPP = PANEL / BROWS;  // units per panel
   constexpr int JCAP = QW * NW * 4;
@@ -115,7 +124,8 @@ __device__ __forceinline__ void ls_pass_body(const LsArgs &a, int64_t pstart, in
   const unsigned tile_bytes = (unsigned)(q * PANEL * sizeof(TV));
   const bool uact = lane < RPW;
   const int urow = wave * RPW + (lane & (RPW - 1));
-  const int upos = (urow % EPL) * 16 + urow / EPL;  // its place in the tile's row order
+  // its place in the tile's row order
+  const int upos = (urow / (16 * LPL) * LPL + urow % LPL) * 16 + urow % (16 * LPL) / LPL;
   const unsigned pan_bytes = (unsigned)((size_t)a.n_max * PANEL * sizeof(TV));
   // byte offsets of the pending columns inside a panel (kOOR: absent)
   const unsigned ocu = hu ? (unsigned)(cc * PANEL * sizeof(TV)) : kOOR;
@@ -151,7 +161,14 @@ __device__ __forceinline__ void ls_pass_body(const LsArgs &a, int64_t pstart, in
     return make_rsrc(Wb + (size_t)(v / UPP) * pbytes + half, u < pend && bytes > half ? bytes - half : 0u);
   };
   auto load_group = [&](const __amdgpu_buffer_rsrc_t &r, int g, TV (&dst)[EPL]) {
-    unpack16<TV>(__builtin_amdgcn_raw_buffer_load_b128(r, (int)goff0, (int)(g * GBYTES), kTileLoad), dst);
+#pragma unroll
+    for (int h = 0; h < EPL / LPL; ++h) {
+      TV v[LPL];
+      unpack16<TV>(__builtin_amdgcn_raw_buffer_load_b128(
+                       r, (int)(goff0 + h * 16 * LPL * sizeof(TV)), (int)(g * GBYTES), kTileLoad), v);
+#pragma unroll
+      for (int e = 0; e < LPL; ++e) dst[h * LPL + e] = v[e];
+    }
   };
   TV yu, yf;
   TX xr;
@@ -173,8 +190,9 @@ __device__ __forceinline__ void ls_pass_body(const LsArgs &a, int64_t pstart, in
     double s[2][EPL];
 #pragma unroll
     for (int e = 0; e < EPL; ++e) s[0][e] = s[1][e] = 0.0;
-    // coefficients of group g + CD are read while group g's products run
-    constexpr int CD = QW >= 14 ? 0 : (QW >= 8 ? 1 : 2);
+    // coefficients of group g + CD are read while group g's products run (read next
+    // to their use, 385-416 columns of an FP32 basis took 2% longer)
+    constexpr int CD = QW >= 8 ? 1 : 2;
     double cw[CD + 1][2];
     auto read_cf = [&](int g) {
 #pragma unroll
@@ -312,6 +330,203 @@ __device__ __forceinline__ void ls_pass_body(const LsArgs &a, int64_t pstart, in
   }
 }
 
+// ---------------------------------------------------------------------------
+// Sweep of an FP64 basis for the sizes that ls_rows names (k_ls_rows): the row
+// passes' tile (8 wavefronts, a 16-byte load of 32 lanes covers a column's 64 rows,
+// QW groups of two columns per wavefront), vector FMAs in both phases, the next
+// panel's tile one panel ahead.  An FP64 basis has two right-hand sides in phase 2,
+// for which the four of the matrix form bring nothing, and here a wavefront reads
+// 1 KiB in one piece where the matrix tile takes 256 bytes of four columns.  Bound:
+// HBM; 2^22 rows, capacity 250: 113-128 columns 702 us per push (matrix form 735),
+// 225-249 1291 us (1386).
+// ---------------------------------------------------------------------------
+template <int QW>
+constexpr int ls_rows_lds_doubles() {
+  return 2 * QW * 16 + 4 * 8 * PANEL + 2 * PANEL + 8 * LS_NSC;
+}
+
+template <typename TX, int QW>
+__device__ __forceinline__ void ls_rows_body(const LsArgs &a, int slot, double *lds) {
+#pragma clang fp contract(off)
+  constexpr int NW = 8, EPL = 2, LPC = 32, CPW = 2;
+  constexpr int JCAP = QW * NW * CPW;
+  constexpr int RPW = PANEL / NW;
+  constexpr int GSTRIDE = NW * CPW;
+  double (*s_coef)[JCAP] = reinterpret_cast<double (*)[JCAP]>(lds);
+  double (*s_red)[2][NW][PANEL] = reinterpret_cast<double (*)[2][NW][PANEL]>(lds + 2 * JCAP);
+  double *s_u = lds + 2 * JCAP + 4 * NW * PANEL;
+  double *s_x = s_u + PANEL;
+  double (*s_sc)[LS_NSC] = reinterpret_cast<double (*)[LS_NSC]>(s_x + PANEL);
+
+  const DevState *st = a.st;
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int cs = lane / LPC;
+  const int rg = lane % LPC;
+
+  // step state (uniform), as in ls_pass_body
+  const int q = uniform(st->q);
+  const int hu = uniform(st->ls_u);
+  const int hf = uniform(st->ls_x);
+  const int hn = a.flush ? 0 : 1;
+  const int cc = q, cf = q + hu, cn = cf + hf;
+  const double cq = hu && hf ? uniform(st->ls_cq) : 0.0;
+
+  for (int c = tid; c < JCAP; c += NW * 64) {
+    s_coef[0][c] = c < q ? a.coefW[c] : 0.0;
+    s_coef[1][c] = c < q ? a.coefZ[c] : 0.0;
+  }
+  __syncthreads();
+
+  const int cbase = wave * CPW + cs;
+  const unsigned goff0 = (unsigned)((wave * CPW * PANEL + lane * EPL) * 8);
+  constexpr unsigned GBYTES = (unsigned)(GSTRIDE * PANEL * 8);
+  const unsigned tile_bytes = (unsigned)(q * PANEL * 8);
+  const bool uact = lane < RPW;
+  const int urow = wave * RPW + (lane % RPW);
+  const unsigned pan_bytes = (unsigned)((size_t)a.n_max * PANEL * 8);
+  // per-row offsets of the pending columns inside a panel (kOOR: absent)
+  const unsigned ocu = uact && hu ? (unsigned)((cc * PANEL + urow) * 8) : kOOR;
+  const unsigned ocf = uact && hf ? (unsigned)((cf * PANEL + urow) * 8) : kOOR;
+  const unsigned ocn = uact && hn ? (unsigned)((cn * PANEL + urow) * 8) : kOOR;
+
+  double acc0[QW], acc1[QW], sc[LS_NSC];
+#pragma unroll
+  for (int g = 0; g < QW; ++g) acc0[g] = acc1[g] = 0.0;
+#pragma unroll
+  for (int k = 0; k < LS_NSC; ++k) sc[k] = 0.0;
+
+  char *Wb = static_cast<char *>(a.W);
+  const size_t pbytes = (size_t)a.n_max * PANEL * 8;
+  double t[QW][EPL], tn[QW][EPL];
+  auto load_tile = [&](int64_t p, double (&dst)[QW][EPL], unsigned bytes) {
+    const __amdgpu_buffer_rsrc_t rt = make_rsrc(Wb + (size_t)p * pbytes, bytes);
+#pragma unroll
+    for (int g = 0; g < QW; ++g)
+      unpack16<double>(__builtin_amdgcn_raw_buffer_load_b128(rt, (int)goff0, (int)(g * GBYTES), kTileLoad), dst[g]);
+  };
+  auto hold = [&](double (&v)[QW][EPL]) {
+#pragma unroll
+    for (int g = 0; g < QW; ++g)
+#pragma unroll
+      for (int e = 0; e < EPL; ++e) asm volatile("" : "+v"(v[g][e]));
+  };
+
+  int64_t p = blockIdx.x;
+  const int64_t pend = a.P, pstep = gridDim.x;
+  if (p < pend) {
+    load_tile(p, t, tile_bytes);
+    hold(t);
+  }
+  int par = 0;
+  for (; p < pend; p += pstep) {
+    // per-row inputs, ahead of the next tile's loads
+    const __amdgpu_buffer_rsrc_t rp = make_rsrc(Wb + (size_t)p * pbytes, pan_bytes);
+    const double yu = buf_load_scalar<double>(rp, ocu);
+    const double yf = buf_load_scalar<double>(rp, ocf);
+    const int64_t rem = a.n - p * PANEL;
+    const unsigned xb = hn ? (unsigned)((rem >= PANEL ? PANEL : (rem > 0 ? rem : 0)) * sizeof(TX)) : 0u;
+    const double xv =
+        buf_load_scalar<TX>(make_rsrc(static_cast<const TX *>(a.x) + (hn ? p * PANEL : 0), xb),
+                            uact ? (unsigned)(urow * sizeof(TX)) : kOOR);
+    const bool more = p + pstep < pend;
+    load_tile(more ? p + pstep : p, tn, more ? tile_bytes : 0u);
+
+    // phase 1: row sums of the tile against sigma o w and sigma o z
+    double u[2][EPL];
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) u[0][e] = u[1][e] = 0.0;
+#pragma unroll
+    for (int g = 0; g < QW; ++g)
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        const double cf_ = s_coef[k][cbase + g * GSTRIDE];
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) u[k][e] = fma(t[g][e], cf_, u[k][e]);
+      }
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+#pragma unroll
+      for (int e = 0; e < EPL; ++e) {
+        u[k][e] = xor_sum<32>(u[k][e]);
+      }
+    // stores of their own: beside the sums they cost the 16-group tile 144 bytes of
+    // scratch a lane
+    if (cs == 0) {
+#pragma unroll
+      for (int k = 0; k < 2; ++k)
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) s_red[par][k][wave][rg * EPL + e] = u[k][e];
+    }
+    __syncthreads();
+    double sw = 0.0, sz = 0.0;
+#pragma unroll
+    for (int w2 = 0; w2 < NW; ++w2) {
+      sw += s_red[par][0][w2][urow];
+      sz += s_red[par][1][w2][urow];
+    }
+    // row update: finished column, formed column, snapshot copy
+    const double ut = yu - sw;
+    const double uf = (yf - sz) - ut * cq;
+    buf_store_scalar<double>(ut, rp, ocu);
+    buf_store_scalar<double>(uf, rp, ocf);
+    buf_store_scalar<double>(xv, rp, ocn);
+    if (uact) {
+      sc[LS_UU] = fma(ut, ut, sc[LS_UU]);
+      sc[LS_UF] = fma(ut, uf, sc[LS_UF]);
+      sc[LS_UX] = fma(ut, xv, sc[LS_UX]);
+      sc[LS_FF] = fma(uf, uf, sc[LS_FF]);
+      sc[LS_FX] = fma(uf, xv, sc[LS_FX]);
+      sc[LS_XX] = fma(xv, xv, sc[LS_XX]);
+      s_u[urow] = uf;
+      s_x[urow] = xv;
+    }
+    __syncthreads();
+    // phase 2: column sums of the tile against the formed column and the snapshot
+    double wu[EPL], wx[EPL];
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) {
+      wu[e] = s_u[rg * EPL + e];
+      wx[e] = s_x[rg * EPL + e];
+    }
+#pragma unroll
+    for (int g = 0; g < QW; ++g)
+#pragma unroll
+      for (int e = 0; e < EPL; ++e) {
+        acc0[g] = fma(t[g][e], wu[e], acc0[g]);
+        acc1[g] = fma(t[g][e], wx[e], acc1[g]);
+      }
+    hold(tn);
+#pragma unroll
+    for (int g = 0; g < QW; ++g)
+#pragma unroll
+      for (int e = 0; e < EPL; ++e) t[g][e] = tn[g][e];
+    par ^= 1;
+  }
+
+#pragma unroll
+  for (int g = 0; g < QW; ++g) {
+    const double v0 = lanes_sum<LPC>(acc0[g]), v1 = lanes_sum<LPC>(acc1[g]);
+    const int c = cbase + g * GSTRIDE;
+    if (rg == 0 && c < q) {
+      a.part0[(size_t)c * a.ldg + slot] = v0;
+      a.part1[(size_t)c * a.ldg + slot] = v1;
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < LS_NSC; ++k) {
+    const double v = lanes_sum<64>(sc[k]);
+    if (lane == 0) s_sc[wave][k] = v;
+  }
+  __syncthreads();
+  if (tid < LS_NSC) {
+    double v = 0.0;
+    for (int w2 = 0; w2 < NW; ++w2) v += s_sc[w2][tid];
+    a.part1[(size_t)(a.n_max + tid) * a.ldg + slot] = v;
+  }
+}
+
 // Sweeps run while the stream is active; flush sweeps also after a
 // non-finite snapshot stopped it (the snapshots before it are completed).
 __device__ __forceinline__ bool ls_runs(const DevState *st, int flush) {
@@ -332,6 +547,14 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ls_wave
   if (a.flush && !a.st->ls_u && !a.st->ls_x) return;
   __shared__ double lds[ls_lds_doubles<TV, NW, QW>()];
   ls_pass_body<TV, TX, NW, QW>(a, blockIdx.x, a.P, gridDim.x, blockIdx.x, lds);
+}
+
+template <typename TX, int QW>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(QW <= 4 ? 4 : 2))) void k_ls_rows(LsArgs a) {
+  if (!ls_runs(a.st, a.flush)) return;
+  if (a.flush && !a.st->ls_u && !a.st->ls_x) return;
+  __shared__ double lds[ls_rows_lds_doubles<QW>()];
+  ls_rows_body<TX, QW>(a, blockIdx.x, lds);
 }
 
 // ---------------------------------------------------------------------------
@@ -652,17 +875,30 @@ __global__ __launch_bounds__(512) void k_ls_finalize(LsSmall a) { ls_finalize_bo
 // Tile shapes: the narrowest tile of 4 wavefronts that covers the final columns
 // (up to 16 groups, 256 columns), 8 wavefronts beyond; option ls_nw = 16: sixteen
 // for 129-256 columns of an FP32 basis.
-int ls_nw(bool tv_f64, int q, int nw_opt) {
+//
+// An FP64 basis takes k_ls_rows (8 wavefronts) where that is the faster one: at
+// 33-64 columns, at 97-128 from 65536 rows on, and beyond 128 from 524288 rows on.
+// Pushes of a stream, time of k_ls_pass over that of k_ls_rows: 33-64 columns 1.01
+// - 1.16 at 3000 .. 2^22 rows; 65-96 0.91 - 1.02; 97-128 0.93 at 20000 rows, 0.99 at
+// 50000, 1.02 at 100037, 1.08 at 2^21; 129-160 0.95 at 300007, 1.03 at 2^20;
+// 225-256 0.98 at 100037, 1.09 at 300007, 1.12 at 2^21.
+static bool ls_rows(bool tv_f64, int q, int64_t P) {
+  return tv_f64 && (q > 128 ? P >= 8192 : (q > 96 ? P >= 1024 : q > 32 && q <= 64));
+}
+
+int ls_nw(bool tv_f64, int q, int nw_opt, int64_t P) {
+  if (ls_rows(tv_f64, q, P)) return 8;
   if (!tv_f64 && nw_opt == 16 && q > 128 && q <= 256) return 16;
   return q <= 256 ? 4 : 8;
 }
 
-int ls_qw(bool tv_f64, int q, int nw_opt) {
-  static const int qs[] = {1, 2, 4, 6, 8, 10, 12, 14, 16};
-  const int nw = ls_nw(tv_f64, q, nw_opt);
+int ls_qw(bool tv_f64, int q, int nw_opt, int64_t P) {
+  static const int qs[] = {1, 2, 4, 6, 8, 10, 12, 14, 15, 16};
+  if (ls_rows(tv_f64, q, P)) return q <= 64 ? 4 : (q <= 128 ? 8 : 16);
+  const int nw = ls_nw(tv_f64, q, nw_opt, P);
   if (nw == 16) return 4;
   for (int w : qs)
-    if (nw * w * 4 >= q && (nw == 4 || w >= 10)) return w;
+    if (nw * w * 4 >= q && (nw == 4 ? w != 15 : w >= 10)) return w;
   return 16;
 }
 
@@ -675,7 +911,6 @@ static const void *ls_fn(int nw, int qw) {
   switch (nw * 100 + qw) {
     FOA_LS(4, 1)
     FOA_LS(4, 2)
-    FOA_LS(4, 4)
     FOA_LS(4, 6)
     FOA_LS(4, 8)
     FOA_LS(4, 10)
@@ -686,11 +921,13 @@ static const void *ls_fn(int nw, int qw) {
       if constexpr (sizeof(TV) == 4) return reinterpret_cast<const void *>(&k_ls_pass<TV, TX, 16, 4>);
       return nullptr;
   }
-  if constexpr (sizeof(TV) == 4) {  // an FP64 basis holds at most 256 final columns
+  if constexpr (sizeof(TV) == 4) {  // an FP64 basis holds at most 256 final columns (33-64: k_ls_rows)
     switch (nw * 100 + qw) {
+      FOA_LS(4, 4)
       FOA_LS(8, 10)
       FOA_LS(8, 12)
       FOA_LS(8, 14)
+      FOA_LS(8, 15)
       FOA_LS(8, 16)
     }
   }
@@ -698,8 +935,15 @@ static const void *ls_fn(int nw, int qw) {
   return nullptr;
 }
 
-static const void *ls_kernel(bool tv_f64, bool tx_f64, int q, int nw_opt) {
-  const int nw = ls_nw(tv_f64, q, nw_opt), qw = ls_qw(tv_f64, q, nw_opt);
+template <typename TX>
+static const void *ls_rows_fn(int qw) {  // covers 16 qw columns
+  if (qw == 4) return reinterpret_cast<const void *>(&k_ls_rows<TX, 4>);
+  return qw == 8 ? reinterpret_cast<const void *>(&k_ls_rows<TX, 8>) : reinterpret_cast<const void *>(&k_ls_rows<TX, 16>);
+}
+
+static const void *ls_kernel(bool tv_f64, bool tx_f64, int q, int nw_opt, int64_t P) {
+  const int nw = ls_nw(tv_f64, q, nw_opt, P), qw = ls_qw(tv_f64, q, nw_opt, P);
+  if (ls_rows(tv_f64, q, P)) return tx_f64 ? ls_rows_fn<double>(qw) : ls_rows_fn<float>(qw);
   if (qw * nw * 4 < q) return nullptr;  // tile narrower than the basis
   if (tv_f64) return tx_f64 ? ls_fn<double, double>(nw, qw) : ls_fn<double, float>(nw, qw);
   return tx_f64 ? ls_fn<float, double>(nw, qw) : ls_fn<float, float>(nw, qw);
@@ -707,16 +951,16 @@ static const void *ls_kernel(bool tv_f64, bool tx_f64, int q, int nw_opt) {
 
 hipError_t launch_ls_pass(bool tv_f64, bool tx_f64, int q, int nw_opt, int grid, const LsArgs &a, hipStream_t s) {
   if (!ls_supported(tv_f64, q)) return hipErrorInvalidValue;
-  const void *f = ls_kernel(tv_f64, tx_f64, q, nw_opt);
+  const void *f = ls_kernel(tv_f64, tx_f64, q, nw_opt, a.P);
   if (!f) return hipErrorInvalidValue;
   void *args[] = {const_cast<LsArgs *>(&a)};
-  return hipLaunchKernel(f, dim3(grid), dim3(64 * ls_nw(tv_f64, q, nw_opt)), args, 0, s);
+  return hipLaunchKernel(f, dim3(grid), dim3(64 * ls_nw(tv_f64, q, nw_opt, a.P)), args, 0, s);
 }
 
-int ls_occupancy(bool tv_f64, bool tx_f64, int q, int nw_opt) {
+int ls_occupancy(bool tv_f64, bool tx_f64, int q, int nw_opt, int64_t P) {
   int nb = 0;
-  const void *f = ls_kernel(tv_f64, tx_f64, q, nw_opt);
-  if (!f || hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, f, 64 * ls_nw(tv_f64, q, nw_opt), 0) != hipSuccess)
+  const void *f = ls_kernel(tv_f64, tx_f64, q, nw_opt, P);
+  if (!f || hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, f, 64 * ls_nw(tv_f64, q, nw_opt, P), 0) != hipSuccess)
     return 1;
   return nb > 0 ? nb : 1;
 }

@@ -344,3 +344,47 @@ def test_sweep_tiles(prec, n, N):
     # is eps kappa at worst for these data
     assert eH <= 10 * eps * kap * np.sqrt(q) and orth <= 10 * np.sqrt(q) * eps * kap
     g["stream"].close()
+
+
+@pytest.mark.parametrize("n,N", [
+    (64 * 1023, 130), (64 * 1023 + 1, 130),     # 97-128 columns: matrix sweep, row sweep
+    (64 * 8191, 257), (64 * 8191 + 1, 257),     # beyond 128
+])
+def test_wide_f64_sweeps(n, N):
+    """An FP64 basis on both sides of the sizes where its sweep changes form, the last
+    panel full and with one row: against the three-sweep form of the same Gaussian
+    snapshots (kappa_2 < 3; each within the bound of test_sweep_tiles), its
+    orthogonality and its factorisation."""
+    import torch
+
+    from paper_1805_05821_amd.stream import FOAStream
+
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n + N)
+    X = torch.randn((N, n), generator=gen, device="cuda", dtype=torch.float32)
+    out = {}
+    for form in ("one_reduction", "cgs2"):
+        s = FOAStream(n, N, prec="f64", breakdown_tol=0.0, ws_fill=0xFF, form=form)
+        s.push_all(X)
+        st, q = s.sync()
+        assert q == N
+        out[form] = s.state()[:2]
+        if form == "one_reduction":
+            V = s.basis(N)
+            B = torch.from_numpy(np.ascontiguousarray(out[form][1][:N, :N])).cuda()
+            # in chunks of rows: one product sums n terms in turn and is off by more
+            # than the basis (about sqrt(n) eps)
+            G = -torch.eye(N, device="cuda", dtype=torch.float64)
+            for r0 in range(0, n, 1024):
+                G += V[:, r0:r0 + 1024] @ V[:, r0:r0 + 1024].T
+            orth = float(torch.linalg.matrix_norm(G, 2))
+            fact = float(torch.linalg.norm(X.double() - B.T @ V) / torch.linalg.norm(X.double()))
+            del V
+        s.close()
+    m = N - 1
+    kap = kappa_of(out["cgs2"][1][:m, :m])
+    H, R = out["one_reduction"][0][:m, :m], out["cgs2"][0][:m, :m]
+    eH = np.linalg.norm(H - R, 2) / np.linalg.norm(R, 2)
+    announce(f"f64 {n} x {N}: kappa={kap:.1e} relH2={eH:.1e} orth={orth:.1e} fact={fact:.1e}")
+    assert eH <= 2 * 10 * EPS64 * kap * np.sqrt(N)
+    assert orth <= 10 * np.sqrt(N) * EPS64 * kap and fact <= 10 * np.sqrt(N) * EPS64 * kap
