@@ -60,20 +60,21 @@ __global__ __launch_bounds__(256) void k_nextb(SmallArgs a) { nextb_body(a, bloc
 __global__ __launch_bounds__(256) void k_init_state(SmallArgs a, double tol) { init_state_body(a, tol); }
 
 // Basis columns out of the panel layout: VEC consecutive rows of CU columns per
-// thread, so a wavefront has CU loads of 64 VEC rows in flight and stores that
-// many rows of a column at once.  VEC = 16 bytes of the basis where the caller's
-// rows and columns are aligned to it, else 1 (four columns in flight are what a
-// row at a time needs as well).  Bound: HBM, half of it writes (a plain copy runs
-// at 4.7 TB/s); 2^22 x 500 FP32, one element per thread: 5.4 ms, 3.1 TB/s.
-constexpr int CU = 4;
-template <typename TV, typename TO, int VEC>
+// thread, 256 VEC rows of a column per workgroup.  Where the caller's rows and
+// columns are aligned to it, VEC is 16 bytes of the basis and a column at a time is
+// enough; else a row at a time, four columns in flight.  Bound: HBM, half of it
+// writes (a plain copy runs at 4.7 TB/s); those of an unaligned column end inside a
+// line, so they go out in long pieces.  2^20 x 100, us, FP32 to FP32 / FP64 to FP64:
+// aligned 158 / 311 (64 threads along the rows, four columns each, 163 / 339; an
+// element per thread 259 / 334), 2^20 + 1 rows 185 / 337 (249 / 431; 270 / 347).
+template <typename TV, typename TO, int VEC, int CU>
 __global__ __launch_bounds__(256) void k_copy_basis(const TV *W, const double *sigma, int64_t r0, int64_t nrows,
                                                     int n_max, int ncols, TO *out, int64_t ld) {
   typedef TV tv __attribute__((ext_vector_type(VEC)));
   typedef TO to __attribute__((ext_vector_type(VEC)));
-  const int64_t i = ((int64_t)blockIdx.x * 64 + (threadIdx.x & 63)) * VEC;
-  const int c0 = ((int)blockIdx.y * 4 + (int)(threadIdx.x >> 6)) * CU;
-  if (i >= nrows || c0 >= ncols) return;
+  const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * VEC;
+  const int c0 = (int)blockIdx.y * CU;
+  if (i >= nrows) return;
   const int64_t r = r0 + i;  // VEC rows from r lie in one panel
   const TV *src = W + (size_t)(r / PANEL) * n_max * PANEL + r % PANEL;
   tv v[CU];
@@ -307,13 +308,13 @@ static hipError_t copy_basis_t(const void *W, const double *sigma, int64_t r0, i
                                void *out, int64_t ld, hipStream_t s) {
   constexpr int VEC = Vec<TV>::EPL;
   const bool vec = r0 % VEC == 0 && ld % VEC == 0 && reinterpret_cast<uintptr_t>(out) % (VEC * sizeof(TO)) == 0;
-  const int rows = 64 * (vec ? VEC : 1);
-  const dim3 grid((unsigned)((nrows + rows - 1) / rows), (unsigned)((ncols + 4 * CU - 1) / (4 * CU)));
+  const int rows = 256 * (vec ? VEC : 1), cu = vec ? 1 : 4;
+  const dim3 grid((unsigned)((nrows + rows - 1) / rows), (unsigned)((ncols + cu - 1) / cu));
   if (vec)
-    hipLaunchKernelGGL((k_copy_basis<TV, TO, VEC>), grid, dim3(256), 0, s, (const TV *)W, sigma, r0, nrows, n_max, ncols,
+    hipLaunchKernelGGL((k_copy_basis<TV, TO, VEC, 1>), grid, dim3(256), 0, s, (const TV *)W, sigma, r0, nrows, n_max, ncols,
                        (TO *)out, ld);
   else
-    hipLaunchKernelGGL((k_copy_basis<TV, TO, 1>), grid, dim3(256), 0, s, (const TV *)W, sigma, r0, nrows, n_max, ncols,
+    hipLaunchKernelGGL((k_copy_basis<TV, TO, 1, 4>), grid, dim3(256), 0, s, (const TV *)W, sigma, r0, nrows, n_max, ncols,
                        (TO *)out, ld);
   return hipGetLastError();
 }

@@ -414,3 +414,28 @@ def test_reduction_lines(prec, n, N):
     """Both sides of every line between sums reduced in the passes and reduce
     kernels, against the oracle as above."""
     test_small_stream_reductions(prec, n, N)
+
+
+@pytest.mark.parametrize("prec", ["f32", "f64"])
+def test_basis_copies_over_workgroups(prec):
+    """Copies of more rows than a workgroup takes (256 at a time, 512 or 1024 where
+    aligned): the first rows and columns of the next one, aligned and not."""
+    import torch
+
+    from paper_1805_05821_amd import foa as F
+
+    n, N = 2100, 9
+    g = run_gpu(np.random.default_rng(2).standard_normal((n, N)), prec, tol=0.0)
+    ctx = g["stream"].ctx
+    for dt, code in ((torch.float32, F.FOA_F32), (torch.float64, F.FOA_F64)):
+        full = torch.from_numpy(np.ascontiguousarray(g["V"].T)).to(device="cuda", dtype=dt)
+        for ncols in (1, 4, 5, N):
+            for r0, nr, ld, off in ((0, n, n, 0), (0, n, n + 1, 0), (4, 1024, 1024, 0), (4, 1025, 1028, 0),
+                                    (8, 512, 512, 0), (8, 513, 516, 0), (1, 256, 256, 0), (1, 257, 257, 1)):
+                buf = torch.full((off + ncols * ld + 8,), 7.0, dtype=dt, device="cuda")
+                F.foa_copy_basis_rows(ctx, r0, nr, buf[off:], ld, code, ncols)
+                torch.cuda.synchronize()
+                want = torch.full_like(buf, 7.0)
+                want[off:off + ncols * ld].view(ncols, ld)[:, :nr] = full[:ncols, r0:r0 + nr]
+                assert torch.equal(buf, want), (dt, ncols, r0, nr, ld, off)
+    g["stream"].close()
