@@ -331,7 +331,8 @@ __device__ __forceinline__ void ls_pass_body(const LsArgs &a, int64_t pstart, in
 }
 
 // ---------------------------------------------------------------------------
-// Sweep of an FP64 basis for the sizes that ls_rows names (k_ls_rows): the row
+// Sweep of an FP64 basis for the sizes that ls_rows names (k_ls_rows) and in the
+// batched form (panels pstart, + pstep, ... < pend as in ls_pass_body): the row
 // passes' tile (8 wavefronts, a 16-byte load of 32 lanes covers a column's 64 rows,
 // QW groups of two columns per wavefront), vector FMAs in both phases, the next
 // panel's tile one panel ahead.  An FP64 basis has two right-hand sides in phase 2,
@@ -346,7 +347,8 @@ constexpr int ls_rows_lds_doubles() {
 }
 
 template <typename TX, int QW>
-__device__ __forceinline__ void ls_rows_body(const LsArgs &a, int slot, double *lds) {
+__device__ __forceinline__ void ls_rows_body(const LsArgs &a, int64_t pstart, int64_t pend, int64_t pstep, int slot,
+                                             double *lds) {
 #pragma clang fp contract(off)
   constexpr int NW = 8, EPL = 2, LPC = 32, CPW = 2;
   constexpr int JCAP = QW * NW * CPW;
@@ -373,6 +375,7 @@ __device__ __forceinline__ void ls_rows_body(const LsArgs &a, int slot, double *
   const int cc = q, cf = q + hu, cn = cf + hf;
   const double cq = hu && hf ? uniform(st->ls_cq) : 0.0;
 
+  __syncthreads();  // the previous call of this workgroup may still read LDS
   for (int c = tid; c < JCAP; c += NW * 64) {
     s_coef[0][c] = c < q ? a.coefW[c] : 0.0;
     s_coef[1][c] = c < q ? a.coefZ[c] : 0.0;
@@ -413,8 +416,7 @@ __device__ __forceinline__ void ls_rows_body(const LsArgs &a, int slot, double *
       for (int e = 0; e < EPL; ++e) asm volatile("" : "+v"(v[g][e]));
   };
 
-  int64_t p = blockIdx.x;
-  const int64_t pend = a.P, pstep = gridDim.x;
+  int64_t p = pstart;
   if (p < pend) {
     load_tile(p, t, tile_bytes);
     hold(t);
@@ -554,7 +556,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(QW <= 4 ? 4
   if (!ls_runs(a.st, a.flush)) return;
   if (a.flush && !a.st->ls_u && !a.st->ls_x) return;
   __shared__ double lds[ls_rows_lds_doubles<QW>()];
-  ls_rows_body<TX, QW>(a, blockIdx.x, lds);
+  ls_rows_body<TX, QW>(a, blockIdx.x, a.P, gridDim.x, blockIdx.x, lds);
 }
 
 // ---------------------------------------------------------------------------
@@ -1019,10 +1021,11 @@ __device__ __forceinline__ LsSmall ls_small_of(const BatchStream &d, int flush) 
   return a;
 }
 
-template <typename TV, typename TX, int NW, int QW, int BK>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ls_waves<TV, NW, QW>()))) void k_ls_pass_batch(
-    BatchArgs b) {
-  __shared__ double lds[ls_lds_doubles<TV, NW, QW>()];
+// ROWS: the sweep is ls_rows_body's (FP64 basis, NW = 8)
+template <typename TV, typename TX, int NW, int QW, int BK, bool ROWS>
+__global__ __launch_bounds__(NW * 64)
+    __attribute__((amdgpu_waves_per_eu(ROWS ? (QW <= 4 ? 4 : 2) : ls_waves<TV, NW, QW>()))) void k_ls_pass_batch(BatchArgs b) {
+  __shared__ double lds[ROWS ? ls_rows_lds_doubles<QW>() : ls_lds_doubles<TV, NW, QW>()];
   const int G = uniform(b.meta[2 * BK + 1]);
   if ((int)blockIdx.x >= G) return;
   const int cnt = uniform(b.meta[2 * BK]);
@@ -1053,7 +1056,11 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ls_wave
     a.n_max = uniform(d.n_max);
     a.ldg = uniform(d.ldg);
     a.flush = flush;
-    ls_pass_body<TV, TX, NW, QW>(a, lo - ps, e - ps, 1, (int)blockIdx.x - uniform(st->seg0), lds);
+    const int slot = (int)blockIdx.x - uniform(st->seg0);
+    if constexpr (ROWS)
+      ls_rows_body<TX, QW>(a, lo - ps, e - ps, 1, slot, lds);
+    else
+      ls_pass_body<TV, TX, NW, QW>(a, lo - ps, e - ps, 1, slot, lds);
     lo = e;
     ++i;
   }
@@ -1111,16 +1118,20 @@ __global__ __launch_bounds__(512) void k_ls_finalize_batch(BatchArgs b) {
 }
 
 // Kernel shape of bucket k (basis sizes up to 32, 64, 128, 256, 512 final
-// columns; an empty basis is in bucket 1): 1, 2, 4, 8, 8
-// wavefronts with 8, 8, 8, 8, 16 groups (an FP64 basis at most 256 columns).
+// columns; an empty basis is in bucket 1): 1, 2, 4, 8, 8 wavefronts with 8, 8, 8, 8,
+// 16 groups of four columns.  An FP64 basis (at most 256 columns) from 33 columns
+// on takes the row form, 8 wavefronts with 4, 8, 16 groups of two: 64 streams of
+// 2^12..2^18 rows and 20..250 columns 93.3 ms, from bucket 3 or 4 on 93.7 and 95.1,
+// the matrix form throughout 102.1; 24 streams of 1000..20000 rows 13.8 ms (14.5).
 bool ls_batch_supported(bool tv_f64, int k) { return k >= 1 && (!tv_f64 || k <= 4); }
 
 template <typename TV, typename TX, int BK>
 static const void *ls_batch_fn(int *nt) {
-  constexpr int NW = BK <= 1 ? 1 : (BK == 2 ? 2 : (BK == 3 ? 4 : 8));
-  constexpr int QW = BK == 5 ? 16 : 8;
+  constexpr bool ROWS = sizeof(TV) == 8 && BK >= 2;
+  constexpr int NW = BK <= 1 ? 1 : (ROWS ? 8 : (BK == 2 ? 2 : (BK == 3 ? 4 : 8)));
+  constexpr int QW = ROWS ? 2 << (BK - 1) : (BK == 5 ? 16 : 8);
   *nt = NW * 64;
-  return reinterpret_cast<const void *>(&k_ls_pass_batch<TV, TX, NW, QW, BK>);
+  return reinterpret_cast<const void *>(&k_ls_pass_batch<TV, TX, NW, QW, BK, ROWS>);
 }
 
 template <typename TV, typename TX>
