@@ -899,18 +899,20 @@ __global__ __launch_bounds__(kGramThreads) void k_bthird(BlockArgs a, int *gate,
 // Launchers
 // ---------------------------------------------------------------------------
 // Workgroup shape of the block passes over j columns (tiles of QW groups of
-// four columns on NW wavefronts) and its resident workgroups per CU.  The
-// narrowest tile that covers j, as the groups beyond it are arithmetic for
-// nothing; 4 wavefronts while their registers hold it (256 columns), 8 beyond,
-// which fill a CU.  The shape itself hardly matters: 2^22 rows, FP32, 8
-// wavefronts from 65 or 129 columns on instead of 4, 284.7 against 286.2 us per
-// snapshot at N = 256; 2, 3 or 4 workgroups per CU throughout 287.1, 290.7 and
-// 284.7 us, at 100037 x 200 39.0, 41.5 and 43.0 against 40.4 us.
+// four columns on NW wavefronts): 4 wavefronts while their registers hold it
+// (256 columns), 8 beyond, which fill a CU, and the narrowest tile that covers j,
+// as the groups beyond it are arithmetic for nothing.  With widths of 1, 2, 4, 8
+// and 16 groups alone: 2^22 x 500 FP32 230.7 ms (217.4 so), 2^22 x 256 67.8
+// (65.6), 300007 x 320 FP64 19.5 (19.0), 100037 x 200 5.07 (4.98).
+// Workgroups per CU: 4 up to 64 columns (2 take 12% longer, 1000003 x 30 FP64), 2 up
+// to 256 (100037 x 200 FP32 4.74 ms, with the 3 that the registers hold 4.96, with
+// 4 5.31; FP64 5.49, 5.72 and 5.98), 1 beyond (with 2, 30000 x 500 FP32 12.6 ms
+// instead of 11.8).
 BlockShape block_shape(int j) {
   static const int q4[] = {1, 2, 4, 6, 8, 10, 12, 14, 16}, q8[] = {10, 12, 14, 16};
   if (j <= 256) {
     for (int q : q4)
-      if (16 * q >= j) return {4, q, q <= 4 ? 4 : (q <= 8 ? 3 : 2)};
+      if (16 * q >= j) return {4, q, q <= 4 ? 4 : 2};
   }
   for (int q : q8)
     if (32 * q >= j) return {8, q, 1};

@@ -275,7 +275,7 @@ hipError_t launch_pass(int mode, bool tv_f64, bool tx_f64, bool prefetch, int nw
 // blocked form (foa_block.hip)
 struct BlockShape {
   int nw, qw;   // wavefronts per workgroup, groups of four columns per wavefront
-  int per_cu;   // workgroups a CU holds
+  int per_cu;   // workgroups launched per CU
 };
 BlockShape block_shape(int j);
 hipError_t launch_bpass(int mode, bool tv_f64, bool tx_f64, int grid, const BlockArgs &a, hipStream_t s);
