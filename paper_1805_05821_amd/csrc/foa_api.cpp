@@ -229,8 +229,6 @@ void release_events(foa_ctx_s *c) {
   c->ev_free.clear();
 }
 
-// Enqueue one push of snapshot x (Algorithm 1: the first-snapshot
-// normalisation for q = 0, else one iteration of its snapshot loop).
 // Pushes that one launch takes from here on (0: the kernels of enqueue_push): a
 // small stream with no kernel shape or grid asked for and no timing of the passes.
 static int small_run(const foa_ctx_s *c, int rem) {
@@ -271,6 +269,8 @@ static foa_status enqueue_small_run(foa_ctx_s *c, const void *x, int64_t ld, int
   return FOA_OK;
 }
 
+// Enqueue one push of snapshot x (Algorithm 1: the first-snapshot
+// normalisation for q = 0, else one iteration of its snapshot loop).
 foa_status enqueue_push(foa_ctx_s *c, const void *x, bool x_f64) {
   if (c->form == 1) return enqueue_ls_push(c, x, x_f64);
   if (small_run(c, 1)) return enqueue_small_run(c, x, 0, 1, x_f64);
@@ -319,7 +319,9 @@ foa_status enqueue_push(foa_ctx_s *c, const void *x, bool x_f64) {
     if ((e = timed_pass(c, PM_C, v64, x_f64, c->prefetch, G, pa, vbytes + nv * sV)) != hipSuccess)
       return hip_err(c, e, "pass C");
     // one workgroup up to 255 columns: FP64 2^20 x 200, finalize and next b of
-    // their own 4.8 + 9.4 us per push, together 5.5 us
+    // their own 4.8 + 9.4 us per push, together 5.5 us; beyond, it reads H_bar
+    // alone longer than a launch costs (together up to 511 columns, 20000 x 500 FP32
+    // 25.9 -> 27.8 ms, 3000 x 500 FP64 18.9 -> 19.7)
     if (j <= kFinNextCols) {
       if ((e = launch_finalize_next(sa, s)) != hipSuccess) return hip_err(c, e, "finalize");
     } else if ((e = launch_finalize(sa, s)) != hipSuccess) {

@@ -172,11 +172,6 @@ foa_status upload_config(foa_batch_s *b, int unit_panels) {
   return FOA_OK;
 }
 
-// All kernels of one step, enqueued on stream s (direct launches or capture).
-// Bucket mode: per pass one row-pass launch per tile bucket up to kmax, then
-// the reductions, finalize and next b.  Persistent mode (FP32 basis): the
-// streams of up to kPersistCols columns run in one persistent launch; first
-// pushes and wider bases take the bucket launches, which skip the others.
 // Most basis columns of a stream while bucket kmax is the widest in use.
 int step_cols(const foa_batch_s *b, int kmax) {
   const int cols = kmax < 1 ? 0 : batch_cols_per_qw(b->prec == FOA_PREC_F64) << (kmax - 1);
@@ -194,6 +189,12 @@ hipError_t enqueue_ls_step(foa_batch_s *b, bool x_f64, hipStream_t s, int kmax) 
   return launch_ls_batch_small(a, step_cols(b, kmax), s);
 }
 
+// All kernels of one step, enqueued on stream s (direct launches or capture).
+// Bucket mode: per pass one row-pass launch per tile bucket up to kmax, then
+// the reductions and finalize (with the next partial beta column).  Persistent
+// mode (FP32 basis): the
+// streams of up to kPersistCols columns run in one persistent launch; first
+// pushes and wider bases take the bucket launches, which skip the others.
 hipError_t enqueue_step(foa_batch_s *b, bool x_f64, hipStream_t s, int kmax) {
   if (b->form == 1) return enqueue_ls_step(b, x_f64, s, kmax);
   const bool v64 = b->prec == FOA_PREC_F64;

@@ -710,7 +710,7 @@ __global__ __launch_bounds__(kGramThreads) void k_bchol(BlockArgs a) {
 // ---------------------------------------------------------------------------
 // Sums over the old columns l < j-1 of H_bar[i, l] beta[l, j-1+k], k < BPK (beta's
 // new columns from the small area): 64 rows x 4 slices of the l range of one of
-// bh_slices(j) workgroups per row chunk, into partb[(slice * BPK + k) * 512 + i].
+// bh_slices(j) workgroups per row chunk, into partb[(slice * BPK + k) * kBhRows + i].
 // One workgroup per row chunk read all of H_bar through 8 CUs: 32 us at 250
 // columns.
 __host__ __device__ constexpr int bh_slices(int j) { return j < 128 ? 1 : (j < 512 ? j / 64 : 8); }

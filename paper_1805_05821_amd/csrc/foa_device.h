@@ -16,8 +16,6 @@ struct Vec {
 };
 
 
-__device__ __forceinline__ double xor_shfl(double v, int m) { return __shfl_xor(v, m, 64); }
-
 // v(lane) + v(lane ^ M) for M = 16 or 32 with the lane-swap VALU instructions
 // (no LDS traffic).  With both operands equal, the 32-swap returns the lower
 // half of the wave in both halves of one result and the upper half in both

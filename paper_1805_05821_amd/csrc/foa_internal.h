@@ -269,7 +269,7 @@ struct LsSmall {
 
 // ---- launchers (defined in foa_kernels.hip) --------------------------------
 // tv_f64: V stored in FP64; tx_f64: snapshot in FP64.
-// nw: wavefronts per workgroup for an FP32 basis (8 or 16; FP64 uses 16).
+// nw: wavefronts per workgroup (4, 8 or 16; see pass_nw).
 hipError_t launch_pass(int mode, bool tv_f64, bool tx_f64, bool prefetch, int nw, int grid,
                        const PassArgs &a, hipStream_t s);
 // blocked form (foa_block.hip)

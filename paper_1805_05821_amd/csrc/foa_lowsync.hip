@@ -31,7 +31,8 @@
 // Kernels (all on the context stream):
 //   k_ls_pass     : the sweep (tile layout of the blocked passes; two coefficient
 //                   vectors in phase 1, two or three right-hand sides in phase 2,
-//                   six scalar sums);
+//                   six scalar sums); k_ls_rows: its row form, where that is the
+//                   faster one for an FP64 basis;
 //   k_ls_reduce   : fixed-order reduction of the workgroup partials;
 //   k_ls_finalize : one workgroup: the finished column's norm, scale and
 //                   breakdown test, H_bar's column from beta, beta's column of
@@ -46,9 +47,9 @@ namespace foa {
 // the whole workgroup (it synchronises).
 //
 // Unit and tile are those of the blocked passes (foa_block.hip): BROWS rows of a
-// panel (64 with an FP32 basis, 32 with an FP64 one), lane l of a wavefront holding
-// the 16-byte chunk l / 4 of column l % 4 of each of its QW groups of four of the
-// q final columns.  Phase 1 sums the tile's rows against sigma o w and sigma o z
+// panel (64 with an FP32 basis; 32 with an FP64 one, both halves up to 2 groups),
+// lane l of a wavefront holding the 16-byte chunk l / 4 of column l % 4 of each of
+// its QW groups of four of the q final columns.  Phase 1 sums the tile's rows against sigma o w and sigma o z
 // (FMA per lane, DPP over the quad, LDS over the wavefronts); the update rows,
 // contiguous per wavefront, read the pending column, the snapshot copy and the
 // new snapshot; phase 2 forms the column sums on v_mfma_f64_4x4x4, whose four
@@ -782,9 +783,9 @@ __device__ inline void ls_finalize_body(const LsSmall &a) {
   if (hf) {
     const int c = q;  // 0-based index of the new pending column
     const double sk = hu ? a.sigma[q0] : 0.0;
-    // FP32 basis: E w.  the product over the earlier final
-    // columns is there; the finished column q0 adds w_q0 E[i, q0] to
-    // rows i < q0 and the whole row q0, sum_l E[q0, l] w_l.
+    // FP32 basis: E w.  The product over the earlier final columns is there; the
+    // finished column q0 adds w_q0 E[i, q0] to rows i < q0 and the whole row q0,
+    // sum_l E[q0, l] w_l.
     double eq0 = 0.0;
     if (a.gram && hu) {
       double t = 0.0;
