@@ -192,9 +192,9 @@ hipError_t enqueue_ls_step(foa_batch_s *b, bool x_f64, hipStream_t s, int kmax) 
 // All kernels of one step, enqueued on stream s (direct launches or capture).
 // Bucket mode: per pass one row-pass launch per tile bucket up to kmax, then
 // the reductions and finalize (with the next partial beta column).  Persistent
-// mode (FP32 basis): the
-// streams of up to kPersistCols columns run in one persistent launch; first
-// pushes and wider bases take the bucket launches, which skip the others.
+// mode (FP32 basis): the streams of up to kPersistCols columns run in one
+// persistent launch; first pushes and wider bases take the bucket launches,
+// which skip the others.
 hipError_t enqueue_step(foa_batch_s *b, bool x_f64, hipStream_t s, int kmax) {
   if (b->form == 1) return enqueue_ls_step(b, x_f64, s, kmax);
   const bool v64 = b->prec == FOA_PREC_F64;
